@@ -10,7 +10,7 @@ LIB = os.path.join(HERE, "liblbm.so")
 PROBE_LIB = os.path.join(HERE, "libprobe.so")
 SOURCES = ["lbm_api.hip", "k2d.hip", "k3d.hip", "surrogate.hip"]
 PROBE_SOURCES = ["probe.hip"]
-HEADERS = ["kernels.h", "lattice.h", "params.h", "launch.h", "launch_impl.h"]
+HEADERS = ["kernels.h", "faces.h", "lattice.h", "params.h", "launch.h", "launch_impl.h"]
 
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
 

@@ -209,13 +209,6 @@ __device__ __forceinline__ void gather(const typename Codec<STORE>::T *__restric
     });
 }
 
-template <int DIM, int STORE>
-__device__ __forceinline__ float gather1(const typename Codec<STORE>::T *__restrict__ fk, const Geometry &g,
-                                         int64_t p, uint32_t tw, int x, int y, int z, int i, float rr)
-{
-    return Codec<STORE>::ld(fk + slot_of<DIM>(g, p, tw, x, y, z, i), weight<DIM>(i), rr);
-}
-
 // Byte offset of population plane i within one component array, formed at
 // its point of use by one scalar multiply.  The copy through an empty asm
 // statement makes the stride opaque, so the compiler cannot hoist the 19
@@ -941,354 +934,11 @@ __global__ __launch_bounds__(256) void k_moments(const typename Codec<STORE>::T 
     });
 }
 
-// chi of eq. (23); undefined (no outflow through x_{N-1}, or flow against the
-// inlets) leaves the outlet uncorrected.
-__device__ __forceinline__ double chi_of(double qin, double qout)
-{
-    return (fabs(qout) < 1e-30 || qin * qout <= 0.0) ? 1.0 : qin / qout;
-}
+}  // namespace lbm
 
-// ---------------------------------------------------------------------------
-// eq. (23) from the sums the node update left in acc (this step's parity):
-// every thread of the first face launch forms chi itself; one thread records
-// Q_in, Q' and chi and clears the sums of the other parity for the next step.
-// ---------------------------------------------------------------------------
-__device__ __forceinline__ double chi_from(const Boundary &bd, const unsigned long long *acc,
-                                           unsigned long long *next, bool record)
-{
-    const double qin = flow_unfix(acc[0]), qout = flow_unfix(acc[1]);
-    const double chi = (bd.has_outlet && bd.chi_on) ? chi_of(qin, qout) : 1.0;
-    if (record) {
-        bd.scal[SC_QIN] = qin;
-        bd.scal[SC_QOUT] = qout;
-        bd.scal[SC_CHI] = chi;
-        next[0] = 0ull;
-        next[1] = 0ull;
-    }
-    return chi;
-}
+#include "faces.h"
 
-// ---------------------------------------------------------------------------
-// The collision of the outlet column with eq. (22) for a given chi (eq. 23).
-// ---------------------------------------------------------------------------
-template <int DIM, int STORE>
-__device__ __forceinline__ void outlet_body(int blk, const typename Codec<STORE>::T *__restrict__ src,
-                                                    typename Codec<STORE>::T *__restrict__ dst,
-                                                    const uint32_t *__restrict__ type,
-                                                    const float2 *__restrict__ psi, const float2 *__restrict__ ref,
-                                                    Geometry g, Physics ph, Boundary bd, int *__restrict__ flag,
-                                                    double chi)
-{
-    using T = typename Codec<STORE>::T;
-    constexpr int Q = Lat<DIM>::Q;
-    const int r = blk * FACE_NT + threadIdx.x;
-    if (r >= bd.n_out) return;
-    const OutletRec rec = bd.out[r];
-    int x, y, z;
-    coords_of(g, rec.bN, x, y, z);
-    const uint32_t tw = type[rec.bN];
-    const int64_t p = pidx(g, x, y, DIM == 3 ? z : -1);
-    float fa[Q], fb[Q];
-    const float2 rf = ref[rec.bN];
-    gather<DIM, STORE>(src, g, p, tw, x, y, z, fa, rf.x);
-    gather<DIM, STORE>(src + (int64_t)Q * g.Ppad, g, p, tw, x, y, z, fb, rf.y);
-    float r1, r2, J1[3], J2[3];
-    moments_of<DIM>(fa, r1, J1);
-    moments_of<DIM>(fb, r2, J2);
-    const float *fF = bd.faceF + (int64_t)rec.slotN * 6;
-    float F1[3] = {fF[0], fF[1], fF[2]}, F2[3] = {fF[3], fF[4], fF[5]}, u[3];
-    const float rt = r1 + r2;
-    static_for<3>([&](auto dc) {
-        constexpr int d = decltype(dc)::value;
-        u[d] = (J1[d] + J2[d] + 0.5f * (F1[d] + F2[d])) / rt;
-    });
-    if (rec.slotP >= 0) {
-        // eq. (22): the outward velocity is chi times that of x_{N-1}
-        const float un = (float)(chi * (double)bd.faceU[rec.slotP]) * bd.out_sign;
-        if (bd.out_axis == 0) u[0] = un;
-        else if (bd.out_axis == 1) u[1] = un;
-        else u[2] = un;
-    }
-    if (!(rt > 0.0f) || !isfinite(rt) || !isfinite(u[0] + u[1] + u[2])) *flag = 1;
-    // reference density of the node that reads population i next step
-    auto dest_psi = [&](auto ic) -> float2 {
-        constexpr int i = decltype(ic)::value;
-        if constexpr (!Codec<STORE>::REF) return make_float2(0.0f, 0.0f);
-        if ((tw >> Lat<DIM>::OPP[i]) & 1u) return psi[rec.bN];
-        const int qx = map_axis(x + Lat<DIM>::E[i][0], g.n[0], g.periodic[0]);
-        const int qy = map_axis(y + Lat<DIM>::E[i][1], g.n[1], g.periodic[1]);
-        const int qz = DIM == 3 ? map_axis(z + Lat<DIM>::E[i][2], g.n[2], g.periodic[2]) : 0;
-        return psi[(int64_t)qx + (int64_t)g.n[0] * ((int64_t)qy + (int64_t)g.n[1] * qz)];
-    };
-    float fo[Q];
-    PairF<DIM> q;
-    to_pairs<DIM>(fa, q);
-    const Rates s1 = {ph.se[0], ph.seps[0], ph.sq, ph.snu[0]};
-    collide_pairs<DIM, STORE == 0>(q, r1, J1, u, F1, s1, fo);
-    static_for<Q>([&](auto ic) {
-        constexpr int i = decltype(ic)::value;
-        Codec<STORE>::st(dst + (int64_t)i * g.Ppad + p, fo[i], weight<DIM>(i), dest_psi(ic).x);
-    });
-    to_pairs<DIM>(fb, q);
-    const Rates s2 = {ph.se[1], ph.seps[1], ph.sq, ph.snu[1]};
-    collide_pairs<DIM, STORE == 0>(q, r2, J2, u, F2, s2, fo);
-    T *d2 = dst + (int64_t)Q * g.Ppad;
-    static_for<Q>([&](auto ic) {
-        constexpr int i = decltype(ic)::value;
-        Codec<STORE>::st(d2 + (int64_t)i * g.Ppad + p, fo[i], weight<DIM>(i), dest_psi(ic).y);
-    });
-}
-
-// ---------------------------------------------------------------------------
-// k_inlet: blocks [0, nb_in) rebuild the entering populations of the inlet
-// nodes (eqs. 13-19); blocks [nb_in, ...) sum u.n_o over x_{N-1} (eq. 21).
-// ---------------------------------------------------------------------------
-template <int DIM, int STORE>
-__device__ __forceinline__ void inlet_body(int blk, typename Codec<STORE>::T *__restrict__ dst,
-                                                   const uint32_t *__restrict__ type,
-                                                   const float2 *__restrict__ psi, Geometry g, Boundary bd,
-                                                   int nb_in)
-{
-    using T = typename Codec<STORE>::T;
-    constexpr int Q = Lat<DIM>::Q;
-    __shared__ double s_red[2 * FACE_NT / 64];
-    if ((int)blk < nb_in) {
-        const int r = blk * FACE_NT + threadIdx.x;
-        if (r >= bd.n_in) return;
-        const InletRec rec = bd.in[r];
-        const Patch pt = bd.patch[rec.patch];
-        int x1, y1, z1, x2, y2, z2;
-        coords_of(g, rec.b1, x1, y1, z1);
-        coords_of(g, rec.b2, x2, y2, z2);
-        const uint32_t tw1 = type[rec.b1], tw2 = type[rec.b2];
-        const int64_t p1 = pidx(g, x1, y1, DIM == 3 ? z1 : -1);
-        const int64_t p2 = pidx(g, x2, y2, DIM == 3 ? z2 : -1);
-        const bool x2_fluid = !(tw2 & T_SOLID);
-        const float un = pt.sign * pt.u_n;
-        const float up[3] = {pt.axis == 0 ? un : 0.0f, pt.axis == 1 ? un : 0.0f, pt.axis == 2 ? un : 0.0f};
-        // rho_k(x2), u(x2) from the streamed f at t+1 with this step's force
-        float fa2[Q], fb2[Q], ra2 = 0.f, rb2 = 0.f, u2[3] = {0.f, 0.f, 0.f};
-        if (x2_fluid) {
-            float Ja[3], Jb[3];
-            // f(t+1) is read with psi(t) as the reference density
-            const float2 r2f = psi[rec.b2];
-            gather<DIM, STORE>(dst, g, p2, tw2, x2, y2, z2, fa2, r2f.x);
-            gather<DIM, STORE>(dst + (int64_t)Q * g.Ppad, g, p2, tw2, x2, y2, z2, fb2, r2f.y);
-            moments_of<DIM>(fa2, ra2, Ja);
-            moments_of<DIM>(fb2, rb2, Jb);
-            const float *F2 = bd.faceF + (int64_t)rec.slot2 * 6;
-            const float rt = ra2 + rb2;
-            static_for<3>([&](auto dc) {
-                constexpr int d = decltype(dc)::value;
-                u2[d] = (Ja[d] + Jb[d] + 0.5f * (F2[d] + F2[3 + d])) / rt;
-            });
-        } else {
-            static_for<Q>([&](auto ic) { fa2[decltype(ic)::value] = 0.0f; fb2[decltype(ic)::value] = 0.0f; });
-        }
-        const float *F1 = bd.faceF + (int64_t)rec.slot1 * 6;
-        static_for<2>([&](auto kc) {
-            constexpr int k = decltype(kc)::value;
-            T *dk = dst + (int64_t)k * Q * g.Ppad;
-            const float rho_p = pt.rho[k];
-            const float rho2 = k == 0 ? ra2 : rb2;
-            const float(&f2)[Q] = k == 0 ? fa2 : fb2;
-            float f1[Q];
-            const float2 r1f = psi[rec.b1];
-            const float rref1 = k == 0 ? r1f.x : r1f.y;
-            // the populations that leave x1: the entering ones are replaced
-            // below, so their ghost slots (a line of their own when the face
-            // is normal to the fastest memory axis) are not read
-            static_for<Q>([&](auto ic) {
-                constexpr int i = decltype(ic)::value;
-                f1[i] = e_axis<DIM>(i, pt.axis) * pt.sign > 0
-                            ? 0.0f
-                            : gather1<DIM, STORE>(dk, g, p1, tw1, x1, y1, z1, i, rref1);
-            });
-            // eq. (13)/(14) on the populations entering the domain
-            static_for<Q>([&](auto ic) {
-                constexpr int i = decltype(ic)::value;
-                if (e_axis<DIM>(i, pt.axis) * pt.sign > 0) {
-                    const float neq = x2_fluid ? f2[i] - feq<DIM>(i, rho2, u2) : 0.0f;
-                    f1[i] = feq<DIM>(i, rho_p, up) + neq;
-                }
-            });
-            if (pt.alpha_on) {
-                // eqs. (15)-(19): alpha_i = w_i sum_d e_id dJ_d / D_d over the
-                // entering set, dJ = rho_k^p u^p - (sum_i e_i f_i + F^k/2)
-                float rr, J[3], D[3] = {0.f, 0.f, 0.f};
-                moments_of<DIM>(f1, rr, J);
-                static_for<Q>([&](auto ic) {
-                    constexpr int i = decltype(ic)::value;
-                    if (e_axis<DIM>(i, pt.axis) * pt.sign > 0) {
-                        static_for<3>([&](auto dc) {
-                            constexpr int d = decltype(dc)::value;
-                            constexpr int e = Lat<DIM>::E[i][d];
-                            if constexpr (e != 0) D[d] += weight<DIM>(i);
-                        });
-                    }
-                });
-                float dJ[3];
-                static_for<3>([&](auto dc) {
-                    constexpr int d = decltype(dc)::value;
-                    dJ[d] = rho_p * up[d] - (J[d] + 0.5f * F1[3 * k + d]);
-                });
-                static_for<Q>([&](auto ic) {
-                    constexpr int i = decltype(ic)::value;
-                    if (e_axis<DIM>(i, pt.axis) * pt.sign > 0) {
-                        float a = 0.0f;
-                        static_for<3>([&](auto dc) {
-                            constexpr int d = decltype(dc)::value;
-                            constexpr int e = Lat<DIM>::E[i][d];
-                            if constexpr (e != 0) a += weight<DIM>(i) * (float)e * dJ[d] / D[d];
-                        });
-                        f1[i] += a;
-                    }
-                });
-            }
-            static_for<Q>([&](auto ic) {
-                constexpr int i = decltype(ic)::value;
-                if (e_axis<DIM>(i, pt.axis) * pt.sign > 0)
-                    Codec<STORE>::st(dk + (int64_t)i * g.Ppad + src_slot<DIM>(g, x1, y1, z1, i), f1[i],
-                                     weight<DIM>(i), rref1);
-            });
-        });
-        return;
-    }
-    // eq. (21): partial sums of the outward normal velocity over x_{N-1}
-    const int r = (blk - nb_in) * FACE_NT + threadIdx.x;
-    double su = 0.0, cnt = 0.0;
-    if (r < bd.n_out) {
-        const OutletRec rec = bd.out[r];
-        if (rec.slotP >= 0) {
-            int x, y, z;
-            coords_of(g, rec.bP, x, y, z);
-            const uint32_t tw = type[rec.bP];
-            const int64_t p = pidx(g, x, y, DIM == 3 ? z : -1);
-            float rt = 0.f, J = 0.f;
-            static_for<2>([&](auto kc) {
-                constexpr int k = decltype(kc)::value;
-                float f[Q], rk, Jk[3];
-                const float2 rpf = psi[rec.bP];
-                gather<DIM, STORE>(dst + (int64_t)k * Q * g.Ppad, g, p, tw, x, y, z, f, k == 0 ? rpf.x : rpf.y);
-                moments_of<DIM>(f, rk, Jk);
-                rt += rk;
-                J += bd.out_sign * pick3(Jk, bd.out_axis);
-            });
-            const float *F = bd.faceF + (int64_t)rec.slotP * 6;
-            const float Fa[3] = {F[0], F[1], F[2]}, Fb[3] = {F[3], F[4], F[5]};
-            J += 0.5f * bd.out_sign * (pick3(Fa, bd.out_axis) + pick3(Fb, bd.out_axis));
-            su = (double)(J / rt);
-            cnt = 1.0;
-        }
-    }
-    block_sum2<FACE_NT>(su, cnt, s_red);
-    if (threadIdx.x == 0) {
-        bd.ucpart[2 * (blk - nb_in)] = su;
-        bd.ucpart[2 * (blk - nb_in) + 1] = cnt;
-    }
-}
-
-template <int DIM, int STORE>
-__global__ __launch_bounds__(FACE_NT) void k_inlet(typename Codec<STORE>::T *__restrict__ dst,
-                                                   const uint32_t *__restrict__ type,
-                                                   const float2 *__restrict__ psi, Geometry g, Boundary bd,
-                                                   int nb_in)
-{
-    inlet_body<DIM, STORE>((int)blockIdx.x, dst, type, psi, g, bd, nb_in);
-}
-
-// ---------------------------------------------------------------------------
-// k_faces: the first launch after the node update.  chi from this step's
-// sums; blocks [0, nb_out) collide the outlet column, blocks [nb_out,
-// nb_out + nb_in) rebuild inlet nodes (only when no inlet node pulls from the
-// outlet column, checked at creation, so the two sets are independent).
-// ---------------------------------------------------------------------------
-template <int DIM, int STORE>
-__global__ __launch_bounds__(FACE_NT) void k_faces(const typename Codec<STORE>::T *__restrict__ src,
-                                                   typename Codec<STORE>::T *__restrict__ dst,
-                                                   const uint32_t *__restrict__ type,
-                                                   const float2 *__restrict__ psi, const float2 *__restrict__ ref,
-                                                   Geometry g, Physics ph, Boundary bd, int *__restrict__ flag,
-                                                   const unsigned long long *__restrict__ acc,
-                                                   unsigned long long *__restrict__ next, int nb_out, int nb_in)
-{
-    const int blk = (int)blockIdx.x;
-    const double chi = chi_from(bd, acc, next, blk == 0 && threadIdx.x == 0);
-    if (blk < nb_out) outlet_body<DIM, STORE>(blk, src, dst, type, psi, ref, g, ph, bd, flag, chi);
-    else if (blk - nb_out < nb_in) inlet_body<DIM, STORE>(blk - nb_out, dst, type, psi, g, bd, nb_in);
-}
-
-// ---------------------------------------------------------------------------
-// k_outlet_fill: eq. (20) for the populations entering through the outlet.
-// ---------------------------------------------------------------------------
-template <int DIM, int STORE>
-__device__ __forceinline__ void outlet_fill_body(int blk, const typename Codec<STORE>::T *__restrict__ src,
-                                                         typename Codec<STORE>::T *__restrict__ dst,
-                                                         const uint32_t *__restrict__ type,
-                                                         const float2 *__restrict__ psi,
-                                                         const float2 *__restrict__ ref, Geometry g, Boundary bd)
-{
-    using T = typename Codec<STORE>::T;
-    constexpr int Q = Lat<DIM>::Q;
-    __shared__ double s_red[2 * FACE_NT / 64];
-    double su, cnt;
-    reduce_partials<FACE_NT>(bd.ucpart, bd.n_ucpart, su, cnt, s_red);
-    double Uc = cnt > 0.0 ? su / cnt : 0.0;
-    const bool clamped = Uc < 0.0;
-    if (clamped) Uc = 0.0;
-    if (blk == 0 && threadIdx.x == 0) {
-        bd.scal[SC_UC] = Uc;
-        if (clamped) bd.scal[SC_CLAMPS] += 1.0;
-    }
-    const int r = blk * FACE_NT + threadIdx.x;
-    if (r >= bd.n_out) return;
-    const OutletRec rec = bd.out[r];
-    int x, y, z;
-    coords_of(g, rec.bN, x, y, z);
-    int xp = 0, yp = 0, zp = 0;
-    uint32_t twp = 0;
-    int64_t pp = 0;
-    if (rec.slotP >= 0) {
-        coords_of(g, rec.bP, xp, yp, zp);
-        twp = type[rec.bP];
-        pp = pidx(g, xp, yp, DIM == 3 ? zp : -1);
-    }
-    const float uc = (float)Uc;
-    // f(t) of x_N from the FP32 history; f(t+1) is stored for x_N with
-    // psi(t) as its reference density, and x' is read at t+1 with psi(t)
-    const float2 rt1 = psi[rec.bN];
-    const float2 rp = rec.slotP >= 0 ? psi[rec.bP] : make_float2(0.0f, 0.0f);
-    static_for<2>([&](auto kc) {
-        constexpr int k = decltype(kc)::value;
-        T *dk = dst + (int64_t)k * Q * g.Ppad;
-        const float r1 = k == 0 ? rt1.x : rt1.y, rpk = k == 0 ? rp.x : rp.y;
-        static_for<Q>([&](auto ic) {
-            constexpr int i = decltype(ic)::value;
-            if (e_axis<DIM>(i, bd.out_axis) * bd.out_sign < 0) {
-                const int64_t a = (int64_t)i * g.Ppad + src_slot<DIM>(g, x, y, z, i);
-                float *h = bd.hist + ((int64_t)k * Q + i) * bd.n_slots + rec.slotN;
-                const float prev = *h;
-                float v = prev;
-                if (rec.slotP >= 0) {
-                    const float fp = gather1<DIM, STORE>(dk, g, pp, twp, xp, yp, zp, i, rpk);
-                    v = (prev + uc * fp) / (1.0f + uc);
-                }
-                *h = v;
-                Codec<STORE>::st(dk + a, v, weight<DIM>(i), r1);
-            }
-        });
-    });
-}
-
-template <int DIM, int STORE>
-__global__ __launch_bounds__(FACE_NT) void k_outlet_fill(const typename Codec<STORE>::T *__restrict__ src,
-                                                         typename Codec<STORE>::T *__restrict__ dst,
-                                                         const uint32_t *__restrict__ type,
-                                                         const float2 *__restrict__ psi,
-                                                         const float2 *__restrict__ ref, Geometry g, Boundary bd)
-{
-    outlet_fill_body<DIM, STORE>((int)blockIdx.x, src, dst, type, psi, ref, g, bd);
-}
+namespace lbm {
 
 // ---------------------------------------------------------------------------
 // State exchange: canonical f[2][Q][N] (FP64) <-> population slots.
@@ -1501,25 +1151,17 @@ void k_main_batch(BatchTab t, int cur)
     }
 }
 
-// eq. (23) from the sums of each member, one thread per member
-static __global__ __launch_bounds__(64) void k_chi_batch(BatchTab t, int cur)
-{
-    const int i = (int)(blockIdx.x * 64 + threadIdx.x);
-    if (i >= t.n) return;
-    const Boundary bd = const_copy(&((CMember *)(t.m + i))->bd);
-    (void)chi_from(bd, bd.qacc + 2 * cur, bd.qacc + 2 * (cur ^ 1), true);
-}
-
 template <int DIM, int STORE>
-__global__ __launch_bounds__(FACE_NT) void k_outlet_batch(BatchTab t, int cur)
+__global__ __launch_bounds__(FACE_NT) void k_faces_batch(BatchTab t, int cur)
 {
     using T = typename Codec<STORE>::T;
-    const int i = member_of(t.out0, t.n, (int)blockIdx.x);
+    const int i = member_of(t.fac0, t.n, (int)blockIdx.x);
     CMember *m = (CMember *)(t.m + i);
     const Boundary bd = const_copy(&m->bd);
-    outlet_body<DIM, STORE>((int)blockIdx.x - t.out0[i], (const T *)m->f[cur], (T *)m->f[cur ^ 1], m->type,
-                            (const float2 *)m->psi[cur], (const float2 *)m->psi[cur ^ 1], const_copy(&m->g),
-                            const_copy(&m->ph), bd, m->flag, bd.scal[SC_CHI]);
+    faces_body<DIM, STORE>((int)blockIdx.x - t.fac0[i], (const T *)m->f[cur], (T *)m->f[cur ^ 1],
+                           (const float2 *)m->psi[cur], (const float2 *)m->psi[cur ^ 1], const_copy(&m->g),
+                           const_copy(&m->ph), bd, m->flag, bd.qacc + 2 * cur, bd.qacc + 2 * (cur ^ 1), m->nb_coll,
+                           m->nb_in_early);
 }
 
 template <int DIM, int STORE>
@@ -1528,8 +1170,8 @@ __global__ __launch_bounds__(FACE_NT) void k_inlet_batch(BatchTab t, int cur)
     using T = typename Codec<STORE>::T;
     const int i = member_of(t.inl0, t.n, (int)blockIdx.x);
     CMember *m = (CMember *)(t.m + i);
-    inlet_body<DIM, STORE>((int)blockIdx.x - t.inl0[i], (T *)m->f[cur ^ 1], m->type, (const float2 *)m->psi[cur],
-                           const_copy(&m->g), const_copy(&m->bd), m->nb_in);
+    inlet_uc_body<DIM, STORE>((int)blockIdx.x - t.inl0[i], (T *)m->f[cur ^ 1], (const float2 *)m->psi[cur],
+                              const_copy(&m->g), const_copy(&m->bd), m->nb_in_late);
 }
 
 template <int DIM, int STORE>
@@ -1538,8 +1180,7 @@ __global__ __launch_bounds__(FACE_NT) void k_outlet_fill_batch(BatchTab t, int c
     using T = typename Codec<STORE>::T;
     const int i = member_of(t.fill0, t.n, (int)blockIdx.x);
     CMember *m = (CMember *)(t.m + i);
-    outlet_fill_body<DIM, STORE>((int)blockIdx.x - t.fill0[i], (const T *)m->f[cur], (T *)m->f[cur ^ 1], m->type,
-                                 (const float2 *)m->psi[cur], (const float2 *)m->psi[cur ^ 1],
+    outlet_fill_body<DIM, STORE>((int)blockIdx.x - t.fill0[i], (T *)m->f[cur ^ 1], (const float2 *)m->psi[cur],
                                  const_copy(&m->g), const_copy(&m->bd));
 }
 

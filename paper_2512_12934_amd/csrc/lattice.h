@@ -146,6 +146,25 @@ template <int DIM> struct Pairs {
     }
 };
 
+// Direction of lane j where lanes hold one direction each (the face kernels):
+// opposite directions in neighbouring lanes, axis pairs before diagonal ones,
+// the rest population last.
+template <int DIM>
+__host__ __device__ constexpr int lane_dir(int j)
+{
+    return DIM == 3 ? (j < 18 ? j + 1 : 0) : (int)((0x086754231ull >> (4 * j)) & 15);
+}
+template <int DIM>
+constexpr bool lane_dirs_ok()
+{
+    for (int j = 0; j + 1 < Lat<DIM>::Q; j += 2) {
+        if (Lat<DIM>::OPP[lane_dir<DIM>(j)] != lane_dir<DIM>(j + 1)) return false;
+        if ((e2_of<DIM>(lane_dir<DIM>(j)) == 1) != (j < 2 * DIM)) return false;
+    }
+    return lane_dir<DIM>(Lat<DIM>::Q - 1) == 0;
+}
+static_assert(lane_dirs_ok<2>() && lane_dirs_ok<3>(), "lane order of the directions");
+
 // Relaxation rates of one component (eq. 4): s_rho = s_j = 1.
 struct Rates {
     float se, seps, sq, snu;

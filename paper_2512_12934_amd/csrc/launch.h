@@ -77,7 +77,7 @@ struct StepArgs {
 struct BatchArgs {
     BatchTab t;
     int cur;
-    unsigned g_psi, g_main, g_chi, g_out, g_inl, g_fill;
+    unsigned g_psi, g_main, g_fac, g_inl, g_fill;
     hipStream_t stream;
 };
 

@@ -40,9 +40,8 @@ void launch_batch_cfg(const BatchArgs &b)
     if (b.g_main)
         hipLaunchKernelGGL((k_main_batch<DIM, STORE, c.psrc, c.tx, c.ty, c.w, c.zc, c.keepb>), dim3(b.g_main),
                            dim3(256), 0, b.stream, b.t, b.cur);
-    if (b.g_chi) hipLaunchKernelGGL(k_chi_batch, dim3(b.g_chi), dim3(64), 0, b.stream, b.t, b.cur);
-    if (b.g_out)
-        hipLaunchKernelGGL((k_outlet_batch<DIM, STORE>), dim3(b.g_out), dim3(FACE_NT), 0, b.stream, b.t, b.cur);
+    if (b.g_fac)
+        hipLaunchKernelGGL((k_faces_batch<DIM, STORE>), dim3(b.g_fac), dim3(FACE_NT), 0, b.stream, b.t, b.cur);
     if (b.g_inl)
         hipLaunchKernelGGL((k_inlet_batch<DIM, STORE>), dim3(b.g_inl), dim3(FACE_NT), 0, b.stream, b.t, b.cur);
     if (b.g_fill)
@@ -108,8 +107,8 @@ void Launcher<DIM>::faces(int storage, const StepArgs &a, int nb_out, int nb_in)
     with_store(storage, [&](auto sc) {
         using T = LBM_STORE_T(sc);
         hipLaunchKernelGGL((k_faces<DIM, decltype(sc)::value>), dim3(nb), dim3(FACE_NT), 0, a.stream,
-                           (const T *)a.src, (T *)a.dst, a.type, (const float2 *)a.psi, a.ref, a.g, a.ph, a.bd,
-                           a.flag, a.qacc, a.qnext, nb_out, nb_in);
+                           (const T *)a.src, (T *)a.dst, (const float2 *)a.psi, a.ref, a.g, a.ph, a.bd, a.flag, a.qacc,
+                           a.qnext, nb_out, nb_in);
     });
 }
 
@@ -119,7 +118,7 @@ void Launcher<DIM>::inlet(int storage, const StepArgs &a, unsigned nb, int nb_in
     with_store(storage, [&](auto sc) {
         using T = LBM_STORE_T(sc);
         hipLaunchKernelGGL((k_inlet<DIM, decltype(sc)::value>), dim3(nb), dim3(FACE_NT), 0, a.stream, (T *)a.dst,
-                           a.type, (const float2 *)a.psi, a.g, a.bd, nb_in);
+                           (const float2 *)a.psi, a.g, a.bd, nb_in);
     });
 }
 
@@ -129,7 +128,7 @@ void Launcher<DIM>::outlet_fill(int storage, const StepArgs &a, unsigned nb)
     with_store(storage, [&](auto sc) {
         using T = LBM_STORE_T(sc);
         hipLaunchKernelGGL((k_outlet_fill<DIM, decltype(sc)::value>), dim3(nb), dim3(FACE_NT), 0, a.stream,
-                           (const T *)a.src, (T *)a.dst, a.type, (const float2 *)a.psi, a.ref, a.g, a.bd);
+                           (T *)a.dst, (const float2 *)a.psi, a.g, a.bd);
     });
 }
 

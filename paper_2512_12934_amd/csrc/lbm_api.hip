@@ -38,11 +38,13 @@ struct Layout {
     std::vector<int> item_list;    // their tile indices
     int64_t grid_main = 0;         // launched blocks (a multiple of 8 * MAIN_XCD_GROUP)
     int64_t n_slots = 0, n_in = 0, n_out = 0;
-    int nb_in = 0, nb_out = 0;
+    int nb_in = 0, nb_out = 0;     // face-kernel blocks of the inlet nodes and of the outlet column
+    int nb_fill = 0;               // blocks of the outlet fill
+    int face_pass = 1;             // see FACE_NT
     int nb_mass = 0;
     bool boundary = false;
     // byte offsets into the workspace
-    size_t o_fA, o_fB, o_type, o_bslot, o_faceF, o_faceU, o_in, o_out, o_qacc, o_ucpart, o_scal,
+    size_t o_fA, o_fB, o_type, o_bslot, o_faceF, o_faceU, o_in, o_out, o_in_tab, o_out_tab, o_qacc, o_ucpart, o_scal,
         o_flag, o_mpart, o_mout, o_patch, o_psi[2], o_items, o_hist, o_wallc, total;
     bool moving = false;
     int cfg = 0;                   // node-update configuration (launch.h)
@@ -329,8 +331,9 @@ std::string build_maps(const lbm_config *c, Maps &m)
             m.type[b2] |= T_X2 | ((uint32_t)q << T_PATCH_SHIFT);
         }
         InletRec r{};
-        r.b1 = b;
-        r.b2 = b2;
+        r.x2_fluid = c->solid[b2] ? 0 : 1;
+        r.b1 = (int)b;
+        r.b2 = r.x2_fluid ? (int)b2 : r.b1;
         r.patch = q;
         m.in.push_back(r);
     }
@@ -344,8 +347,8 @@ std::string build_maps(const lbm_config *c, Maps &m)
             const int64_t bp = (int64_t)xp[0] + (int64_t)c->n[0] * ((int64_t)xp[1] + (int64_t)c->n[1] * xp[2]);
             m.type[b] |= T_OUTLET;
             OutletRec r{};
-            r.bN = b;
-            r.bP = bp;
+            r.bN = (int)b;
+            r.bP = (int)bp;
             if (!c->solid[bp]) {
                 if (m.type[bp] & (T_INLET | T_OUTLET)) return "the outlet is less than two nodes from an open face";
                 m.type[bp] |= T_XPRIME;
@@ -373,15 +376,15 @@ std::string build_maps(const lbm_config *c, Maps &m)
             return "a moving wall next to the outlet column is not supported";
     for (auto &r : m.in) {
         r.slot1 = m.bslot[r.b1];
-        r.slot2 = c->solid[r.b2] ? r.slot1 : m.bslot[r.b2];
+        r.slot2 = m.bslot[r.b2];
     }
     // does the inlet rule read a population that the outlet collision
     // writes?  It reads the streamed populations of x1 and x2, so it
     // depends on the outlet column when one of them pulls from it
     for (const auto &r : m.in) {
         for (int k = 0; k < 2 && !m.inlet_pulls_outlet; k++) {
+            if (k == 1 && !r.x2_fluid) continue;
             const int64_t b = k == 0 ? r.b1 : r.b2;
-            if (c->solid[b]) continue;
             const int xc[3] = {(int)(b % c->n[0]), (int)((b / c->n[0]) % c->n[1]),
                                (int)(b / ((int64_t)c->n[0] * c->n[1]))};
             for (int i = 0; i < Q; i++) {
@@ -414,6 +417,76 @@ int default_cfg(const lbm_config *c)
 {
     (void)c;
     return 0;
+}
+
+// Fills the records' padded indices and the slot tables of the face kernels.
+template <int DIM>
+void face_tables(const Geometry &g, Maps &m, std::vector<int> &in_tab, std::vector<int> &out_tab)
+{
+    constexpr int Q = Lat<DIM>::Q;
+    auto coords = [&](int b, int *x) {
+        x[0] = b % g.n[0];
+        x[1] = b / g.n[0] % g.n[1];
+        x[2] = b / (g.n[0] * g.n[1]);
+    };
+    auto padded = [&](const int *x) -> int64_t {
+        return (int64_t)(x[0] + g.xoff) +
+               (int64_t)g.P[0] * ((int64_t)(x[1] + 1) + (DIM == 3 ? (int64_t)g.P[1] * (x[2] + 1) : 0));
+    };
+    // the slot that streams population i into box node b: its own slot of
+    // the opposite direction on bounce-back, else that of x - e_i (wrapped on
+    // periodic axes; the padding holds what the open faces supply)
+    auto slot = [&](int b, int i) -> int {
+        int x[3];
+        coords(b, x);
+        if ((m.type[b] >> i) & 1u) return (int)((int64_t)Lat<DIM>::OPP[i] * g.Ppad + padded(x));
+        for (int a = 0; a < DIM; a++) {
+            x[a] -= Lat<DIM>::E[i][a];
+            if (g.periodic[a]) x[a] = (x[a] + g.n[a]) % g.n[a];
+        }
+        return (int)((int64_t)i * g.Ppad + padded(x));
+    };
+    // the node that reads what box node b stores for direction i (the mirror
+    // image beyond an open face, where nobody reads it)
+    auto reader = [&](int b, int i) -> int {
+        if ((m.type[b] >> Lat<DIM>::OPP[i]) & 1u) return b;
+        int x[3];
+        coords(b, x);
+        for (int a = 0; a < DIM; a++) {
+            x[a] += Lat<DIM>::E[i][a];
+            if (x[a] < 0) x[a] = g.periodic[a] ? x[a] + g.n[a] : -1 - x[a];
+            else if (x[a] >= g.n[a]) x[a] = g.periodic[a] ? x[a] - g.n[a] : 2 * g.n[a] - 1 - x[a];
+        }
+        return x[0] + g.n[0] * (x[1] + g.n[1] * x[2]);
+    };
+    in_tab.resize(m.in.size() * 2 * Q);
+    out_tab.resize(m.out.size() * 3 * Q);
+    for (size_t r = 0; r < m.in.size(); r++)
+        for (int j = 0; j < Q; j++) {
+            in_tab[(2 * r) * Q + j] = slot(m.in[r].b1, lane_dir<DIM>(j));
+            in_tab[(2 * r + 1) * Q + j] = slot(m.in[r].b2, lane_dir<DIM>(j));
+        }
+    for (size_t r = 0; r < m.out.size(); r++) {
+        int x[3];
+        coords(m.out[r].bN, x);
+        m.out[r].pN = (int)padded(x);
+        for (int j = 0; j < Q; j++) {
+            out_tab[(3 * r) * Q + j] = slot(m.out[r].bN, lane_dir<DIM>(j));
+            out_tab[(3 * r + 1) * Q + j] = slot(m.out[r].bP, lane_dir<DIM>(j));
+            out_tab[(3 * r + 2) * Q + j] = reader(m.out[r].bN, lane_dir<DIM>(j));
+        }
+    }
+}
+
+// Byte m: the lane of the m-th direction that enters through the outlet.
+template <int DIM>
+uint64_t entering_lanes(int axis, int sign)
+{
+    uint64_t v = 0;
+    int n = 0;
+    for (int j = 0; j < Lat<DIM>::Q; j++)
+        if (Lat<DIM>::E[lane_dir<DIM>(j)][axis] * sign < 0) v |= (uint64_t)j << (8 * n++);
+    return v;
 }
 
 Layout make_layout(const Canon &k, const Maps &m)
@@ -494,8 +567,12 @@ Layout make_layout(const Canon &k, const Maps &m)
     for (auto s : m.bslot) L.n_slots = std::max<int64_t>(L.n_slots, s + 1);
     L.moving = m.moving;
     L.boundary = L.n_in > 0 || c->has_outlet;
-    L.nb_in = (int)((L.n_in + FACE_NT - 1) / FACE_NT);
-    L.nb_out = (int)((L.n_out + FACE_NT - 1) / FACE_NT);
+    L.face_pass = std::max(L.n_in, L.n_out) > FACE_WIDE ? 4 : 1;
+    const int per_block = FACE_NT / 64 * (c->dim == 3 ? FaceMap<3>::NPW : FaceMap<2>::NPW) * L.face_pass;
+    const int per_fill = c->dim == 3 ? FillMap<3>::NPB : FillMap<2>::NPB;
+    L.nb_in = (int)((L.n_in + per_block - 1) / per_block);
+    L.nb_out = (int)((L.n_out + per_block - 1) / per_block);
+    L.nb_fill = (int)((L.n_out + per_fill - 1) / per_fill);
     L.inlet_early = !(c->has_outlet && c->outlet.chi_on) || !m.inlet_pulls_outlet;
     L.nb_mass = (int)std::min<int64_t>(1024, (g.N + 255) / 256);
     const size_t fbytes = (size_t)2 * L.Q * g.Ppad * (L.storage == LBM_STORE_F32 ? 4 : 2);
@@ -509,6 +586,8 @@ Layout make_layout(const Canon &k, const Maps &m)
     L.o_faceU = take((size_t)L.n_slots * 4);
     L.o_in = take((size_t)L.n_in * sizeof(InletRec));
     L.o_out = take((size_t)L.n_out * sizeof(OutletRec));
+    L.o_in_tab = take((size_t)L.n_in * 2 * L.Q * 4);
+    L.o_out_tab = take((size_t)L.n_out * 3 * L.Q * 4);
     L.o_qacc = take(4 * sizeof(unsigned long long));
     L.o_ucpart = take((size_t)std::max(L.nb_out, 1) * 16);
     L.o_scal = take(SC_COUNT * 8);
@@ -711,7 +790,7 @@ template <int DIM> struct Ops {
             }
             if (L.nb_out > 0) {
                 if (ev) (void)hipEventRecord(ev[6], c->stream);
-                Lx::outlet_fill(L.storage, a, (unsigned)L.nb_out);
+                Lx::outlet_fill(L.storage, a, (unsigned)L.nb_fill);
                 if (ev) (void)hipEventRecord(ev[7], c->stream);
             }
         }
@@ -885,6 +964,14 @@ lbm_status lbm_create(const lbm_config *cfg, void *dev_ws, size_t ws_bytes, void
     bd.qacc = (unsigned long long *)(ws + L.o_qacc);
     bd.ucpart = (double *)(ws + L.o_ucpart);
     bd.n_ucpart = L.nb_out;
+    bd.in_tab = (const int *)(ws + L.o_in_tab);
+    bd.out_tab = (const int *)(ws + L.o_out_tab);
+    bd.out_enter = cfg->dim == 2 ? entering_lanes<2>(bd.out_axis, bd.out_sign)
+                                 : entering_lanes<3>(bd.out_axis, bd.out_sign);
+    bd.face_pass = L.face_pass;
+    std::vector<int> in_tab, out_tab;
+    if (cfg->dim == 2) face_tables<2>(L.g, m, in_tab, out_tab);
+    else face_tables<3>(L.g, m, in_tab, out_tab);
     bd.scal = (double *)(ws + L.o_scal);
     bd.patch = (const Patch *)(ws + L.o_patch);
     bd.hist = (float *)(ws + L.o_hist);
@@ -896,10 +983,14 @@ lbm_status lbm_create(const lbm_config *cfg, void *dev_ws, size_t ws_bytes, void
         HIPCHECK(c, hipMemsetAsync(ws, 0, L.total, s));
         HIPCHECK(c, hipMemcpyAsync(ws + L.o_type, m.type.data(), m.type.size() * 4, hipMemcpyHostToDevice, s));
         HIPCHECK(c, hipMemcpyAsync(ws + L.o_bslot, m.bslot.data(), m.bslot.size() * 4, hipMemcpyHostToDevice, s));
-        if (L.n_in)
+        if (L.n_in) {
             HIPCHECK(c, hipMemcpyAsync(ws + L.o_in, m.in.data(), m.in.size() * sizeof(InletRec), hipMemcpyHostToDevice, s));
-        if (L.n_out)
+            HIPCHECK(c, hipMemcpyAsync(ws + L.o_in_tab, in_tab.data(), in_tab.size() * 4, hipMemcpyHostToDevice, s));
+        }
+        if (L.n_out) {
             HIPCHECK(c, hipMemcpyAsync(ws + L.o_out, m.out.data(), m.out.size() * sizeof(OutletRec), hipMemcpyHostToDevice, s));
+            HIPCHECK(c, hipMemcpyAsync(ws + L.o_out_tab, out_tab.data(), out_tab.size() * 4, hipMemcpyHostToDevice, s));
+        }
         HIPCHECK(c, hipMemcpyAsync(ws + L.o_patch, patches, sizeof patches, hipMemcpyHostToDevice, s));
         std::vector<float> wallc;
         if (L.moving) {
@@ -1126,7 +1217,7 @@ struct lbm_batch {
     std::vector<lbm_ctx *> m;
     int dim = 0, storage = 0, cfg = 0;
     BatchTab tab{};
-    unsigned g_psi = 0, g_main = 0, g_chi = 0, g_out = 0, g_inl = 0, g_fill = 0;
+    unsigned g_psi = 0, g_main = 0, g_fac = 0, g_inl = 0, g_fill = 0;
     hipStream_t stream = nullptr;
     int cur = 0;
     int64_t steps = 0;
@@ -1200,8 +1291,7 @@ void batch_launch(lbm_batch *b, hipStream_t s)
     a.cur = b->cur;
     a.g_psi = b->g_psi;
     a.g_main = b->g_main;
-    a.g_chi = b->g_chi;
-    a.g_out = b->g_out;
+    a.g_fac = b->g_fac;
     a.g_inl = b->g_inl;
     a.g_fill = b->g_fill;
     a.stream = s;
@@ -1265,8 +1355,7 @@ lbm_status lbm_batch_create(const lbm_config *cfgs, int n, void *dev_ws, size_t 
     char *ws = (char *)dev_ws;
     size_t off = 0;
     std::vector<Member> mem(n);
-    std::vector<int> item0(n + 1, 0), psi0(n + 1, 0), out0(n + 1, 0), inl0(n + 1, 0), fill0(n + 1, 0);
-    bool faces = false;
+    std::vector<int> item0(n + 1, 0), psi0(n + 1, 0), fac0(n + 1, 0), inl0(n + 1, 0), fill0(n + 1, 0);
     for (int i = 0; i < n; i++) {
         lbm_ctx *c = nullptr;
         const lbm_status st = lbm_create(&mc[i], ws + off, bytes[i], hip_stream, &c);
@@ -1292,16 +1381,17 @@ lbm_status lbm_batch_create(const lbm_config *cfgs, int n, void *dev_ws, size_t 
         M.tiles_y = L.tiles[1];
         M.n_items = (int)L.nblocks_main;
         M.item_list = (const int *)(c->ws + L.o_items);
-        M.nb_in = L.nb_in;
-        M.nb_out = L.nb_out;
+        M.nb_coll = c->bd.has_outlet && c->bd.chi_on ? L.nb_out : 0;
+        M.nb_in_early = L.inlet_early ? L.nb_in : 0;
+        M.nb_in_late = L.nb_in - M.nb_in_early;
         M.flag = c->flag();
-        const bool chi_stage = L.boundary && c->bd.has_outlet && c->bd.chi_on;
         item0[i + 1] = item0[i] + M.n_items;
         psi0[i + 1] = psi0[i] + (L.psi_mode ? (int)((L.g.N + 255) / 256) : 0);
-        out0[i + 1] = out0[i] + (chi_stage ? L.nb_out : 0);
-        inl0[i + 1] = inl0[i] + (L.boundary ? L.nb_in + L.nb_out : 0);
-        fill0[i + 1] = fill0[i] + (L.boundary ? L.nb_out : 0);
-        faces = faces || L.boundary;
+        // at least one block of the first face launch: it records the eq. 23
+        // sums and clears the next ones
+        fac0[i + 1] = fac0[i] + (L.boundary ? std::max(1, M.nb_coll + M.nb_in_early) : 0);
+        inl0[i + 1] = inl0[i] + (L.boundary ? M.nb_in_late + L.nb_out : 0);
+        fill0[i + 1] = fill0[i] + (L.boundary ? L.nb_fill : 0);
     }
     char *t = ws + off;
     auto put = [&](const void *src, size_t nbytes) -> char * {
@@ -1317,10 +1407,10 @@ lbm_status lbm_batch_create(const lbm_config *cfgs, int n, void *dev_ws, size_t 
         for (int w = item0[i]; w < item0[i + 1]; w++) item_mem[w] = i;
     b->tab.item_mem = (const int *)put(item_mem.data(), sizeof(int) * item_mem.size());
     b->tab.psi0 = (const int *)put(psi0.data(), sizeof(int) * (n + 1));
-    b->tab.out0 = (const int *)put(out0.data(), sizeof(int) * (n + 1));
+    b->tab.fac0 = (const int *)put(fac0.data(), sizeof(int) * (n + 1));
     b->tab.inl0 = (const int *)put(inl0.data(), sizeof(int) * (n + 1));
     b->tab.fill0 = (const int *)put(fill0.data(), sizeof(int) * (n + 1));
-    if (!b->tab.m || !b->tab.item0 || !b->tab.item_mem || !b->tab.psi0 || !b->tab.out0 || !b->tab.inl0 ||
+    if (!b->tab.m || !b->tab.item0 || !b->tab.item_mem || !b->tab.psi0 || !b->tab.fac0 || !b->tab.inl0 ||
         !b->tab.fill0) {
         delete b;
         return bfail(nullptr, LBM_EDEVICE, "upload of the batch tables failed");
@@ -1334,8 +1424,7 @@ lbm_status lbm_batch_create(const lbm_config *cfgs, int n, void *dev_ws, size_t 
     const int items = item0[n];
     b->g_main = (unsigned)std::min((items + 7) / 8 * 8, 2048);
     b->g_psi = (unsigned)psi0[n];
-    b->g_chi = faces ? (unsigned)((n + 63) / 64) : 0u;
-    b->g_out = (unsigned)out0[n];
+    b->g_fac = (unsigned)fac0[n];
     b->g_inl = (unsigned)inl0[n];
     b->g_fill = (unsigned)fill0[n];
     *out = b;

@@ -23,18 +23,22 @@ enum : uint32_t {
 
 constexpr int MAX_PATCH = 8;
 
-// One inlet node x1 and its partner x2 = x1 + n.
+// One inlet node x1 and its partner x2 = x1 + n (box indices and face-buffer
+// slots; x2 repeats x1 where it is solid).
 struct InletRec {
-    int64_t b1, b2;     // box indices
-    int slot1, slot2;   // face-buffer slots
+    int b1, b2;
+    int slot1, slot2;
     int patch;
-    int pad;
+    int x2_fluid;
 };
 
-// One outlet node x_N and its partner x' = x_N - n_o.
+// One outlet node x_N and its partner x' = x_N - n_o (bP repeats bN and
+// slotP < 0 where it is solid).
 struct OutletRec {
-    int64_t bN, bP;
-    int slotN, slotP;   // slotP < 0 when x' is solid
+    int bN, bP;
+    int slotN, slotP;
+    int pN;             // padded index of x_N
+    int pad;
 };
 
 struct Physics {
@@ -78,6 +82,13 @@ struct Boundary {
     int n_in, n_out;          // record counts
     const InletRec *in;
     const OutletRec *out;
+    // population slots within one component array, in lane order (lane_dir):
+    // [n_in][2][Q] those that stream into x1 and x2, [n_out][3][Q] those that
+    // stream into x_N and x', and the box index of the node that reads what
+    // x_N stores
+    const int *in_tab, *out_tab;
+    uint64_t out_enter;       // byte m: lane of the m-th direction entering through the outlet
+    int face_pass;            // records per wave of the face kernels (see FACE_NT)
     const int *bslot;         // [N] face-buffer slot of role nodes, -1 elsewhere
     int n_xp;                 // fluid x_{N-1} nodes; face slots [0, n_in) are the inlet nodes and
                               // [n_in, n_in + n_xp) the x_{N-1} nodes, both in record order
@@ -103,9 +114,25 @@ struct Boundary {
     const float *wallc;
 };
 
-// Threads per block of the face kernels (one wave: the face node counts are
-// small, so narrow blocks spread the uncoalesced face gathers over more CUs).
-constexpr int FACE_NT = 64;
+// Threads per block of the face kernels.  A block takes FACE_NT / 64 x
+// face_pass records (twice that in 2-D); face_pass is 1 for faces of up to
+// FACE_WIDE nodes, which then spread over the most CUs, and 4 above, where
+// every CU has work either way and each block of the outlet fill sums the
+// partial sums that all blocks left.
+constexpr int FACE_NT = 256;
+constexpr int FACE_WIDE = 2048;
+// Lanes per component and node of a face wave, and nodes per wave.
+template <int DIM> struct FaceMap {
+    static constexpr int GL = DIM == 3 ? 32 : 16;
+    static constexpr int NPW = 64 / (2 * GL);
+};
+// The outlet fill: entering directions, lanes per component and node, nodes
+// per block.
+template <int DIM> struct FillMap {
+    static constexpr int NE = DIM == 3 ? 5 : 3;
+    static constexpr int EL = DIM == 3 ? 8 : 4;
+    static constexpr int NPB = FACE_NT / (2 * EL);
+};
 // Consecutive node-update work items that one XCD takes per turn.
 constexpr int MAIN_XCD_GROUP = 4;
 
@@ -120,7 +147,7 @@ struct Member {
     Boundary bd;
     int tiles_x, tiles_y, n_items;
     const int *item_list;      // [n_items] tiles of the node update that hold fluid
-    int nb_in, nb_out;         // face-kernel blocks
+    int nb_coll, nb_in_early, nb_in_late;   // face-kernel blocks
     int *flag;
 };
 
@@ -133,8 +160,8 @@ struct BatchTab {
     const int *item0;          // node-update work items
     const int *item_mem;       // the member of each node-update work item
     const int *psi0;           // k_psi blocks
-    const int *out0;           // outlet-collision blocks
-    const int *inl0;           // inlet-kernel blocks (inlet nodes, then U_c partials)
+    const int *fac0;           // blocks of the first face launch (outlet collision, early inlet nodes)
+    const int *inl0;           // inlet-kernel blocks (the other inlet nodes, then U_c partials)
     const int *fill0;          // outlet-fill blocks
 };
 
