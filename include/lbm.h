@@ -300,8 +300,10 @@ lbm_status lbm_probe(lbm_ctx *ctx, int k, const lbm_box *box, double threshold, 
 /* Synchronises and labels the face-connected components of the dispersed
  * phase of component k in box.  *n_out receives their number; the first
  * min(n, max_out) of them, ordered by their smallest node index, are written
- * to out (host memory, caller owned).  Allocates and frees its own device
- * scratch (4 bytes x 2 per node); not for use inside a graph capture. */
+ * to out (host memory, caller owned).  Its device scratch is the population
+ * array that the next step overwrites, so it allocates nothing (a box that
+ * fills a domain of some ten nodes excepted); not for use inside a graph
+ * capture. */
 lbm_status lbm_components(lbm_ctx *ctx, int k, const lbm_box *box, double threshold,
                           lbm_component *out, int max_out, int *n_out);
 

@@ -1190,11 +1190,6 @@ __global__ __launch_bounds__(FACE_NT) void k_outlet_fill_batch(BatchTab t, int c
 // threshold; droplets are its face-connected components.
 // ---------------------------------------------------------------------------
 
-__device__ __forceinline__ bool in_box(const Box3 &bx, int x, int y, int z)
-{
-    return x >= bx.lo[0] && x < bx.hi[0] && y >= bx.lo[1] && y < bx.hi[1] && z >= bx.lo[2] && z < bx.hi[2];
-}
-
 // rho_k of a fluid node from its post-streaming populations
 template <int DIM, int STORE>
 __device__ __forceinline__ float node_rho(const typename Codec<STORE>::T *__restrict__ src, const Geometry &g,
@@ -1208,126 +1203,235 @@ __device__ __forceinline__ float node_rho(const typename Codec<STORE>::T *__rest
     return r;
 }
 
-// count of dispersed nodes in the box, added to *out (zeroed by k_zero64)
-template <int DIM, int STORE>
+// Count of dispersed nodes in the box.  ONE: a single block takes the whole
+// box and writes the count; else every wave adds its own to *out (zeroed by
+// k_zero64).
+template <int DIM, int STORE, bool ONE>
 __global__ __launch_bounds__(256) void k_probe(const typename Codec<STORE>::T *__restrict__ src,
                                                const uint32_t *__restrict__ type, const float2 *__restrict__ ref,
                                                Geometry g, int k, Box3 bx, float thr,
                                                unsigned long long *__restrict__ out)
 {
     const int ex = bx.hi[0] - bx.lo[0], ey = bx.hi[1] - bx.lo[1], ez = bx.hi[2] - bx.lo[2];
-    const int64_t v = (int64_t)blockIdx.x * 256 + threadIdx.x;
-    int hit = 0;
-    if (v < (int64_t)ex * ey * ez) {
-        const int x = bx.lo[0] + (int)(v % ex), y = bx.lo[1] + (int)((v / ex) % ey),
-                  z = bx.lo[2] + (int)(v / ((int64_t)ex * ey));
-        const int64_t b = (int64_t)x + (int64_t)g.n[0] * ((int64_t)y + (int64_t)g.n[1] * z);
-        const uint32_t tw = type[b];
-        if (!(tw & T_SOLID)) {
-            const float2 rf = ref[b];
-            hit = node_rho<DIM, STORE>(src, g, tw | T_EDGE, x, y, z, k, k == 0 ? rf.x : rf.y) > thr;
+    const int64_t vol = (int64_t)ex * ey * ez;
+    unsigned long long c = 0;                   // of the wave
+    for (int64_t v0 = (int64_t)blockIdx.x * 256; v0 < vol; v0 += (int64_t)gridDim.x * 256) {
+        const int64_t v = v0 + threadIdx.x;
+        int hit = 0;
+        if (v < vol) {
+            const int x = bx.lo[0] + (int)(v % ex), y = bx.lo[1] + (int)((v / ex) % ey),
+                      z = bx.lo[2] + (int)(v / ((int64_t)ex * ey));
+            const int64_t b = (int64_t)x + (int64_t)g.n[0] * ((int64_t)y + (int64_t)g.n[1] * z);
+            const uint32_t tw = type[b];
+            if (!(tw & T_SOLID)) {
+                const float2 rf = ref[b];
+                hit = node_rho<DIM, STORE>(src, g, tw | T_EDGE, x, y, z, k, k == 0 ? rf.x : rf.y) > thr;
+            }
         }
+        c += __popcll(__ballot(hit));
     }
-    const unsigned long long c = __popcll(__ballot(hit));
-    if ((threadIdx.x & 63) == 0 && c) atomicAdd(out, c);
+    if constexpr (ONE) {
+        __shared__ unsigned long long s_c[4];
+        if ((threadIdx.x & 63) == 0) s_c[threadIdx.x >> 6] = c;
+        __syncthreads();
+        if (threadIdx.x == 0) *out = s_c[0] + s_c[1] + s_c[2] + s_c[3];
+    } else {
+        if ((threadIdx.x & 63) == 0 && c) atomicAdd(out, c);
+    }
 }
 
 static __global__ void k_zero64(unsigned long long *p) { *p = 0ull; }
 
-// label = own box index on dispersed nodes of the box, -1 elsewhere
+// Connected components by union-find over the nodes of the box (linear index
+// v, x fastest): lab[v] is a node of the same component with a smaller or
+// equal index, -1 off the dispersed phase.  Four launches, whatever the shape
+// of the components:
+//   k_lab_init    lab[v] = start of v's x-run within its wave
+//   k_lab_merge   unites runs across waves, rows and planes
+//   k_lab_roots   lab[v] = root; each root takes a slot and clears its record
+//   k_lab_stats   size, smallest caller index and bounding box
+// (k_lab_order then sorts the records.)  Minimum-label propagation with a host
+// read-back every four passes and one atomic per node and quantity took
+// 1.24 ms on an 800x202 field of 12 droplets, 1.05 ms of it in the atomics of
+// all nodes of a droplet on one record; here a wave first reduces its nodes.
+
+// One level of the forest; other blocks change labels while they are read,
+// but only to smaller nodes of the same component, so an old value is valid.
+__device__ __forceinline__ int lab_load(const int *lab, int v)
+{
+    return __hip_atomic_load(lab + v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+__device__ __forceinline__ int lab_find(const int *lab, int v)
+{
+    for (int p = lab_load(lab, v); p != v; p = lab_load(lab, v)) v = p;   // p < v: ends
+    return v;
+}
+// Every pass replaces the larger root by what its label was before, which is
+// smaller, or ends.
+__device__ __forceinline__ void lab_unite(int *lab, int a, int b)
+{
+    while (true) {
+        a = lab_find(lab, a);
+        b = lab_find(lab, b);
+        if (a == b) return;
+        if (a < b) {
+            const int t = a;
+            a = b;
+            b = t;
+        }
+        const int old = atomicMin(lab + a, b);
+        if (old == a) return;
+        a = old;
+    }
+}
+
+// Coordinates of node v of the box (offsets from its corner).
+__device__ __forceinline__ void box_coords(const int (&ext)[3], uint32_t v, int &x, int &y, int &z)
+{
+    const uint32_t row = v / (uint32_t)ext[0];
+    x = (int)(v - row * (uint32_t)ext[0]);
+    z = (int)(row / (uint32_t)ext[1]);
+    y = (int)(row - (uint32_t)z * (uint32_t)ext[1]);
+}
+
 template <int DIM, int STORE>
 __global__ __launch_bounds__(256) void k_lab_init(const typename Codec<STORE>::T *__restrict__ src,
                                                   const uint32_t *__restrict__ type,
                                                   const float2 *__restrict__ ref, Geometry g, int k, Box3 bx,
-                                                  float thr, int *__restrict__ lab)
+                                                  float thr, int *__restrict__ lab, int *__restrict__ n_roots)
 {
-    const int64_t b = (int64_t)blockIdx.x * 256 + threadIdx.x;
-    if (b >= g.N) return;
+    const int ext[3] = {bx.hi[0] - bx.lo[0], bx.hi[1] - bx.lo[1], bx.hi[2] - bx.lo[2]};
+    const uint32_t v = blockIdx.x * 256u + threadIdx.x, vol = (uint32_t)ext[0] * ext[1] * ext[2];
+    if (v == 0) *n_roots = 0;
+    int x = 0, y = 0, z = 0;
+    bool in = false;
+    if (v < vol) {
+        box_coords(ext, v, x, y, z);
+        const int gx = bx.lo[0] + x, gy = bx.lo[1] + y, gz = bx.lo[2] + z;
+        const int64_t b = (int64_t)gx + (int64_t)g.n[0] * ((int64_t)gy + (int64_t)g.n[1] * gz);
+        const uint32_t tw = type[b];
+        if (!(tw & T_SOLID)) {
+            const float2 rf = ref[b];
+            in = node_rho<DIM, STORE>(src, g, tw | T_EDGE, gx, gy, gz, k, k == 0 ? rf.x : rf.y) > thr;
+        }
+    }
+    // the run of dispersed nodes that this lane continues within its wave
+    const int lane = threadIdx.x & 63;
+    const unsigned long long m = __ballot(in), starts = ~(m & (m << 1)) | __ballot(x == 0);
+    const int start = 63 - __clzll((long long)(starts & (~0ull >> (63 - lane))));
+    if (v < vol) lab[v] = in ? (int)v - (lane - start) : -1;
+}
+
+static __global__ __launch_bounds__(256) void k_lab_merge(Box3 bx, int *lab)
+{
+    const int ext[3] = {bx.hi[0] - bx.lo[0], bx.hi[1] - bx.lo[1], bx.hi[2] - bx.lo[2]};
+    const uint32_t u = blockIdx.x * 256u + threadIdx.x;
+    if (u >= (uint32_t)ext[0] * ext[1] * ext[2]) return;
+    const int v = (int)u;
+    auto in = [&](int w) { return lab_load(lab, w) >= 0; };
+    if (!in(v)) return;
     int x, y, z;
-    coords_of(g, b, x, y, z);
-    const uint32_t tw = type[b];
-    bool in = !(tw & T_SOLID) && in_box(bx, x, y, z);
-    if (in) {
-        const float2 rf = ref[b];
-        in = node_rho<DIM, STORE>(src, g, tw | T_EDGE, x, y, z, k, k == 0 ? rf.x : rf.y) > thr;
-    }
-    lab[b] = in ? (int)b : -1;
+    box_coords(ext, u, x, y, z);
+    const bool left = x > 0 && in(v - 1);
+    if (left && (threadIdx.x & 63) == 0) lab_unite(lab, v, v - 1);
+    // a neighbour row or plane is met once per pair of runs: where the nodes
+    // to the left of both are dispersed too, the pair is united there
+    if (y > 0 && in(v - ext[0]) && !(left && in(v - ext[0] - 1))) lab_unite(lab, v, v - ext[0]);
+    const int pl = ext[0] * ext[1];
+    if (z > 0 && in(v - pl) && !(left && in(v - pl - 1))) lab_unite(lab, v, v - pl);
 }
 
-// One pass of minimum-label propagation over face neighbours plus pointer
-// jumping (lab[lab[b]] <= lab[b]).  Labels only decrease, so passes may run
-// concurrently and in any order; the fixed point is the smallest box index
-// of each component.
-static __global__ __launch_bounds__(256) void k_lab_prop(Geometry g, int dim, int *lab, int *changed)
+// roots (lab[v] == v) get consecutive slots in an arbitrary order (records
+// beyond cap are counted, not kept); the records are ordered afterwards
+static __global__ __launch_bounds__(256) void k_lab_roots(Box3 bx, int *lab, int *__restrict__ slot,
+                                                          CompStat *__restrict__ st, int cap, int *n_roots)
 {
-    const int64_t b = (int64_t)blockIdx.x * 256 + threadIdx.x;
-    if (b >= g.N) return;
-    const int l = lab[b];
-    if (l < 0) return;
-    int x, y, z;
-    coords_of(g, b, x, y, z);
-    int m = l;
-    auto take = [&](int64_t nb) {
-        const int v = lab[nb];
-        if (v >= 0 && v < m) m = v;
-    };
-    if (x > 0) take(b - 1);
-    if (x + 1 < g.n[0]) take(b + 1);
-    if (y > 0) take(b - g.n[0]);
-    if (y + 1 < g.n[1]) take(b + g.n[0]);
-    if (dim == 3) {
-        const int64_t pl = (int64_t)g.n[0] * g.n[1];
-        if (z > 0) take(b - pl);
-        if (z + 1 < g.n[2]) take(b + pl);
-    }
-    const int j = lab[m];
-    if (j >= 0 && j < m) m = j;
-    if (m < l) {
-        lab[b] = m;
-        *changed = 1;
-    }
-}
-
-// roots (lab[b] == b) get consecutive slots in an arbitrary order; the host
-// orders the components afterwards
-static __global__ __launch_bounds__(256) void k_lab_roots(Geometry g, const int *__restrict__ lab,
-                                                          int *__restrict__ slot, int *__restrict__ n_roots)
-{
-    const int64_t b = (int64_t)blockIdx.x * 256 + threadIdx.x;
-    if (b >= g.N) return;
-    if (lab[b] == (int)b) slot[b] = atomicAdd(n_roots, 1);
-}
-
-// per component: size, smallest caller-frame index, caller-frame bounding box
-// (integer atomics: the result does not depend on the order)
-static __global__ __launch_bounds__(256) void k_lab_stats_init(CompStat *st, int n)
-{
-    const int i = blockIdx.x * 256 + threadIdx.x;
-    if (i >= n) return;
-    st[i].size = 0ull;
-    st[i].first = ~0ull;
+    const uint32_t u = blockIdx.x * 256u + threadIdx.x;
+    const uint32_t vol = (uint32_t)(bx.hi[0] - bx.lo[0]) * (bx.hi[1] - bx.lo[1]) * (bx.hi[2] - bx.lo[2]);
+    if (u >= vol) return;
+    const int v = (int)u;
+    if (lab_load(lab, v) < 0) return;
+    const int root = lab_find(lab, v);
+    lab[v] = root;                       // any value on the way to the root is valid for the others
+    if (root != v) return;
+    const int s = atomicAdd(n_roots, 1);
+    slot[v] = s;
+    if (s >= cap) return;
+    CompStat c;
+    c.size = 0ull;
+    c.first = ~0ull;
     for (int a = 0; a < 3; a++) {
-        st[i].lo[a] = 0x7fffffff;
-        st[i].hi[a] = -1;
+        c.lo[a] = 0x7fffffff;
+        c.hi[a] = -1;
     }
+    st[s] = c;
 }
 
-static __global__ __launch_bounds__(256) void k_lab_stats(Geometry g, const int *__restrict__ lab,
-                                                          const int *__restrict__ slot, CompStat *st)
+// Sizes, first nodes and bounding boxes.  A wave takes a strip of 64 nodes in
+// x and LAB_ROWS consecutive rows, and adds what it holds of one component to
+// its record at once (integer atomics: the result does not depend on their
+// order).
+constexpr int LAB_ROWS = 4;
+__device__ __forceinline__ int wave_min(int v)
 {
-    const int64_t b = (int64_t)blockIdx.x * 256 + threadIdx.x;
-    if (b >= g.N) return;
-    const int l = lab[b];
-    if (l < 0) return;
-    CompStat *c = st + slot[l];
-    int x, y, z;
-    coords_of(g, b, x, y, z);
-    const int mc[3] = {x, y, z};
-    atomicAdd(&c->size, 1ull);
-    atomicMin(&c->first, (unsigned long long)caller_index(g, x, y, z));
-    for (int a = 0; a < 3; a++) {
-        atomicMin(&c->lo[g.ax[a]], mc[a]);
-        atomicMax(&c->hi[g.ax[a]], mc[a] + 1);
+#pragma unroll
+    for (int o = 32; o > 0; o >>= 1) v = min(v, __shfl_xor(v, o, 64));
+    return v;
+}
+
+static __global__ __launch_bounds__(256) void k_lab_stats(Geometry g, Box3 bx, const int *__restrict__ lab,
+                                                          const int *__restrict__ slot, CompStat *st, int cap)
+{
+    const int ex = bx.hi[0] - bx.lo[0], ey = bx.hi[1] - bx.lo[1], ez = bx.hi[2] - bx.lo[2];
+    const int strips = (ex + 63) / 64, rows = ey * ez;
+    const int w = (int)(blockIdx.x * 4 + (threadIdx.x >> 6)), lane = threadIdx.x & 63;
+    const int x = (w % strips) * 64 + lane, row0 = (w / strips) * LAB_ROWS;
+    if (row0 >= rows) return;                            // uniform over the wave
+    // each lane's four nodes: slot of the component, or -1
+    int sl[LAB_ROWS];
+#pragma unroll
+    for (int i = 0; i < LAB_ROWS; i++) {
+        const bool valid = x < ex && row0 + i < rows;
+        const int l = valid ? lab[(row0 + i) * ex + x] : -1;
+        sl[i] = l >= 0 ? slot[l] : -1;
+        if (sl[i] >= cap) sl[i] = -1;
+    }
+    while (true) {
+        // the next component: the first one a lane still holds
+        int mine = -1;
+#pragma unroll
+        for (int i = LAB_ROWS - 1; i >= 0; i--) mine = sl[i] >= 0 ? sl[i] : mine;
+        const unsigned long long have = __ballot(mine >= 0);
+        if (!have) return;
+        const int s = __shfl(mine, __ffsll((long long)have) - 1, 64);
+        int size = 0, first = 0x7fffffff, lo[3] = {0x7fffffff, 0x7fffffff, 0x7fffffff}, hi[3] = {-1, -1, -1};
+#pragma unroll
+        for (int i = 0; i < LAB_ROWS; i++) {
+            const bool hit = sl[i] == s;
+            size += __popcll(__ballot(hit));
+            if (!hit) continue;
+            sl[i] = -1;
+            const int row = row0 + i, zz = row / ey, mc[3] = {bx.lo[0] + x, bx.lo[1] + row - zz * ey, bx.lo[2] + zz};
+            first = min(first, (int)caller_index(g, mc[0], mc[1], mc[2]));
+            for (int a = 0; a < 3; a++) {
+                lo[a] = min(lo[a], mc[a]);
+                hi[a] = max(hi[a], mc[a] + 1);
+            }
+        }
+        first = wave_min(first);
+        for (int a = 0; a < 3; a++) {
+            lo[a] = wave_min(lo[a]);
+            hi[a] = -wave_min(-hi[a]);
+        }
+        if (lane == 0) {
+            CompStat *c = st + s;
+            atomicAdd(&c->size, (unsigned long long)size);
+            atomicMin(&c->first, (unsigned long long)first);
+            for (int a = 0; a < 3; a++) {
+                atomicMin(&c->lo[g.ax[a]], lo[a]);
+                atomicMax(&c->hi[g.ax[a]], hi[a]);
+            }
+        }
     }
 }
 

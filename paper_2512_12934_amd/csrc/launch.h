@@ -96,10 +96,9 @@ template <int DIM> struct Launcher {
     static void batch_step(int storage, int cfg, const BatchArgs &b);
     // droplet labels
     static void probe(int storage, const StepArgs &a, int k, const Box3 &bx, float thr, unsigned long long *out);
-    static void lab_init(int storage, const StepArgs &a, int k, const Box3 &bx, float thr, int *lab);
-    static void lab_prop(const StepArgs &a, int *lab, int *changed, int passes);
-    static void lab_roots(const StepArgs &a, const int *lab, int *slot, int *n_roots);
-    static void lab_stats(const StepArgs &a, const int *lab, const int *slot, CompStat *st, int n);
+    static void lab_init(int storage, const StepArgs &a, int k, const Box3 &bx, float thr, int *lab, int *n_roots);
+    static void lab_components(const StepArgs &a, const Box3 &bx, int *lab, int *slot, CompStat *st, int cap,
+                               int *n_roots);
 };
 
 extern template struct Launcher<2>;

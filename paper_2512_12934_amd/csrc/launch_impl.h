@@ -176,47 +176,47 @@ template <int DIM>
 void Launcher<DIM>::probe(int storage, const StepArgs &a, int k, const Box3 &bx, float thr, unsigned long long *out)
 {
     const int64_t vol = (int64_t)(bx.hi[0] - bx.lo[0]) * (bx.hi[1] - bx.lo[1]) * (bx.hi[2] - bx.lo[2]);
-    hipLaunchKernelGGL(k_zero64, dim3(1), dim3(1), 0, a.stream, out);
-    if (vol <= 0) return;
+    // a cross-section of a channel (hundreds of nodes, the usual probe) is a
+    // few passes of one block, less than the launch that would clear the
+    // count for many blocks; from PROBE_ONE nodes on the passes cost more
+    constexpr int64_t PROBE_ONE = 2048;
+    const bool one = vol <= PROBE_ONE;
+    if (!one) hipLaunchKernelGGL(k_zero64, dim3(1), dim3(1), 0, a.stream, out);
+    const unsigned nb = one ? 1u : (unsigned)((vol + 255) / 256);
+    with_store(storage, [&](auto sc) {
+        using T = LBM_STORE_T(sc);
+        if (one)
+            hipLaunchKernelGGL((k_probe<DIM, decltype(sc)::value, true>), dim3(1), dim3(256), 0, a.stream,
+                               (const T *)a.src, a.type, a.ref, a.g, k, bx, thr, out);
+        else
+            hipLaunchKernelGGL((k_probe<DIM, decltype(sc)::value, false>), dim3(nb), dim3(256), 0, a.stream,
+                               (const T *)a.src, a.type, a.ref, a.g, k, bx, thr, out);
+    });
+}
+
+template <int DIM>
+void Launcher<DIM>::lab_init(int storage, const StepArgs &a, int k, const Box3 &bx, float thr, int *lab, int *n_roots)
+{
+    const int64_t vol = (int64_t)(bx.hi[0] - bx.lo[0]) * (bx.hi[1] - bx.lo[1]) * (bx.hi[2] - bx.lo[2]);
     const unsigned nb = (unsigned)((vol + 255) / 256);
     with_store(storage, [&](auto sc) {
         using T = LBM_STORE_T(sc);
-        hipLaunchKernelGGL((k_probe<DIM, decltype(sc)::value>), dim3(nb), dim3(256), 0, a.stream, (const T *)a.src,
-                           a.type, a.ref, a.g, k, bx, thr, out);
-    });
-}
-
-template <int DIM>
-void Launcher<DIM>::lab_init(int storage, const StepArgs &a, int k, const Box3 &bx, float thr, int *lab)
-{
-    const unsigned nb = (unsigned)((a.g.N + 255) / 256);
-    with_store(storage, [&](auto sc) {
-        using T = LBM_STORE_T(sc);
         hipLaunchKernelGGL((k_lab_init<DIM, decltype(sc)::value>), dim3(nb), dim3(256), 0, a.stream,
-                           (const T *)a.src, a.type, a.ref, a.g, k, bx, thr, lab);
+                           (const T *)a.src, a.type, a.ref, a.g, k, bx, thr, lab, n_roots);
     });
 }
 
 template <int DIM>
-void Launcher<DIM>::lab_prop(const StepArgs &a, int *lab, int *changed, int passes)
+void Launcher<DIM>::lab_components(const StepArgs &a, const Box3 &bx, int *lab, int *slot, CompStat *st, int cap,
+                                   int *n_roots)
 {
-    const unsigned nb = (unsigned)((a.g.N + 255) / 256);
-    for (int p = 0; p < passes; p++) hipLaunchKernelGGL(k_lab_prop, dim3(nb), dim3(256), 0, a.stream, a.g, DIM, lab, changed);
-}
-
-template <int DIM>
-void Launcher<DIM>::lab_roots(const StepArgs &a, const int *lab, int *slot, int *n_roots)
-{
-    const unsigned nb = (unsigned)((a.g.N + 255) / 256);
-    hipLaunchKernelGGL(k_lab_roots, dim3(nb), dim3(256), 0, a.stream, a.g, lab, slot, n_roots);
-}
-
-template <int DIM>
-void Launcher<DIM>::lab_stats(const StepArgs &a, const int *lab, const int *slot, CompStat *st, int n)
-{
-    if (n > 0) hipLaunchKernelGGL(k_lab_stats_init, dim3((n + 255) / 256), dim3(256), 0, a.stream, st, n);
-    const unsigned nb = (unsigned)((a.g.N + 255) / 256);
-    hipLaunchKernelGGL(k_lab_stats, dim3(nb), dim3(256), 0, a.stream, a.g, lab, slot, st);
+    const int64_t ex = bx.hi[0] - bx.lo[0], rows = (int64_t)(bx.hi[1] - bx.lo[1]) * (bx.hi[2] - bx.lo[2]);
+    const unsigned nb = (unsigned)((ex * rows + 255) / 256);
+    hipLaunchKernelGGL(k_lab_merge, dim3(nb), dim3(256), 0, a.stream, bx, lab);
+    hipLaunchKernelGGL(k_lab_roots, dim3(nb), dim3(256), 0, a.stream, bx, lab, slot, st, cap, n_roots);
+    const int64_t waves = (ex + 63) / 64 * ((rows + LAB_ROWS - 1) / LAB_ROWS);
+    hipLaunchKernelGGL(k_lab_stats, dim3((unsigned)((waves + 3) / 4)), dim3(256), 0, a.stream, a.g, bx, lab, slot, st,
+                       cap);
 }
 
 template <int DIM>

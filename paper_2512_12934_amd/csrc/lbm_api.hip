@@ -608,15 +608,27 @@ Layout make_layout(const Canon &k, const Maps &m)
 // entry point allocates nothing.  Each device holds its own copy for the
 // life of the process; host code uses only the device address that
 // hipGetSymbolAddress returns for it (the array's name is a host-side
-// stand-in).  Layout: lab [MAX_NODES] int, slot [MAX_NODES] int, two int
-// counters, MAX_COMPONENTS CompStat, MAX_COMPONENTS lbm_component (ordered).
-constexpr size_t SCR_LAB = 0;
-constexpr size_t SCR_SLOT = SCR_LAB + (size_t)LBM_COMPONENTS_STATIC_MAX_NODES * 4;
-constexpr size_t SCR_FLAGS = SCR_SLOT + (size_t)LBM_COMPONENTS_STATIC_MAX_NODES * 4;
-constexpr size_t SCR_STATS = SCR_FLAGS + 256;
-constexpr size_t SCR_SORTED = SCR_STATS + (size_t)LBM_COMPONENTS_STATIC_MAX_COMPONENTS * sizeof(CompStat);
-constexpr size_t SCR_BYTES = SCR_SORTED + (size_t)LBM_COMPONENTS_STATIC_MAX_COMPONENTS * sizeof(lbm_component);
+// stand-in).  Layout: see LabelScratch.
+constexpr size_t LABEL_HEAD = 64;      // the component count, then the ordered records: read back in one copy
+constexpr int LABEL_SORT_MAX = LBM_COMPONENTS_STATIC_MAX_COMPONENTS;   // more are ordered on the host
 static_assert(sizeof(CompStat) % 8 == 0 && sizeof(lbm_component) % 8 == 0, "scratch record alignment");
+
+// Carve-up of the labelling scratch for a box of `nodes` nodes and up to
+// `cap` components.
+struct LabelScratch {
+    size_t sorted, stats, lab, slot, total;
+    LabelScratch(int64_t nodes, int64_t cap)
+    {
+        sorted = LABEL_HEAD;
+        stats = sorted + (size_t)std::min<int64_t>(cap, LABEL_SORT_MAX) * sizeof(lbm_component);
+        lab = stats + (size_t)cap * sizeof(CompStat);
+        slot = lab + (size_t)nodes * 4;
+        total = slot + (size_t)nodes * 4;
+    }
+};
+constexpr size_t SCR_BYTES = LABEL_HEAD +
+                             (size_t)LBM_COMPONENTS_STATIC_MAX_COMPONENTS * (sizeof(lbm_component) + sizeof(CompStat)) +
+                             (size_t)LBM_COMPONENTS_STATIC_MAX_NODES * 8;
 
 static __device__ __align__(256) unsigned char scratch[SCR_BYTES];
 
@@ -644,26 +656,32 @@ void *static_scratch_ptr(int dev)
     return g_scratch_ptr[dev];
 }
 
-// Orders the n component records by their smallest node index (all distinct)
+// Orders the component records by their smallest node index (all distinct)
 // into the caller's record layout: record i goes to the rank of its first
-// index among all n.
-__global__ __launch_bounds__(256) void k_lab_order(const CompStat *__restrict__ st, int n,
-                                                   lbm_component *__restrict__ out)
+// index among all.  Leaves more than cap records to the host.
+__global__ __launch_bounds__(256) void k_lab_order(const CompStat *__restrict__ st, const int *__restrict__ n_roots,
+                                                   int cap, lbm_component *__restrict__ out)
 {
-    const int i = blockIdx.x * 256 + threadIdx.x;
-    if (i >= n) return;
-    const unsigned long long fi = st[i].first;
-    int rank = 0;
-    for (int j = 0; j < n; j++) rank += st[j].first < fi ? 1 : 0;
-    lbm_component r;
-    r.first = (int64_t)fi;
-    r.size = (int64_t)st[i].size;
-    for (int d = 0; d < 3; d++) {
-        r.lo[d] = st[i].lo[d];
-        r.hi[d] = st[i].hi[d];
+    const int n = *n_roots;
+    if (n > cap) return;
+    for (int i = blockIdx.x * 256 + threadIdx.x; i < n; i += gridDim.x * 256) {
+        const unsigned long long fi = st[i].first;
+        int rank = 0;
+        for (int j = 0; j < n; j++) rank += st[j].first < fi ? 1 : 0;
+        lbm_component r;
+        r.first = (int64_t)fi;
+        r.size = (int64_t)st[i].size;
+        for (int d = 0; d < 3; d++) {
+            r.lo[d] = st[i].lo[d];
+            r.hi[d] = st[i].hi[d];
+        }
+        out[rank] = r;
     }
-    out[rank] = r;
 }
+
+// Pinned host memory per context, for results that a synchronising call reads
+// back (a copy into pageable memory costs a second staging step).
+constexpr size_t PIN_BYTES = 1024;
 
 }  // namespace
 
@@ -679,6 +697,8 @@ struct lbm_ctx {
     int64_t steps = 0;
     double mass0[2] = {0, 0};
     bool unstable = false;
+    char *pin = nullptr;   // PIN_BYTES of pinned host memory
+    bool own_pin = false;  // false: part of a batch's allocation
     std::string err;
     // Step loop as a replayed HIP graph: graph_steps steps per graph, one
     // executable per parity of the A/B arrays at its start, captured on a
@@ -691,6 +711,7 @@ struct lbm_ctx {
         for (auto &g : gx)
             if (g) (void)hipGraphExecDestroy(g);
         if (cap) (void)hipStreamDestroy(cap);
+        if (own_pin) (void)hipHostFree(pin);
     }
     void *fsrc() const { return ws + (cur == 0 ? L.o_fA : L.o_fB); }
     void *fdst() const { return ws + (cur == 0 ? L.o_fB : L.o_fA); }
@@ -866,6 +887,8 @@ lbm_status capture_steps(lbm_ctx *c, int parity)
     return LBM_OK;
 }
 
+lbm_status create_ctx(const lbm_config *cfg, void *dev_ws, size_t ws_bytes, void *hip_stream, char *pin, lbm_ctx **out);
+
 }  // namespace
 
 extern "C" {
@@ -880,6 +903,17 @@ size_t lbm_workspace_bytes(const lbm_config *cfg)
 }
 
 lbm_status lbm_create(const lbm_config *cfg, void *dev_ws, size_t ws_bytes, void *hip_stream, lbm_ctx **out)
+{
+    return create_ctx(cfg, dev_ws, ws_bytes, hip_stream, nullptr, out);
+}
+
+}  // extern "C"
+
+namespace {
+
+// lbm_create; pin: the caller's PIN_BYTES of pinned memory, or NULL to
+// allocate them.
+lbm_status create_ctx(const lbm_config *cfg, void *dev_ws, size_t ws_bytes, void *hip_stream, char *pin, lbm_ctx **out)
 {
     if (!out) return fail(nullptr, LBM_EINVAL, "out is NULL");
     *out = nullptr;
@@ -905,6 +939,17 @@ lbm_status lbm_create(const lbm_config *cfg, void *dev_ws, size_t ws_bytes, void
     c->cfg.wall_u = nullptr;
     c->ws = (char *)dev_ws;
     c->stream = (hipStream_t)hip_stream;
+    c->pin = pin;
+    if (!pin) {
+        void *p = nullptr;
+        if (hipHostMalloc(&p, PIN_BYTES, hipHostMallocDefault) != hipSuccess) {
+            (void)hipGetLastError();
+            delete c;
+            return fail(nullptr, LBM_ENOMEM, "no pinned host memory");
+        }
+        c->pin = (char *)p;
+        c->own_pin = true;
+    }
     if (hipGetDevice(&c->device) != hipSuccess) {
         delete c;
         return fail(nullptr, LBM_EDEVICE, "hipGetDevice failed");
@@ -1030,6 +1075,10 @@ lbm_status lbm_create(const lbm_config *cfg, void *dev_ws, size_t ws_bytes, void
     *out = c;
     return LBM_OK;
 }
+
+}  // namespace
+
+extern "C" {
 
 lbm_status lbm_step(lbm_ctx *c, int64_t n)
 {
@@ -1225,12 +1274,14 @@ struct lbm_batch {
     int graph_steps = 16;
     hipStream_t cap = nullptr;
     hipGraphExec_t gx[2] = {nullptr, nullptr};
+    void *pin = nullptr;   // PIN_BYTES of pinned host memory per member
     ~lbm_batch()
     {
         for (auto &g : gx)
             if (g) (void)hipGraphExecDestroy(g);
         if (cap) (void)hipStreamDestroy(cap);
         for (auto *c : m) delete c;
+        if (pin) (void)hipHostFree(pin);
     }
 };
 
@@ -1352,13 +1403,19 @@ lbm_status lbm_batch_create(const lbm_config *cfgs, int n, void *dev_ws, size_t 
     b->stream = (hipStream_t)hip_stream;
     b->dim = mc[0].dim;
     b->storage = mc[0].storage;
+    if (hipHostMalloc(&b->pin, (size_t)n * PIN_BYTES, hipHostMallocDefault) != hipSuccess) {
+        (void)hipGetLastError();
+        b->pin = nullptr;
+        delete b;
+        return bfail(nullptr, LBM_ENOMEM, "no pinned host memory");
+    }
     char *ws = (char *)dev_ws;
     size_t off = 0;
     std::vector<Member> mem(n);
     std::vector<int> item0(n + 1, 0), psi0(n + 1, 0), fac0(n + 1, 0), inl0(n + 1, 0), fill0(n + 1, 0);
     for (int i = 0; i < n; i++) {
         lbm_ctx *c = nullptr;
-        const lbm_status st = lbm_create(&mc[i], ws + off, bytes[i], hip_stream, &c);
+        const lbm_status st = create_ctx(&mc[i], ws + off, bytes[i], hip_stream, (char *)b->pin + i * PIN_BYTES, &c);
         if (st != LBM_OK) {
             const std::string msg = "member " + std::to_string(i) + ": " + g_create_error;
             delete b;
@@ -1517,6 +1574,69 @@ std::string to_box(const lbm_ctx *c, const lbm_box *in, Box3 &bx)
     return "";
 }
 
+int64_t box_volume(const Box3 &bx)
+{
+    return (int64_t)(bx.hi[0] - bx.lo[0]) * (bx.hi[1] - bx.lo[1]) * (bx.hi[2] - bx.lo[2]);
+}
+
+// Labels the box with the scratch at base (carved up as sc, records for up to
+// cap components), synchronises, and writes the first max_out components in
+// the order of their smallest node.  *n_out receives their number, which may
+// exceed cap; nothing is written to out then.
+lbm_status run_labels(lbm_ctx *c, int k, const Box3 &bx, double threshold, char *base, const LabelScratch &sc, int cap,
+                      lbm_component *out, int max_out, int *n_out)
+{
+    constexpr int REC0 = (int)((PIN_BYTES - LABEL_HEAD) / sizeof(lbm_component));   // records that come with the count
+    if (box_volume(bx) == 0) {
+        *n_out = 0;
+        return LBM_OK;
+    }
+    int *n_roots = (int *)base, *lab = (int *)(base + sc.lab), *slot = (int *)(base + sc.slot);
+    CompStat *st = (CompStat *)(base + sc.stats);
+    lbm_component *sorted = (lbm_component *)(base + sc.sorted);
+    const int sort_max = std::min(cap, LABEL_SORT_MAX);
+    const StepArgs a = step_args(c);
+    if (c->L.dim == 2) {
+        Launcher<2>::lab_init(c->L.storage, a, k, bx, (float)threshold, lab, n_roots);
+        Launcher<2>::lab_components(a, bx, lab, slot, st, cap, n_roots);
+    } else {
+        Launcher<3>::lab_init(c->L.storage, a, k, bx, (float)threshold, lab, n_roots);
+        Launcher<3>::lab_components(a, bx, lab, slot, st, cap, n_roots);
+    }
+    hipLaunchKernelGGL(k_lab_order, dim3((sort_max + 255) / 256), dim3(256), 0, c->stream, st, n_roots, sort_max, sorted);
+    HIPCHECK(c, hipGetLastError());
+    const int ahead = std::min({REC0, sort_max, max_out});
+    HIPCHECK(c, hipMemcpyAsync(c->pin, base, LABEL_HEAD + ahead * sizeof(lbm_component), hipMemcpyDeviceToHost, c->stream));
+    HIPCHECK(c, hipStreamSynchronize(c->stream));
+    int n = 0;
+    memcpy(&n, c->pin, sizeof n);
+    *n_out = n;
+    const int want = std::min(n, max_out);
+    if (n > cap || want <= 0) return LBM_OK;
+    if (n <= sort_max) {
+        memcpy(out, c->pin + LABEL_HEAD, (size_t)std::min(want, ahead) * sizeof(lbm_component));
+        if (want > ahead) {
+            HIPCHECK(c, hipMemcpyAsync(out + ahead, sorted + ahead, (size_t)(want - ahead) * sizeof(lbm_component),
+                                       hipMemcpyDeviceToHost, c->stream));
+            HIPCHECK(c, hipStreamSynchronize(c->stream));
+        }
+        return LBM_OK;
+    }
+    std::vector<CompStat> h(n);
+    HIPCHECK(c, hipMemcpyAsync(h.data(), st, sizeof(CompStat) * n, hipMemcpyDeviceToHost, c->stream));
+    HIPCHECK(c, hipStreamSynchronize(c->stream));
+    std::sort(h.begin(), h.end(), [](const CompStat &p, const CompStat &q) { return p.first < q.first; });
+    for (int i = 0; i < want; i++) {
+        out[i].first = (int64_t)h[i].first;
+        out[i].size = (int64_t)h[i].size;
+        for (int d = 0; d < 3; d++) {
+            out[i].lo[d] = h[i].lo[d];
+            out[i].hi[d] = h[i].hi[d];
+        }
+    }
+    return LBM_OK;
+}
+
 }  // namespace
 
 extern "C" {
@@ -1543,62 +1663,16 @@ lbm_status lbm_components(lbm_ctx *c, int k, const lbm_box *box, double threshol
     Box3 bx{};
     const std::string why = to_box(c, box, bx);
     if (!why.empty()) return fail(c, LBM_EINVAL, why);
-    const StepArgs a = step_args(c);
-    const int64_t N = c->L.g.N;
-    int *lab = nullptr, *slot = nullptr, *flags = nullptr;
-    CompStat *st = nullptr;
-    auto release = [&]() {
-        if (lab) (void)hipFree(lab);
-        if (slot) (void)hipFree(slot);
-        if (flags) (void)hipFree(flags);
-        if (st) (void)hipFree(st);
-    };
-    auto run = [&]() -> lbm_status {
-        HIPCHECK(c, hipMalloc(&lab, (size_t)N * 4));
-        HIPCHECK(c, hipMalloc(&slot, (size_t)N * 4));
-        HIPCHECK(c, hipMalloc(&flags, 8));
-        const bool d2 = c->L.dim == 2;
-        if (d2) Launcher<2>::lab_init(c->L.storage, a, k, bx, (float)threshold, lab);
-        else Launcher<3>::lab_init(c->L.storage, a, k, bx, (float)threshold, lab);
-        // propagate until no label changes (at most N rounds; pointer jumping
-        // makes it a few dozen in practice)
-        for (int64_t round = 0;; round++) {
-            if (round > N) return fail(c, LBM_EDEVICE, "label propagation did not converge");
-            HIPCHECK(c, hipMemsetAsync(flags, 0, 4, c->stream));
-            if (d2) Launcher<2>::lab_prop(a, lab, flags, 4);
-            else Launcher<3>::lab_prop(a, lab, flags, 4);
-            int changed = 0;
-            HIPCHECK(c, hipMemcpyAsync(&changed, flags, 4, hipMemcpyDeviceToHost, c->stream));
-            HIPCHECK(c, hipStreamSynchronize(c->stream));
-            if (!changed) break;
-        }
-        HIPCHECK(c, hipMemsetAsync(flags + 1, 0, 4, c->stream));
-        if (d2) Launcher<2>::lab_roots(a, lab, slot, flags + 1);
-        else Launcher<3>::lab_roots(a, lab, slot, flags + 1);
-        int nr = 0;
-        HIPCHECK(c, hipMemcpyAsync(&nr, flags + 1, 4, hipMemcpyDeviceToHost, c->stream));
-        HIPCHECK(c, hipStreamSynchronize(c->stream));
-        *n_out = nr;
-        if (nr == 0) return LBM_OK;
-        HIPCHECK(c, hipMalloc(&st, sizeof(CompStat) * nr));
-        if (d2) Launcher<2>::lab_stats(a, lab, slot, st, nr);
-        else Launcher<3>::lab_stats(a, lab, slot, st, nr);
-        std::vector<CompStat> h(nr);
-        HIPCHECK(c, hipMemcpyAsync(h.data(), st, sizeof(CompStat) * nr, hipMemcpyDeviceToHost, c->stream));
-        HIPCHECK(c, hipStreamSynchronize(c->stream));
-        std::sort(h.begin(), h.end(), [](const CompStat &p, const CompStat &q) { return p.first < q.first; });
-        for (int i = 0; i < nr && i < max_out; i++) {
-            out[i].first = (int64_t)h[i].first;
-            out[i].size = (int64_t)h[i].size;
-            for (int d = 0; d < 3; d++) {
-                out[i].lo[d] = h[i].lo[d];
-                out[i].hi[d] = h[i].hi[d];
-            }
-        }
-        return LBM_OK;
-    };
-    const lbm_status r = run();
-    release();
+    // the population array that the next step writes holds nothing between
+    // steps: it is the scratch, unless the box is nearly the whole of a tiny
+    // domain
+    const int64_t vol = box_volume(bx), cap = (vol + 1) / 2;     // no field has more face-connected components
+    const LabelScratch sc(vol, cap);
+    if (sc.total <= c->L.o_type - c->L.o_fB) return run_labels(c, k, bx, threshold, (char *)c->fdst(), sc, (int)cap, out, max_out, n_out);
+    char *own = nullptr;
+    HIPCHECK(c, hipMalloc(&own, sc.total));
+    const lbm_status r = run_labels(c, k, bx, threshold, own, sc, (int)cap, out, max_out, n_out);
+    (void)hipFree(own);
     return r;
 }
 
@@ -1619,44 +1693,14 @@ lbm_status lbm_components_static(lbm_ctx *c, int k, const lbm_box *box, double t
     if (dev != c->device) return fail(c, LBM_EINVAL, "the context's device is not the current device");
     char *base = (char *)static_scratch_ptr(dev);
     if (!base) return fail(c, LBM_EDEVICE, "static scratch not resolved on this device");
-    int *lab = (int *)(base + SCR_LAB);
-    int *slot = (int *)(base + SCR_SLOT);
-    int *flags = (int *)(base + SCR_FLAGS);
-    CompStat *st = (CompStat *)(base + SCR_STATS);
-    lbm_component *sorted = (lbm_component *)(base + SCR_SORTED);
-    const StepArgs a = step_args(c);
-    const bool d2 = c->L.dim == 2;
-    if (d2) Launcher<2>::lab_init(c->L.storage, a, k, bx, (float)threshold, lab);
-    else Launcher<3>::lab_init(c->L.storage, a, k, bx, (float)threshold, lab);
-    for (int64_t round = 0;; round++) {
-        if (round > N) return fail(c, LBM_EDEVICE, "label propagation did not converge");
-        HIPCHECK(c, hipMemsetAsync(flags, 0, 4, c->stream));
-        if (d2) Launcher<2>::lab_prop(a, lab, flags, 4);
-        else Launcher<3>::lab_prop(a, lab, flags, 4);
-        int changed = 0;
-        HIPCHECK(c, hipMemcpyAsync(&changed, flags, 4, hipMemcpyDeviceToHost, c->stream));
-        HIPCHECK(c, hipStreamSynchronize(c->stream));
-        if (!changed) break;
-    }
-    HIPCHECK(c, hipMemsetAsync(flags + 1, 0, 4, c->stream));
-    if (d2) Launcher<2>::lab_roots(a, lab, slot, flags + 1);
-    else Launcher<3>::lab_roots(a, lab, slot, flags + 1);
-    int nr = 0;
-    HIPCHECK(c, hipMemcpyAsync(&nr, flags + 1, 4, hipMemcpyDeviceToHost, c->stream));
-    HIPCHECK(c, hipStreamSynchronize(c->stream));
-    if (nr > LBM_COMPONENTS_STATIC_MAX_COMPONENTS)
-        return fail(c, LBM_EINVAL, "more components than the static labelling scratch holds (" + std::to_string(nr) +
+    const LabelScratch sc(LBM_COMPONENTS_STATIC_MAX_NODES, LBM_COMPONENTS_STATIC_MAX_COMPONENTS);
+    int n = 0;
+    const lbm_status st = run_labels(c, k, bx, threshold, base, sc, LBM_COMPONENTS_STATIC_MAX_COMPONENTS, out, max_out, &n);
+    if (st != LBM_OK) return st;
+    if (n > LBM_COMPONENTS_STATIC_MAX_COMPONENTS)
+        return fail(c, LBM_EINVAL, "more components than the static labelling scratch holds (" + std::to_string(n) +
                                        " > " + std::to_string(LBM_COMPONENTS_STATIC_MAX_COMPONENTS) + ")");
-    *n_out = nr;
-    if (nr == 0) return LBM_OK;
-    if (d2) Launcher<2>::lab_stats(a, lab, slot, st, nr);
-    else Launcher<3>::lab_stats(a, lab, slot, st, nr);
-    hipLaunchKernelGGL(k_lab_order, dim3((nr + 255) / 256), dim3(256), 0, c->stream, st, nr, sorted);
-    HIPCHECK(c, hipGetLastError());
-    const int nc = std::min(nr, max_out);
-    if (nc > 0)
-        HIPCHECK(c, hipMemcpyAsync(out, sorted, sizeof(lbm_component) * nc, hipMemcpyDeviceToHost, c->stream));
-    HIPCHECK(c, hipStreamSynchronize(c->stream));
+    *n_out = n;
     return LBM_OK;
 }
 

@@ -52,3 +52,86 @@ def test_face_nodes(kind, width, storage):
     assert _step_error(c, storage) < TOL[storage]
     # a second step reads what the face kernels of the first one stored
     assert _step_error(c, storage, steps=2) < 2 * TOL[storage]
+
+
+def _components(field, lo):
+    """Face-connected components of a boolean [z, y, x] box, by first node of
+    the domain whose corner the box's lo is relative to."""
+    from scipy import ndimage
+    lab, n = ndimage.label(field, structure=ndimage.generate_binary_structure(3, 1))
+    out = []
+    for j, (sz, sy, sx) in enumerate(ndimage.find_objects(lab), 1):
+        zz, yy, xx = np.nonzero(lab[sz, sy, sx] == j)
+        zz, yy, xx = zz + sz.start + lo[2], yy + sy.start + lo[1], xx + sx.start + lo[0]
+        out.append((xx, yy, zz))
+    return out
+
+
+# rows and boxes around a wave (64 nodes) and a block (256), a box that leaves
+# the domain's rim out, more components than are ordered on the device, a
+# spiral (a chain as long as the box), one node, nothing
+PATTERNS = ["checker", "spiral", "stripes", "comb", "one", "none", "full"]
+
+
+@pytest.mark.parametrize("layout", ["caller", "face_last"])
+@pytest.mark.parametrize("shape", [(3, 3, 1), (63, 5, 1), (65, 66, 1), (257, 37, 1), (130, 129, 1), (5, 3, 4),
+                                   (66, 9, 7)])
+@pytest.mark.parametrize("pattern", PATTERNS)
+def test_label_patterns(pattern, shape, layout):
+    """Components and probe counts of planted fields equal a CPU labelling."""
+    import torch
+    from paper_2512_12934_amd.lbm import LBM
+    if layout == "face_last" and shape[2] == 1:
+        pytest.skip("a 3-D layout")
+    nx, ny, nz = shape
+    z, y, x = np.meshgrid(np.arange(nz), np.arange(ny), np.arange(nx), indexing="ij")
+    if pattern == "checker":
+        f = (x + y + z) % 2 == 0
+    elif pattern == "spiral":
+        f = np.zeros((nz, ny, nx), bool)
+        x0, x1, y0, y1 = 0, nx - 1, 0, ny - 1
+        while x0 <= x1 and y0 <= y1:
+            f[:, y0, max(0, x0 - 1):x1 + 1] = True
+            f[:, y0:y1 + 1, x1] = True
+            if y1 > y0:
+                f[:, y1, x0:x1 + 1] = True
+                f[:, min(y0 + 2, y1):y1 + 1, x0] = True
+            x0, x1, y0, y1 = x0 + 2, x1 - 2, y0 + 2, y1 - 2
+    elif pattern == "stripes":
+        f = y % 2 == 0
+    elif pattern == "comb":
+        f = (x % 2 == 0) | (y == ny - 1)
+    elif pattern == "one":
+        f = (x == nx // 2) & (y == ny - 1) & (z == 0)
+    else:
+        f = np.full((nz, ny, nx), pattern == "full")
+    dim = 2 if nz == 1 else 3
+    rho = np.where(f.reshape(-1), 1.0, 0.2)
+    c = cases.Case(f"labels_{pattern}", dim, shape, (True, True, True), (0.1, 0.1), 0.9,
+                   solid=np.zeros(f.size, np.uint8), rho0=np.stack([rho, 1.2 - rho]))
+    print(f"[gpu] {c.name} {shape} {layout}", flush=True)
+    sim = LBM(c, layout=layout)
+    boxes = [((0, 0, 0), shape)]
+    if min(nx, ny) > 3:
+        boxes.append(((1, 1, 0), (nx - 1, ny, nz)))
+    for lo, hi in boxes:
+        ref = []
+        for xx, yy, zz in _components(f[lo[2]:hi[2], lo[1]:hi[1], lo[0]:hi[0]], lo):
+            ref.append({"first": int((xx + nx * (yy + ny * zz)).min()), "size": len(xx),
+                        "lo": (int(xx.min()), int(yy.min()), int(zz.min())),
+                        "hi": (int(xx.max()) + 1, int(yy.max()) + 1, int(zz.max()) + 1)})
+        ref.sort(key=lambda r: r["first"])
+        got, n = sim.components(0, lo, hi, 0.6, max_out=max(1, len(ref)))
+        assert n == len(ref) and got == ref
+        if n <= 4096:
+            assert sim.components(0, lo, hi, 0.6, max_out=max(1, len(ref)), static=True) == (got, n)
+        count = torch.full((1,), -1, dtype=torch.int64, device="cuda:0")
+        sim.probe(0, lo, hi, 0.6, count)
+        assert int(count) == sum(r["size"] for r in ref)
+    # the labelling leaves the state as it was
+    before = sim.get_state()
+    other = LBM(c, layout=layout)
+    assert np.array_equal(before, other.get_state())
+    sim.step(2)
+    other.step(2)
+    assert np.array_equal(sim.get_state(), other.get_state())
