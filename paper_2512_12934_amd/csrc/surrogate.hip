@@ -5,16 +5,22 @@
 // by more than a threshold send the query back to the lattice Boltzmann
 // solver (the fallback mask).
 //
-// Training is full-batch Adam on the mean squared error:
-//   k_fwd_bwd  one block per (64-sample tile, member): forward, backward and
-//              the tile's partial gradient of every parameter (FP32, VALU)
-//   k_adam     per parameter: the tile partials summed in tile order (so the
-//              result does not depend on scheduling), then the Adam update
+// Training is full-batch Adam on the mean squared error, two launches per
+// epoch (per CHUNK samples of a larger set):
+//   k_fwd_bwd  one block per (16-sample tile, member): forward and backward,
+//              both 128 x 128 products on FP32 matrix instructions; leaves
+//              the activations and the back-propagated errors
+//   k_grad     per 16x16 tile of W2, or per 64 of the other parameters: the
+//              gradient, summed over 64-sample groups in order (so the result
+//              does not depend on scheduling), then the Adam update in place
 // Inference:
-//   k_predict  one block per 64 queries, every member in turn: layer 1 on
+//   k_predict  one block per 16 queries, several members at a time: layer 1 on
 //              VALU, layer 2 as 16x16x16 BF16 MFMA tiles with FP32
 //              accumulation, layer 3 on VALU; ensemble mean, standard
 //              deviation and the fallback flag.
+// FP32 matrix instructions round every product-sum like a chain of FMAs in
+// ascending k (checked bit for bit), so the sums have the order and the bits
+// of the plain loops over k.
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
@@ -29,7 +35,11 @@ namespace {
 
 constexpr int H = 128;                       // hidden width
 constexpr int NIN = 4, NOUT = 2;
-constexpr int TS = 64;                       // samples per block
+constexpr int QT = 16;                       // queries / samples per block
+constexpr int FT = 512;                      // threads per block of the training kernels
+constexpr int GROUP = 64;                    // samples whose gradient is summed before it joins the total
+constexpr int CHUNK = 8192;                  // samples whose activations are held at once
+constexpr int LH = H + 4;                    // row pitch of FP32 activations in LDS (rows 4 banks apart)
 // parameter vector of one member
 constexpr int O_W1 = 0;                      // [H][NIN]
 constexpr int O_B1 = O_W1 + H * NIN;         // [H]
@@ -74,281 +84,423 @@ __global__ void k_init(float *__restrict__ params, float *__restrict__ am, float
     av[t] = 0.0f;
 }
 
-// Forward and backward pass of one 64-sample tile through one member.
-// loss = sum over samples and outputs of (y - Y)^2 / (n * NOUT); the tile's
-// part of every gradient goes to gpart[member][tile][P], its loss to
-// lpart[member][tile].
-__global__ __launch_bounds__(256) void k_fwd_bwd(const float *__restrict__ params, const float *__restrict__ X,
-                                                 const float *__restrict__ Y, int n, float *__restrict__ gpart,
-                                                 float *__restrict__ lpart)
-{
-    const int tile = blockIdx.x, m = blockIdx.y, ntile = gridDim.x;
-    const float *w = params + (int64_t)m * P;
-    float *g = gpart + ((int64_t)m * ntile + tile) * P;
-    __shared__ float s_w2t[H * H];           // W2 transposed: s_w2t[j * H + i] = W2[i][j]
-    __shared__ float s_h1[TS * H];           // tanh(layer 1), then dz1
-    __shared__ float s_h2[TS * H];           // tanh(layer 2), then dz2
-    __shared__ float s_x[TS * NIN];
-    __shared__ float s_dy[TS * NOUT];
-    __shared__ float s_red[256];
-    const int tid = threadIdx.x;
-    const int s0 = tile * TS;
-    const int ns = min(TS, n - s0);          // valid samples of this tile
+typedef short bf16x4 __attribute__((ext_vector_type(4)));
+typedef float f32x4 __attribute__((ext_vector_type(4)));
 
-    for (int e = tid; e < H * H; e += 256) {
-        const int i = e / H, j = e % H;
-        s_w2t[j * H + i] = w[O_W2 + e];
-    }
-    for (int e = tid; e < TS * NIN; e += 256) s_x[e] = e / NIN < ns ? X[(int64_t)s0 * NIN + e] : 0.0f;
+// What one chunk of samples leaves for the gradient: activations and errors
+// [member][rows][H], output errors and loss terms [member][rows][NOUT].
+struct Acts {
+    float *h1, *h2, *z2, *z1, *dy, *lterm;
+    int rows;                                // capacity per member
+};
+
+// Forward and backward pass of one 16-sample tile through one member.
+// loss = sum over samples and outputs of (y - Y)^2 / (n * NOUT).  Row s of
+// the chunk is sample base + s; rows past the last sample up to the tile's end
+// carry zero errors.
+//
+// The work of a tile is three 128-deep products of 16 x 128 (0.5 MFLOP each):
+// what bounds it is latency, so the tile is small (125 blocks for 385 samples
+// and 5 members, where 64-sample tiles gave 35), every weight a wave needs is
+// loaded before the layer that uses it, and the products run on matrix
+// instructions, which read each activation from LDS once per 16 outputs
+// (VALU loops read it once per output and held the whole of W2 in LDS: 102 us
+// a launch for 385 samples, 5 members; now 11.5 us here and 7.8 us in k_grad,
+// against 4.9 + 4.6 us for the separate gradient-sum and loss launches).
+__global__ __launch_bounds__(FT) void k_fwd_bwd(const float *__restrict__ params, const float *__restrict__ w2t,
+                                                 const float *__restrict__ X, const float *__restrict__ Y, int n,
+                                                 int base, Acts act)
+{
+    const int m = blockIdx.y, s0 = blockIdx.x * QT;
+    const float *w = params + (int64_t)m * P;
+    const float *wt = w2t + (int64_t)m * H * H;
+    const int64_t arow = (int64_t)m * act.rows + s0;
+    __shared__ __align__(16) float s_h1[QT * LH], s_h2[QT * LH], s_z2[QT * LH], s_w3[NOUT * LH];
+    __shared__ float s_x[QT * NIN], s_dy[QT * NOUT];
+    const int tid = threadIdx.x, wave = tid / 64, lane = tid % 64, r = lane % 16, q = lane / 16;
+    const int ns = min(QT, n - base - s0);   // valid samples of this tile
+    const int col = 16 * wave + r;           // this lane's output column
+
+    // layer 2 weights in operand order: W2[col][4t + q]
+    float wf[H / 4];
+#pragma unroll
+    for (int t = 0; t < H / 4; t++) wf[t] = wt[(4 * t + q) * H + col];
+    if (tid < QT * NIN) s_x[tid] = tid / NIN < ns ? X[(int64_t)(base + s0) * NIN + tid] : 0.0f;
+    if (tid < NOUT * H) s_w3[tid / H * LH + tid % H] = w[O_W3 + tid];
     __syncthreads();
 
     // layer 1: h1[s][i] = tanh(b1[i] + sum_c W1[i][c] x[s][c])
-    for (int e = tid; e < TS * H; e += 256) {
-        const int s = e / H, i = e % H;
-        float a = w[O_B1 + i];
-        for (int c = 0; c < NIN; c++) a = fmaf(w[O_W1 + i * NIN + c], s_x[s * NIN + c], a);
-        s_h1[e] = tanhf(a);
+    const int i = tid % H, sb = tid / H;
+    {
+        const float b1 = w[O_B1 + i];
+        float w1[NIN];
+        for (int c = 0; c < NIN; c++) w1[c] = w[O_W1 + i * NIN + c];
+        for (int s = sb; s < QT; s += FT / H) {
+            float a = b1;
+            for (int c = 0; c < NIN; c++) a = fmaf(w1[c], s_x[s * NIN + c], a);
+            const float h = tanhf(a);
+            s_h1[s * LH + i] = h;
+            act.h1[(arow + s) * H + i] = h;
+        }
     }
     __syncthreads();
 
-    // layer 2: thread owns unit i and samples sb, sb + 2, ...
-    const int i = tid % H, sb = tid / H;
+    // layer 2: samples x 16 columns per wave, summed from the bias upwards in j
     {
-        float acc[TS / 2];
-        for (int k = 0; k < TS / 2; k++) acc[k] = w[O_B2 + i];
-        for (int j = 0; j < H; j++) {
-            const float wij = s_w2t[j * H + i];
+        const float b2 = w[O_B2 + col];
+        f32x4 acc = {b2, b2, b2, b2};
 #pragma unroll
-            for (int k = 0; k < TS / 2; k++) acc[k] = fmaf(s_h1[(sb + 2 * k) * H + j], wij, acc[k]);
-        }
+        for (int t = 0; t < H / 4; t++)
+            acc = __builtin_amdgcn_mfma_f32_16x16x4f32(s_h1[r * LH + 4 * t + q], wf[t], acc, 0, 0, 0);
+        // the weights of the backward product, on their way while tanh runs:
+        // W2[4t + q][col]
 #pragma unroll
-        for (int k = 0; k < TS / 2; k++) s_h2[(sb + 2 * k) * H + i] = tanhf(acc[k]);
+        for (int t = 0; t < H / 4; t++) wf[t] = w[O_W2 + (4 * t + q) * H + col];
+        for (int e = 0; e < 4; e++) s_h2[(4 * q + e) * LH + col] = tanhf(acc[e]);
     }
     __syncthreads();
 
     // layer 3 and the loss: one thread per (sample, output)
-    float lsum = 0.0f;
-    if (tid < TS * NOUT) {
+    if (tid < QT * NOUT) {
         const int s = tid / NOUT, o = tid % NOUT;
         float y = w[O_B3 + o];
-        for (int j = 0; j < H; j++) y = fmaf(w[O_W3 + o * H + j], s_h2[s * H + j], y);
-        float d = 0.0f;
+#pragma unroll 8
+        for (int j = 0; j < H; j += 4) {
+            const float4 a = *(const float4 *)(s_w3 + o * LH + j), b = *(const float4 *)(s_h2 + s * LH + j);
+            y = fmaf(a.x, b.x, y);
+            y = fmaf(a.y, b.y, y);
+            y = fmaf(a.z, b.z, y);
+            y = fmaf(a.w, b.w, y);
+        }
+        float d = 0.0f, lt = 0.0f;
         if (s < ns) {
-            const float r = y - Y[(int64_t)(s0 + s) * NOUT + o];
-            lsum = r * r / (float)(n * NOUT);
-            d = 2.0f * r / (float)(n * NOUT);
+            const float res = y - Y[(int64_t)(base + s0 + s) * NOUT + o];
+            lt = res * res / (float)(n * NOUT);
+            d = 2.0f * res / (float)(n * NOUT);
         }
         s_dy[tid] = d;
+        act.dy[arow * NOUT + tid] = d;
+        act.lterm[arow * NOUT + tid] = lt;
     }
-    s_red[tid] = lsum;
     __syncthreads();
-    for (int st = 128; st > 0; st >>= 1) {
-        if (tid < st) s_red[tid] += s_red[tid + st];
+    // dz2[s][i] = (sum_o dy[s][o] W3[o][i]) (1 - h2^2)
+    for (int s = sb; s < QT; s += FT / H) {
+        float d = 0.0f;
+        for (int o = 0; o < NOUT; o++) d = fmaf(s_dy[s * NOUT + o], s_w3[o * LH + i], d);
+        const float h = s_h2[s * LH + i];
+        const float z = d * (1.0f - h * h);
+        s_z2[s * LH + i] = z;
+        act.z2[(arow + s) * H + i] = z;
+        act.h2[(arow + s) * H + i] = h;
+    }
+    __syncthreads();
+    // dz1[s][j] = (sum_i dz2[s][i] W2[i][j]) (1 - h1^2)
+    f32x4 acc = {0.0f, 0.0f, 0.0f, 0.0f};
+#pragma unroll
+    for (int t = 0; t < H / 4; t++)
+        acc = __builtin_amdgcn_mfma_f32_16x16x4f32(s_z2[r * LH + 4 * t + q], wf[t], acc, 0, 0, 0);
+    for (int e = 0; e < 4; e++) {
+        const int s = 4 * q + e;
+        const float h = s_h1[s * LH + col];
+        act.z1[(arow + s) * H + col] = acc[e] * (1.0f - h * h);
+    }
+}
+
+// Units of k_grad per member: the 16x16 tiles of W2, 64 of the other
+// parameters each (b2, W3, W1 and b1, b3), the loss.
+constexpr int G_TILES = (H / 16) * (H / 16);
+constexpr int G_REST = H + NOUT * H + (NIN + 1) * H + NOUT;
+constexpr int G_VECS = (G_REST + 63) / 64;
+constexpr int G_UNITS = G_TILES + G_VECS + 1;
+
+struct Adam {
+    float lr, b1, b2, eps, c1, c2;
+};
+
+// The gradient of one unit over the rows [0, nr) of a chunk: wave v takes the
+// 64-sample groups v, v + 8, ..., and the groups' sums are added in order.
+// The total starts from 0, or from gsum after an earlier chunk; after the
+// last chunk it is copied to gout and / or updates the parameters.
+__global__ __launch_bounds__(FT) void k_grad(float *__restrict__ params, float *__restrict__ w2t,
+                                              float *__restrict__ am, float *__restrict__ av,
+                                              float *__restrict__ gsum, const float *__restrict__ X, int base, int nr,
+                                              Acts act, int first, int last, int update, Adam ad,
+                                              float *__restrict__ gout, float *__restrict__ loss)
+{
+    const int m = blockIdx.y, unit = blockIdx.x;
+    const int tid = threadIdx.x, wave = tid / 64, lane = tid % 64, r = lane % 16, q = lane / 16;
+    const int ng = (nr + GROUP - 1) / GROUP;
+    const int64_t row0 = (int64_t)m * act.rows;
+    constexpr int NW = FT / 64;
+    __shared__ float s_part[NW * 256];
+    const bool tile = unit < G_TILES, is_loss = unit == G_UNITS - 1;
+    // the parameter this thread totals, and (other units) its two factors
+    int p = -1;
+    const float *pa = nullptr, *pb = nullptr;
+    int sa = 0, sbs = 0;
+    if (tile && tid < 256) {
+        p = O_W2 + (16 * (unit / 8) + tid / 16) * H + 16 * (unit % 8) + tid % 16;
+    } else if (!tile && !is_loss) {
+        int e = (unit - G_TILES) * 64 + lane;
+        if (e < H) {                                             // b2: sum of dz2
+            p = O_B2 + e;
+            pa = act.z2 + row0 * H + e;
+            sa = H;
+        } else if ((e -= H) < NOUT * H) {                        // W3: dy h2
+            const int o = e / H;
+            p = O_W3 + e;
+            pa = act.h2 + row0 * H + e % H;
+            sa = H;
+            pb = act.dy + row0 * NOUT + o;
+            sbs = NOUT;
+        } else if ((e -= NOUT * H) < (NIN + 1) * H) {            // W1, b1: dz1 x, sum of dz1
+            const int c = e / H, j = e % H;
+            p = c < NIN ? O_W1 + j * NIN + c : O_B1 + j;
+            pa = act.z1 + row0 * H + j;
+            sa = H;
+            if (c < NIN) {
+                pb = X + (int64_t)base * NIN + c;
+                sbs = NIN;
+            }
+        } else if ((e -= (NIN + 1) * H) < NOUT) {                // b3: sum of dy
+            p = O_B3 + e;
+            pa = act.dy + row0 * NOUT + e;
+            sa = NOUT;
+        }
+    }
+    const int64_t t = (int64_t)m * P + p;
+    float total = 0.0f;
+    if (!first) {
+        if (is_loss) total = loss[m];
+        else if (p >= 0) total = gsum[t];
+    }
+    for (int g0 = 0; g0 < ng; g0 += NW) {
+        const int g = g0 + wave;
+        if (g < ng) {
+            const int s0 = g * GROUP, left = nr - s0;
+            if (tile) {
+                // rows beyond the last sample's tile add nothing
+                const int steps = left >= GROUP ? GROUP / 4 : (left + QT - 1) / QT * (QT / 4);
+                const float *za = act.z2 + (row0 + s0 + q) * H + 16 * (unit / 8) + r;
+                const float *hb = act.h1 + (row0 + s0 + q) * H + 16 * (unit % 8) + r;
+                f32x4 acc = {0.0f, 0.0f, 0.0f, 0.0f};
+                float a[GROUP / 4], b[GROUP / 4];
+#pragma unroll
+                for (int k = 0; k < GROUP / 4; k++) {
+                    a[k] = za[4 * k * H];
+                    b[k] = hb[4 * k * H];
+                }
+#pragma unroll
+                for (int k = 0; k < GROUP / 4; k++) {
+                    // (the buffers hold whole groups; what lies there is not used)
+                    a[k] = k < steps ? a[k] : 0.0f;
+                    b[k] = k < steps ? b[k] : 0.0f;
+                }
+#pragma unroll
+                for (int k = 0; k < GROUP / 4; k++) acc = __builtin_amdgcn_mfma_f32_16x16x4f32(a[k], b[k], acc, 0, 0, 0);
+                for (int e = 0; e < 4; e++) s_part[wave * 256 + (4 * q + e) * 16 + r] = acc[e];
+            } else if (is_loss) {
+                const float *l = act.lterm + (row0 + s0) * NOUT;
+                const int have = min(left, GROUP) * NOUT;
+                float v = (lane < have ? l[lane] : 0.0f) + (lane + 64 < have ? l[lane + 64] : 0.0f);
+                for (int o = 32; o > 0; o >>= 1) v += __shfl_down(v, o, 64);
+                if (lane == 0) s_part[wave * 64] = v;
+            } else if (p >= 0) {
+                const int rows = min(left, GROUP);
+                const float *qa = pa + (int64_t)s0 * sa, *qb = pb ? pb + (int64_t)s0 * sbs : nullptr;
+                float a = 0.0f;
+                int s = 0;
+                // 16 rows' loads in flight at a time
+                for (; s + 16 <= rows; s += 16) {
+                    float f[16], h[16];
+#pragma unroll
+                    for (int k = 0; k < 16; k++) f[k] = qa[(s + k) * sa];
+                    if (qb) {
+#pragma unroll
+                        for (int k = 0; k < 16; k++) h[k] = qb[(s + k) * sbs];
+                    } else {
+#pragma unroll
+                        for (int k = 0; k < 16; k++) h[k] = 1.0f;
+                    }
+#pragma unroll
+                    for (int k = 0; k < 16; k++) a = fmaf(f[k], h[k], a);
+                }
+                for (; s < rows; s++) a = fmaf(qa[s * sa], qb ? qb[s * sbs] : 1.0f, a);
+                s_part[wave * 64 + lane] = a;
+            }
+        }
+        __syncthreads();
+        const int stride = tile ? 256 : 64, at = tile ? tid : lane;
+        if (tid < 256)
+            for (int v = 0; v < NW && g0 + v < ng; v++) total += s_part[v * stride + at];
         __syncthreads();
     }
-    if (tid == 0) lpart[(int64_t)m * ntile + tile] = s_red[0];
-
-    // layer 3 gradients: dW3[o][j] = sum_s dy[s][o] h2[s][j]; db3[o] = sum_s dy[s][o]
-    for (int e = tid; e < NOUT * H; e += 256) {
-        const int o = e / H, j = e % H;
-        float a = 0.0f;
-        for (int s = 0; s < TS; s++) a = fmaf(s_dy[s * NOUT + o], s_h2[s * H + j], a);
-        g[O_W3 + e] = a;
+    if (is_loss) {
+        if (tid == 0) loss[m] = total;
+        return;
     }
-    if (tid < NOUT) {
-        float a = 0.0f;
-        for (int s = 0; s < TS; s++) a += s_dy[s * NOUT + tid];
-        g[O_B3 + tid] = a;
+    if (p < 0 || (!tile && wave != 0)) return;
+    if (!last) {
+        gsum[t] = total;
+        return;
     }
-    __syncthreads();
-    // dz2[s][i] = (sum_o dy[s][o] W3[o][i]) (1 - h2^2), in place of h2
-    for (int e = tid; e < TS * H; e += 256) {
-        const int s = e / H, u = e % H;
-        float d = 0.0f;
-        for (int o = 0; o < NOUT; o++) d = fmaf(s_dy[s * NOUT + o], w[O_W3 + o * H + u], d);
-        const float h = s_h2[e];
-        s_h2[e] = d * (1.0f - h * h);
-    }
-    __syncthreads();
-    // dW2[i][j] = sum_s dz2[s][i] h1[s][j]: thread owns unit i and 64 of the j
-    {
-        const int jb = (tid / H) * (H / 2);
-        float acc[H / 2];
-        for (int k = 0; k < H / 2; k++) acc[k] = 0.0f;
-        float db = 0.0f;
-        for (int s = 0; s < TS; s++) {
-            const float dz = s_h2[s * H + i];
-            db += dz;
-#pragma unroll
-            for (int k = 0; k < H / 2; k++) acc[k] = fmaf(dz, s_h1[s * H + jb + k], acc[k]);
-        }
-        for (int k = 0; k < H / 2; k++) g[O_W2 + i * H + jb + k] = acc[k];
-        if (jb == 0) g[O_B2 + i] = db;
-    }
-    __syncthreads();
-    // dz1[s][j] = (sum_i dz2[s][i] W2[i][j]) (1 - h1^2): thread owns j and samples sb, sb + 2, ...
-    {
-        const int j = tid % H;
-        float acc[TS / 2];
-        for (int k = 0; k < TS / 2; k++) acc[k] = 0.0f;
-        for (int u = 0; u < H; u++) {
-            const float wuj = w[O_W2 + u * H + j];
-#pragma unroll
-            for (int k = 0; k < TS / 2; k++) acc[k] = fmaf(s_h2[(sb + 2 * k) * H + u], wuj, acc[k]);
-        }
-        __syncthreads();                     // every read of h1 by the dW2 pass is done
-#pragma unroll
-        for (int k = 0; k < TS / 2; k++) {
-            const float h = s_h1[(sb + 2 * k) * H + j];
-            s_h1[(sb + 2 * k) * H + j] = acc[k] * (1.0f - h * h);
-        }
-    }
-    __syncthreads();
-    // dW1[j][c] = sum_s dz1[s][j] x[s][c]; db1[j] = sum_s dz1[s][j]
-    for (int e = tid; e < H * (NIN + 1); e += 256) {
-        const int j = e / (NIN + 1), c = e % (NIN + 1);
-        float a = 0.0f;
-        for (int s = 0; s < TS; s++) a = fmaf(s_h1[s * H + j], c < NIN ? s_x[s * NIN + c] : 1.0f, a);
-        if (c < NIN) g[O_W1 + j * NIN + c] = a;
-        else g[O_B1 + j] = a;
-    }
-}
-
-// gradient = tile partials summed in tile order; optional copy out; Adam step
-__global__ void k_adam(float *__restrict__ params, float *__restrict__ am, float *__restrict__ av,
-                       const float *__restrict__ gpart, int members, int ntile, float lr, float b1, float b2,
-                       float eps, float c1, float c2, int update, float *__restrict__ gout)
-{
-    const int64_t t = (int64_t)blockIdx.x * 256 + threadIdx.x;
-    if (t >= (int64_t)members * P) return;
-    const int m = (int)(t / P), p = (int)(t % P);
-    float gsum = 0.0f;
-    for (int k = 0; k < ntile; k++) gsum += gpart[((int64_t)m * ntile + k) * P + p];
-    if (gout) gout[t] = gsum;
+    if (gout) gout[t] = total;
     if (!update) return;
-    const float mm = b1 * am[t] + (1.0f - b1) * gsum;
-    const float vv = b2 * av[t] + (1.0f - b2) * gsum * gsum;
+    const float mm = ad.b1 * am[t] + (1.0f - ad.b1) * total;
+    const float vv = ad.b2 * av[t] + (1.0f - ad.b2) * total * total;
     am[t] = mm;
     av[t] = vv;
-    params[t] -= lr * (mm / c1) / (sqrtf(vv / c2) + eps);
+    const float nw = params[t] - ad.lr * (mm / ad.c1) / (sqrtf(vv / ad.c2) + ad.eps);
+    params[t] = nw;
+    if (tile) w2t[(int64_t)m * H * H + (p - O_W2) % H * H + (p - O_W2) / H] = nw;
 }
 
-// loss per member: tile partials in tile order
-__global__ void k_loss(const float *__restrict__ lpart, int members, int ntile, float *__restrict__ out)
+// W2 of every member transposed, as the forward product of training reads it
+// (k_grad keeps it up to date)
+__global__ void k_w2_transpose(const float *__restrict__ params, int members, float *__restrict__ w2t)
 {
-    const int m = threadIdx.x;
-    if (m >= members) return;
-    float a = 0.0f;
-    for (int k = 0; k < ntile; k++) a += lpart[m * ntile + k];
-    out[m] = a;
+    const int64_t t = (int64_t)blockIdx.x * 256 + threadIdx.x;
+    if (t >= (int64_t)members * H * H) return;
+    const int m = (int)(t / (H * H)), e = (int)(t % (H * H)), j = e / H, i = e % H;
+    w2t[t] = params[(int64_t)m * P + O_W2 + i * H + j];
 }
 
-// W2 of every member as BF16 (round to nearest even) for inference
+// W2 of every member as BF16 (round to nearest even) for inference, in the
+// order the matrix instructions of k_predict read it: [column tile][pair of
+// 16-wide k chunks][lane][chunk of the pair][4 values of k]
 __global__ void k_w2_bf16(const float *__restrict__ params, int members, uint16_t *__restrict__ w2)
 {
     const int64_t t = (int64_t)blockIdx.x * 256 + threadIdx.x;
     if (t >= (int64_t)members * H * H) return;
     const int m = (int)(t / (H * H)), e = (int)(t % (H * H));
-    w2[t] = to_bf16(params[(int64_t)m * P + O_W2 + e]);
+    const int ct = e / (16 * H), kp = e / 512 % 4, lane = e / 8 % 64, c = e / 4 % 2, k = e % 4;
+    const int i = 16 * ct + lane % 16, j = 32 * kp + 16 * c + 4 * (lane / 16) + k;
+    w2[t] = to_bf16(params[(int64_t)m * P + O_W2 + i * H + j]);
 }
 
-typedef short bf16x4 __attribute__((ext_vector_type(4)));
-typedef float f32x4 __attribute__((ext_vector_type(4)));
+// One block of 512 threads (8 waves) answers 16 queries, `mc` members at a
+// time: wave v owns the columns 16v .. 16v + 15 of layer 2 of each of them.
+//
+// Two thirds of the time of a block is tanh, the rest latency, so the queries
+// are spread thin (4096 queries are 256 blocks, one per CU; 64-query blocks
+// left three CUs of four idle) and the members of a pass run side by side, not
+// in turn: their layer-3 sums are 128-long dependent chains.  4096 queries and
+// 5 members take 11.7 us a call, against 99 us with 64-query blocks, members
+// in turn and 2-byte loads of W2.
+constexpr int PT = 512;                      // threads per block
+constexpr int LB = H + 8;                    // row pitch of BF16 activations in LDS
+constexpr int MC_MAX = 5;                    // members per pass (69 KB of LDS: two blocks per CU)
+constexpr size_t predict_lds(int mc) { return (size_t)mc * (QT * LH * 4 + QT * LB * 2 + NOUT * LH * 4); }
 
-// One block of 256 threads (4 waves) answers 64 queries with every member.
-__global__ __launch_bounds__(256) void k_predict(const float *__restrict__ params, const uint16_t *__restrict__ w2,
-                                                 int members, const float *__restrict__ X, int n,
-                                                 float *__restrict__ mean, float *__restrict__ sd,
-                                                 uint8_t *__restrict__ fallback, float thresh, float2 oscale,
-                                                 float2 oshift)
+__global__ __launch_bounds__(PT) void k_predict(const float *__restrict__ params, const uint16_t *__restrict__ w2,
+                                                int members, int mc, const float *__restrict__ X, int n,
+                                                float *__restrict__ mean, float *__restrict__ sd,
+                                                uint8_t *__restrict__ fallback, float thresh, float2 oscale,
+                                                float2 oshift)
 {
-    __shared__ uint16_t s_h1[TS * H];        // layer-1 activations, BF16
-    __shared__ float s_h2[TS * H];           // layer-2 activations
-    __shared__ float s_y[TS * NOUT];
-    __shared__ float s_sum[TS * NOUT], s_sq[TS * NOUT];
+    extern __shared__ __align__(16) unsigned char s_dyn[];
+    float *s_h2 = (float *)s_dyn;                                // [mc][QT][LH] layer-2 activations
+    float *s_w3 = s_h2 + mc * QT * LH;                           // [mc][NOUT][LH]
+    uint16_t *s_h1 = (uint16_t *)(s_w3 + mc * NOUT * LH);        // [mc][QT][LB] layer-1 activations, BF16
+    __shared__ float s_x[QT * NIN], s_y[MC_MAX * QT * NOUT];
     const int tid = threadIdx.x, wave = tid / 64, lane = tid % 64;
-    const int s0 = blockIdx.x * TS;
-    const int ns = min(TS, n - s0);
-    if (tid < TS * NOUT) {
-        s_sum[tid] = 0.0f;
-        s_sq[tid] = 0.0f;
-    }
-    for (int m = 0; m < members; m++) {
-        const float *w = params + (int64_t)m * P;
-        const uint16_t *w2m = w2 + (int64_t)m * H * H;
+    const int s0 = blockIdx.x * QT;
+    const int ns = min(QT, n - s0);
+    if (tid < QT * NIN) s_x[tid] = tid / NIN < ns ? X[(int64_t)s0 * NIN + tid] : 0.0f;
+    float sum = 0.0f, sq = 0.0f;                                 // of query tid / 2, output tid % 2 (tid < 32)
+    for (int m0 = 0; m0 < members; m0 += mc) {
+        const int nm = min(mc, members - m0);
         __syncthreads();
-        for (int e = tid; e < TS * H; e += 256) {
-            const int s = e / H, i = e % H;
-            float a = w[O_B1 + i];
-            if (s < ns)
-                for (int c = 0; c < NIN; c++) a = fmaf(w[O_W1 + i * NIN + c], X[(int64_t)(s0 + s) * NIN + c], a);
-            s_h1[e] = to_bf16(tanhf(a));
+        const int i = tid % H, sb = tid / H;
+        for (int m = 0; m < nm; m++) {
+            const float *w = params + (int64_t)(m0 + m) * P;
+            const float b1 = w[O_B1 + i];
+            float w1[NIN];
+            for (int c = 0; c < NIN; c++) w1[c] = w[O_W1 + i * NIN + c];
+            for (int s = sb; s < QT; s += PT / H) {
+                float a = b1;
+                if (s < ns)
+                    for (int c = 0; c < NIN; c++) a = fmaf(w1[c], s_x[s * NIN + c], a);
+                s_h1[(m * QT + s) * LB + i] = to_bf16(tanhf(a));
+            }
+            if (tid < NOUT * H) s_w3[(m * NOUT + tid / H) * LH + tid % H] = w[O_W3 + tid];
         }
         __syncthreads();
-        // z2 = h1 W2^T: wave w owns sample rows 16w .. 16w + 15 and all 8
-        // column tiles.  16x16x16 operands: lane l holds row (A) / column (B)
+        // z2 = h1 W2^T.  16x16x16 operands: lane l holds row (A) / column (B)
         // l % 16 and k = 4 (l / 16) .. +3 of the 16-wide k chunk; the result
         // holds column l % 16 and rows 4 (l / 16) .. +3.
-        const int r = lane % 16, kq = 4 * (lane / 16);
-        for (int ct = 0; ct < H / 16; ct++) {
+        const int r = lane % 16, q = lane / 16, col = 16 * wave + r;
+        for (int m = 0; m < nm; m++) {
+            const float b2 = params[(int64_t)(m0 + m) * P + O_B2 + col];
+            const uint4 *wb = (const uint4 *)(w2 + (int64_t)(m0 + m) * H * H + wave * 16 * H) + lane;
+            uint4 bw[4];
+#pragma unroll
+            for (int kp = 0; kp < 4; kp++) bw[kp] = wb[64 * kp];
             f32x4 acc = {0.0f, 0.0f, 0.0f, 0.0f};
-            for (int kc = 0; kc < H; kc += 16) {
-                bf16x4 a, b;
-                const uint16_t *pa = s_h1 + (16 * wave + r) * H + kc + kq;
-                const uint16_t *pb = w2m + (int64_t)(16 * ct + r) * H + kc + kq;
-                for (int q = 0; q < 4; q++) {
-                    a[q] = (short)pa[q];
-                    b[q] = (short)pb[q];
-                }
-                acc = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(a, b, acc, 0, 0, 0);
+#pragma unroll
+            for (int kp = 0; kp < 4; kp++) {
+                const uint2 lo = make_uint2(bw[kp].x, bw[kp].y), hi = make_uint2(bw[kp].z, bw[kp].w);
+                const uint16_t *pa = s_h1 + (m * QT + r) * LB + 32 * kp + 4 * q;
+                const uint2 alo = *(const uint2 *)pa, ahi = *(const uint2 *)(pa + 16);
+                acc = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(__builtin_bit_cast(bf16x4, alo),
+                                                                __builtin_bit_cast(bf16x4, lo), acc, 0, 0, 0);
+                acc = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(__builtin_bit_cast(bf16x4, ahi),
+                                                                __builtin_bit_cast(bf16x4, hi), acc, 0, 0, 0);
             }
-            const int col = 16 * ct + r;
-            for (int q = 0; q < 4; q++) {
-                const int row = 16 * wave + kq + q;
-                s_h2[row * H + col] = tanhf(acc[q] + w[O_B2 + col]);
-            }
+            for (int e = 0; e < 4; e++) s_h2[(m * QT + 4 * q + e) * LH + col] = tanhf(acc[e] + b2);
         }
         __syncthreads();
-        if (tid < TS * NOUT) {
-            const int s = tid / NOUT, o = tid % NOUT;
-            float y = w[O_B3 + o];
-            for (int j = 0; j < H; j++) y = fmaf(w[O_W3 + o * H + j], s_h2[s * H + j], y);
+        if (tid < nm * QT * NOUT) {
+            const int m = tid / (QT * NOUT), s = tid / NOUT % QT, o = tid % NOUT;
+            float y = params[(int64_t)(m0 + m) * P + O_B3 + o];
+            const float *w3 = s_w3 + (m * NOUT + o) * LH, *h2 = s_h2 + (m * QT + s) * LH;
+#pragma unroll 4
+            for (int j = 0; j < H; j += 4) {
+                const float4 a = *(const float4 *)(w3 + j), b = *(const float4 *)(h2 + j);
+                y = fmaf(a.x, b.x, y);
+                y = fmaf(a.y, b.y, y);
+                y = fmaf(a.z, b.z, y);
+                y = fmaf(a.w, b.w, y);
+            }
             // the caller's units (the statistics and the fallback test use them)
             y = o == 0 ? fmaf(y, oscale.x, oshift.x) : fmaf(y, oscale.y, oshift.y);
-            s_sum[tid] += y;
-            s_sq[tid] += y * y;
+            s_y[tid] = y;
         }
+        __syncthreads();
+        if (tid < QT * NOUT)
+            for (int m = 0; m < nm; m++) {
+                const float y = s_y[m * QT * NOUT + tid];
+                sum += y;
+                sq += y * y;
+            }
     }
-    __syncthreads();
-    if (tid < TS * NOUT) {
+    if (tid < 64) {                                              // the first wave, whole, for the exchange below
         const int s = tid / NOUT;
-        const float mu = s_sum[tid] / (float)members;
-        const float var = fmaxf(s_sq[tid] / (float)members - mu * mu, 0.0f);
-        s_y[tid] = mu;
-        if (s < ns) {
+        const bool live = tid < QT * NOUT && s < ns;
+        const float mu = sum / (float)members;
+        const float var = fmaxf(sq / (float)members - mu * mu, 0.0f);
+        const int off = sqrtf(var) > thresh * fabsf(mu) ? 1 : 0;
+        const int any = off | __shfl_xor(off, 1, 64);
+        if (live) {
             mean[(int64_t)s0 * NOUT + tid] = mu;
             sd[(int64_t)s0 * NOUT + tid] = sqrtf(var);
+            if (tid % NOUT == 0) fallback[s0 + s] = any ? 1 : 0;
         }
-        s_sum[tid] = sqrtf(var) > thresh * fabsf(mu) ? 1.0f : 0.0f;
-    }
-    __syncthreads();
-    if (tid < TS && tid < ns) {
-        bool fb = false;
-        for (int o = 0; o < NOUT; o++) fb = fb || s_sum[tid * NOUT + o] != 0.0f;
-        fallback[s0 + tid] = fb ? 1 : 0;
     }
 }
 
 }  // namespace
 
 struct surr_ctx {
-    int members = 0, max_n = 0, ntile_max = 0;
+    int members = 0, max_n = 0;
     char *ws = nullptr;
     hipStream_t stream = nullptr;
-    float *params = nullptr, *am = nullptr, *av = nullptr, *gpart = nullptr, *lpart = nullptr, *loss = nullptr;
+    float *params = nullptr, *am = nullptr, *av = nullptr, *gsum = nullptr, *w2t = nullptr, *loss = nullptr;
+    Acts act{};
     uint16_t *w2 = nullptr;
     int64_t adam_t = 0;
-    bool w2_fresh = false;
+    bool w2_fresh = false;     // w2 holds the current weights
+    bool w2t_fresh = false;    // w2t does
     std::string err;
 };
 
@@ -360,20 +512,23 @@ constexpr size_t SALIGN = 256;
 size_t salign(size_t v) { return (v + SALIGN - 1) / SALIGN * SALIGN; }
 
 struct SLayout {
-    size_t params, am, av, gpart, lpart, loss, w2, total;
+    size_t params, am, av, gsum, w2t, act[4], out[2], loss, w2, total;
+    int rows;
 };
 
 SLayout surr_layout(int members, int max_n)
 {
-    const int nt = (max_n + TS - 1) / TS;
     SLayout L{};
+    L.rows = std::min((max_n + GROUP - 1) / GROUP * GROUP, CHUNK);
     size_t o = 0;
     auto take = [&](size_t b) { size_t at = o; o += salign(std::max<size_t>(b, 1)); return at; };
     L.params = take((size_t)members * P * 4);
     L.am = take((size_t)members * P * 4);
     L.av = take((size_t)members * P * 4);
-    L.gpart = take((size_t)members * nt * P * 4);
-    L.lpart = take((size_t)members * nt * 4);
+    L.gsum = take((size_t)members * P * 4);
+    L.w2t = take((size_t)members * H * H * 4);
+    for (auto &a : L.act) a = take((size_t)members * L.rows * H * 4);
+    for (auto &a : L.out) a = take((size_t)members * L.rows * NOUT * 4);
     L.loss = take((size_t)members * 4);
     L.w2 = take((size_t)members * H * H * 2);
     L.total = o;
@@ -403,18 +558,27 @@ bool args_ok(int members, int hidden, int max_n)
 // given), Adam step if update
 lbm_status pass(surr_ctx *c, const float *X, const float *Y, int n, float lr, bool update, float *gout)
 {
-    const int nt = (n + TS - 1) / TS;
-    hipLaunchKernelGGL(k_fwd_bwd, dim3(nt, c->members), dim3(256), 0, c->stream, c->params, X, Y, n, c->gpart,
-                       c->lpart);
-    const float b1 = 0.9f, b2 = 0.999f, eps = 1e-8f;
-    if (update) c->adam_t++;
-    const float c1 = update ? 1.0f - std::pow(b1, (float)c->adam_t) : 1.0f;
-    const float c2 = update ? 1.0f - std::pow(b2, (float)c->adam_t) : 1.0f;
-    const int64_t np = (int64_t)c->members * P;
-    hipLaunchKernelGGL(k_adam, dim3((unsigned)((np + 255) / 256)), dim3(256), 0, c->stream, c->params, c->am, c->av,
-                       c->gpart, c->members, nt, lr, b1, b2, eps, c1, c2, update ? 1 : 0, gout);
-    hipLaunchKernelGGL(k_loss, dim3(1), dim3(64), 0, c->stream, c->lpart, c->members, nt, c->loss);
-    if (update) c->w2_fresh = false;
+    if (!c->w2t_fresh) {
+        const int64_t ne = (int64_t)c->members * H * H;
+        hipLaunchKernelGGL(k_w2_transpose, dim3((unsigned)((ne + 255) / 256)), dim3(256), 0, c->stream, c->params,
+                           c->members, c->w2t);
+        c->w2t_fresh = true;
+    }
+    Adam ad{lr, 0.9f, 0.999f, 1e-8f, 1.0f, 1.0f};
+    if (update) {
+        c->adam_t++;
+        ad.c1 = 1.0f - std::pow(ad.b1, (float)c->adam_t);
+        ad.c2 = 1.0f - std::pow(ad.b2, (float)c->adam_t);
+        c->w2_fresh = false;
+    }
+    for (int base = 0; base < n; base += c->act.rows) {
+        const int nr = std::min(c->act.rows, n - base);
+        hipLaunchKernelGGL(k_fwd_bwd, dim3((unsigned)((nr + QT - 1) / QT), (unsigned)c->members), dim3(FT), 0,
+                           c->stream, c->params, c->w2t, X, Y, n, base, c->act);
+        hipLaunchKernelGGL(k_grad, dim3(G_UNITS, (unsigned)c->members), dim3(FT), 0, c->stream, c->params, c->w2t,
+                           c->am, c->av, c->gsum, X, base, nr, c->act, base == 0 ? 1 : 0,
+                           base + nr >= n ? 1 : 0, update ? 1 : 0, ad, gout, c->loss);
+    }
     SHIPCHECK(c, hipGetLastError());
     return LBM_OK;
 }
@@ -444,14 +608,15 @@ lbm_status surr_create(int members, int hidden, int max_n, uint64_t seed, void *
     surr_ctx *c = new surr_ctx();
     c->members = members;
     c->max_n = max_n;
-    c->ntile_max = (max_n + TS - 1) / TS;
     c->ws = (char *)dev_ws;
     c->stream = (hipStream_t)hip_stream;
     c->params = (float *)(c->ws + L.params);
     c->am = (float *)(c->ws + L.am);
     c->av = (float *)(c->ws + L.av);
-    c->gpart = (float *)(c->ws + L.gpart);
-    c->lpart = (float *)(c->ws + L.lpart);
+    c->gsum = (float *)(c->ws + L.gsum);
+    c->w2t = (float *)(c->ws + L.w2t);
+    c->act = {(float *)(c->ws + L.act[0]), (float *)(c->ws + L.act[1]), (float *)(c->ws + L.act[2]),
+              (float *)(c->ws + L.act[3]), (float *)(c->ws + L.out[0]), (float *)(c->ws + L.out[1]), L.rows};
     c->loss = (float *)(c->ws + L.loss);
     c->w2 = (uint16_t *)(c->ws + L.w2);
     const int64_t np = (int64_t)members * P;
@@ -505,8 +670,10 @@ lbm_status surr_predict(surr_ctx *c, const float *X, int n, float *mean, float *
                            c->members, c->w2);
         c->w2_fresh = true;
     }
-    hipLaunchKernelGGL(k_predict, dim3((unsigned)((n + TS - 1) / TS)), dim3(256), 0, c->stream, c->params, c->w2,
-                       c->members, X, n, mean, sd, fallback, thresh, osc, osh);
+    // as few passes over the members as the LDS allows, of equal size
+    const int passes = (c->members + MC_MAX - 1) / MC_MAX, mc = (c->members + passes - 1) / passes;
+    hipLaunchKernelGGL(k_predict, dim3((unsigned)((n + QT - 1) / QT)), dim3(PT), predict_lds(mc), c->stream, c->params,
+                       c->w2, c->members, mc, X, n, mean, sd, fallback, thresh, osc, osh);
     SHIPCHECK(c, hipGetLastError());
     return LBM_OK;
 }
@@ -525,6 +692,7 @@ lbm_status surr_set_params(surr_ctx *c, const float *host, size_t bytes)
     SHIPCHECK(c, hipMemcpyAsync(c->params, host, bytes, hipMemcpyHostToDevice, c->stream));
     SHIPCHECK(c, hipStreamSynchronize(c->stream));
     c->w2_fresh = false;
+    c->w2t_fresh = false;
     return LBM_OK;
 }
 

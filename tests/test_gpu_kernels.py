@@ -135,3 +135,50 @@ def test_label_patterns(pattern, shape, layout):
     sim.step(2)
     other.step(2)
     assert np.array_equal(sim.get_state(), other.get_state())
+
+
+# samples around a tile (16), a gradient group (64), the eight groups that run
+# at once (512) and a chunk (8192)
+@pytest.mark.parametrize("n", [1, 15, 16, 17, 63, 64, 65, 512, 513, 8192, 8193])
+def test_surrogate_gradients(n):
+    """Gradient and loss against the FP64 oracle.  An FP32 sum of n terms of
+    like size is off by at most n/64 + 64 roundings of 6e-8 of the sum of their
+    magnitudes: 1e-4 of the largest gradient covers n = 8193."""
+    from oracle import mlp_oracle as mo
+    from paper_2512_12934_amd.surrogate import Surrogate
+    print(f"[gpu] surrogate gradients n={n}", flush=True)
+    rng = np.random.default_rng(n)
+    X = rng.uniform(-1, 1, (n, 4)).astype(np.float32)
+    Y = np.stack([np.sin(2 * X[:, 0]), np.cos(X[:, 3]) - 0.3 * X[:, 1]], 1).astype(np.float32)
+    s = Surrogate(members=2, max_n=n, seed=n)
+    g, loss = s.forward_backward(X, Y)
+    th = s.get_params().astype(np.float64)
+    for m in range(2):
+        go = mo.grad(th[m], X, Y, 128)
+        assert np.abs(g[m] - go).max() < 1e-4 * np.abs(go).max()
+        assert abs(loss[m] - mo.loss(th[m], X, Y, 128)) < 1e-5 * max(1.0, loss[m])
+    # a parameter set put in from outside is the one that trains
+    s.set_params(s.get_params()[::-1].copy())
+    g2, _ = s.forward_backward(X, Y)
+    assert np.array_equal(g2, g[::-1])
+
+
+# members around one pass over them (5), queries around a block (16)
+@pytest.mark.parametrize("members", [1, 4, 5, 6, 11, 64])
+@pytest.mark.parametrize("n", [1, 16, 17, 250])
+def test_surrogate_predict(members, n):
+    """Ensemble mean and deviation against the FP64 oracle's BF16 inference
+    (2e-3: a layer-1 activation whose FP32 value rounds to the other BF16
+    neighbour moves an output by 2^-9 of one weight product)."""
+    import torch
+    from oracle import mlp_oracle as mo
+    from paper_2512_12934_amd.surrogate import Surrogate
+    print(f"[gpu] surrogate predict members={members} n={n}", flush=True)
+    s = Surrogate(members=members, max_n=16, seed=5)
+    X = np.random.default_rng(n).uniform(-1, 1, (n, 4)).astype(np.float32)
+    mean, sd, fb = (v.cpu().numpy() for v in s.predict(X, threshold=0.05, out_scale=(0.5, 2.0), out_shift=(1.0, 3.0)))
+    mu, so, fo = mo.ensemble(list(s.get_params().astype(np.float64)), X, 128, 0.05, out_scale=(0.5, 2.0),
+                             out_shift=(1.0, 3.0))
+    assert np.abs(mean - mu).max() < 2e-3 and np.abs(sd - so).max() < 2e-3
+    margin = np.abs(so - 0.05 * np.abs(mu)).min(axis=1) > 5e-3
+    assert (fb.astype(bool)[margin] == fo[margin]).all()
