@@ -473,67 +473,95 @@ __device__ __forceinline__ void main_item(const typename Codec<STORE>::T *__rest
         const int x0 = tx * TX, y0 = DIM == 3 ? ty * TY : 0;
         const int s0 = ch * ZC, s1 = min(s0 + ZC, ns);
 
-        // psi of sweep planes [pa, pb) into the ring
-        auto load_planes = [&](int pa, int pb) {
-            const int cnt = (pb - pa) * PLANE;
-            for (int h = threadIdx.x; h < cnt; h += 256) {
-                const int pl = pa + h / PLANE, r = h % PLANE;
-                const int lx = r % HX, ly = r / HX;
-                int gx = x0 - 2 + lx, gy, gz;
-                if (DIM == 3) { gy = y0 - 2 + ly; gz = pl; }
-                else { gy = pl; gz = 0; }
-                const bool need = gx < g.n[0] + 2 && gy < g.n[1] + 2 && (DIM == 2 || gz < g.n[2] + 2);
-                const int slot = ((pl + 4 * R) % R) * PLANE + r;
+        // psi of NP sweep planes from plane pa on into the ring: positions
+        // threadIdx.x, threadIdx.x + 256, ... of them.  The loads of U
+        // positions are in flight at once (of all of them where registers
+        // allow): with one position at a time a block of a small domain spent
+        // most of its life in one memory round trip after another.  between()
+        // runs after the first loads are issued.
+        auto load_planes = [&](auto npc, int pa, auto &&between) {
+            constexpr int NP = decltype(npc)::value, CNT = NP * PLANE, IT = (CNT + 255) / 256;
+            constexpr int UMAX = PSRC == 1 ? 8 : 2;
+            constexpr int U = (IT + (IT + UMAX - 1) / UMAX - 1) / ((IT + UMAX - 1) / UMAX);
+            static_for<(IT + U - 1) / U>([&](auto cc) {
+                constexpr int C = decltype(cc)::value;
+                int slot[U], gx[U], gy[U], gz[U];
+                bool have[U], need[U];
+                static_for<U>([&](auto uc) {
+                    constexpr int u = decltype(uc)::value;
+                    const int h = (int)threadIdx.x + 256 * (C * U + u);
+                    const int pl = pa + h / PLANE, r = h % PLANE;
+                    const int lx = r % HX, ly = r / HX;
+                    have[u] = C * U + u + 1 < IT ? true : h < CNT;
+                    if (C * U + u >= IT) have[u] = false;
+                    int x = x0 - 2 + lx, y = DIM == 3 ? y0 - 2 + ly : pl, z = DIM == 3 ? pl : 0;
+                    need[u] = have[u] && x < g.n[0] + 2 && y < g.n[1] + 2 && (DIM == 2 || z < g.n[2] + 2);
+                    slot[u] = ((pl + 4 * R) % R) * PLANE + r;
+                    // positions that no node needs read the box's first node
+                    gx[u] = need[u] ? map_axis(x, g.n[0], g.periodic[0]) : 0;
+                    gy[u] = need[u] ? map_axis(y, g.n[1], g.periodic[1]) : 0;
+                    gz[u] = DIM == 3 && need[u] ? map_axis(z, g.n[2], g.periodic[2]) : 0;
+                });
+                auto box = [&](int u) {
+                    return (int64_t)gx[u] + (int64_t)g.n[0] * ((int64_t)gy[u] + (int64_t)g.n[1] * gz[u]);
+                };
                 if constexpr (PSRC == 1) {
                     // psi of this step from k_psi; solids carry -0.0 (zero in
                     // every sum, and the sign marks them for the adhesion stencil)
-                    float2 v = make_float2(0.0f, 0.0f);
-                    uint8_t sol = 1;
-                    if (need) {
-                        gx = map_axis(gx, g.n[0], g.periodic[0]);
-                        gy = map_axis(gy, g.n[1], g.periodic[1]);
-                        if (DIM == 3) gz = map_axis(gz, g.n[2], g.periodic[2]);
-                        v = psi[(int64_t)gx + (int64_t)g.n[0] * ((int64_t)gy + (int64_t)g.n[1] * gz)];
-                        sol = signbit(v.x) ? 1 : 0;
-                    }
-                    s_psi[slot] = v;
-                    s_sol[slot] = sol;
-                    continue;
+                    float2 v[U];
+                    static_for<U>([&](auto uc) { v[decltype(uc)::value] = psi[box(decltype(uc)::value)]; });
+                    if constexpr (C == 0) between();
+                    static_for<U>([&](auto uc) {
+                        constexpr int u = decltype(uc)::value;
+                        if (!have[u]) return;
+                        s_psi[slot[u]] = v[u];
+                        s_sol[slot[u]] = !need[u] || signbit(v[u].x) ? 1 : 0;
+                    });
+                } else {
+                    uint32_t tw[U];
+                    float2 rf[U];
+                    typename Buf<STORE>::Raw h1[U][Q], h2[U][Q];
+                    static_for<U>([&](auto uc) {
+                        constexpr int u = decltype(uc)::value;
+                        tw[u] = type[box(u)];
+                        rf[u] = make_float2(0.0f, 0.0f);
+                        if constexpr (Codec<STORE>::REF) rf[u] = ref[box(u)];
+                    });
+                    if constexpr (C == 0) between();
+                    static_for<U>([&](auto uc) {
+                        constexpr int u = decltype(uc)::value;
+                        // lanes off the fluid gather a valid node, unused, so
+                        // that no load waits at the end of a branch
+                        const bool fluid = need[u] && !(tw[u] & T_SOLID);
+                        tw[u] = fluid ? tw[u] : T_SOLID;
+                        const uint32_t t = fluid ? tw[u] : 0u;
+                        const int ax = fluid ? gx[u] : 1, ay = fluid ? gy[u] : 1, az = fluid ? gz[u] : 1;
+                        const uint32_t pp = (uint32_t)pidx(g, ax, ay, DIM == 3 ? az : -1);
+                        const bool wave_fast = __ballot((t & (T_BBMASK | T_EDGE)) != 0) == 0;
+                        bgather2_raw<DIM, STORE>(rs0, rs1, g, pp, t, ax, ay, DIM == 3 ? az : 0, wave_fast, h1[u], h2[u]);
+                    });
+                    static_for<U>([&](auto uc) {
+                        constexpr int u = decltype(uc)::value;
+                        if (!have[u]) return;
+                        const bool fluid = !(tw[u] & T_SOLID);
+                        float f[Q], p1 = 0.0f, p2 = 0.0f;
+                        if constexpr (STAGE) {
+                            if (fluid)
+                                static_for<Q>([&](auto ic) {
+                                    constexpr int i = decltype(ic)::value;
+                                    s_fr[slot[u] * 2 * Q + i] = h1[u][i];
+                                    s_fr[slot[u] * 2 * Q + Q + i] = h2[u][i];
+                                });
+                        }
+                        decode<DIM, STORE>(h1[u], f, rf[u].x);
+                        static_for<Q>([&](auto ic) { p1 += f[decltype(ic)::value]; });
+                        decode<DIM, STORE>(h2[u], f, rf[u].y);
+                        static_for<Q>([&](auto ic) { p2 += f[decltype(ic)::value]; });
+                        s_psi[slot[u]] = fluid ? make_float2(p1, p2) : make_float2(0.0f, 0.0f);
+                        s_sol[slot[u]] = fluid ? 0 : 1;
+                    });
                 }
-                uint32_t tw = T_SOLID;
-                uint32_t pp = 0;
-                if (need) {
-                    gx = map_axis(gx, g.n[0], g.periodic[0]);
-                    gy = map_axis(gy, g.n[1], g.periodic[1]);
-                    if (DIM == 3) gz = map_axis(gz, g.n[2], g.periodic[2]);
-                    const int64_t b = (int64_t)gx + (int64_t)g.n[0] * ((int64_t)gy + (int64_t)g.n[1] * gz);
-                    tw = type[b];
-                    pp = (uint32_t)pidx(g, gx, gy, DIM == 3 ? gz : -1);
-                }
-                const bool fluid = !(tw & T_SOLID);
-                const bool wave_fast = __ballot(fluid && (tw & (T_BBMASK | T_EDGE))) == 0;
-                float p1 = 0.0f, p2 = 0.0f;
-                if (fluid) {
-                    float f[Q];
-                    float2 rf = make_float2(0.0f, 0.0f);
-                    if constexpr (Codec<STORE>::REF) rf = ref[(int64_t)gx + (int64_t)g.n[0] * ((int64_t)gy + (int64_t)g.n[1] * gz)];
-                    typename Buf<STORE>::Raw h1[Q], h2[Q];
-                    bgather2_raw<DIM, STORE>(rs0, rs1, g, pp, tw, gx, gy, gz, wave_fast, h1, h2);
-                    if constexpr (STAGE) {
-                        static_for<Q>([&](auto ic) {
-                            constexpr int i = decltype(ic)::value;
-                            s_fr[slot * 2 * Q + i] = h1[i];
-                            s_fr[slot * 2 * Q + Q + i] = h2[i];
-                        });
-                    }
-                    decode<DIM, STORE>(h1, f, rf.x);
-                    static_for<Q>([&](auto ic) { p1 += f[decltype(ic)::value]; });
-                    decode<DIM, STORE>(h2, f, rf.y);
-                    static_for<Q>([&](auto ic) { p2 += f[decltype(ic)::value]; });
-                }
-                s_psi[slot] = make_float2(p1, p2);
-                s_sol[slot] = fluid ? 0 : 1;
-            }
+            });
         };
 
         // node k of this thread in the sweep window starting at plane w0
@@ -544,16 +572,34 @@ __device__ __forceinline__ void main_item(const typename Codec<STORE>::T *__rest
             const bool valid = x < g.n[0] && sv < s1 && (DIM == 2 || y < g.n[1]);
             return valid ? type[(int64_t)x + (int64_t)g.n[0] * ((int64_t)y + (int64_t)g.n[1] * z)] : T_SOLID;
         };
-        load_planes(s0 - 2, s0 + 2);
+        // the populations of the window's node, where a thread has one node per
+        // window: gathered between the ring's loads and their use
+        constexpr bool AHEAD = NPT == 1 && KEEPB && !STAGE;
+        typename Buf<STORE>::Raw q1[Q], q2[Q];
+        constexpr bool ONE = ZC == W;              // one window: its planes and the halo's at once
+        if constexpr (!ONE) load_planes(std::integral_constant<int, 4>{}, s0 - 2, [] {});
         for (int w0 = s0; w0 < s1; w0 += W) {
-            __syncthreads();                      // ring slots of w0-6..w0-3 are free
+            if constexpr (!ONE) __syncthreads();  // ring slots of w0-6..w0-3 are free
             // the type words of the window's nodes are loaded together with
             // the psi planes, whose wait covers them: loaded node by node they
             // would each wait for the previous node's stores to complete (the
             // memory counter also counts stores)
             uint32_t twq[NPT];
             static_for<NPT>([&](auto jc) { twq[decltype(jc)::value] = type_of(sweep_of(w0, decltype(jc)::value)); });
-            load_planes(w0 + 2, w0 + W + 2);
+            auto ahead = [&] {
+                if constexpr (AHEAD) {
+                    // lanes off the fluid gather a valid node, unused
+                    const int sv = sweep_of(w0, 0);
+                    const bool fluid = !(twq[0] & T_SOLID);
+                    const uint32_t t = fluid ? twq[0] : 0u;
+                    const int x = fluid ? x0 + lx : 1, y = fluid ? (DIM == 3 ? y0 + ly : sv) : 1, z = DIM == 3 ? (fluid ? sv : 1) : 0;
+                    const bool wave_fast = __ballot((t & (T_BBMASK | T_EDGE)) != 0) == 0;
+                    bgather2_raw<DIM, STORE>(rs0, rs1, g, (uint32_t)pidx(g, x, y, DIM == 3 ? z : -1), t, x, y, z,
+                                             wave_fast, q1, q2);
+                }
+            };
+            if constexpr (ONE) load_planes(std::integral_constant<int, W + 4>{}, w0 - 2, ahead);
+            else load_planes(std::integral_constant<int, W>{}, w0 + 2, ahead);
             __syncthreads();
             // settle the type loads here, once per window: an empty statement
             // that reads them, so that the wait is not placed at the head of
@@ -587,7 +633,13 @@ __device__ __forceinline__ void main_item(const typename Codec<STORE>::T *__rest
                 // the populations of the node: loads issued here, before the
                 // force stencil, so the LDS work below hides their latency
                 typename Buf<STORE>::Raw h1[Q], h2[Q];
-                if constexpr (STAGE) {
+                if constexpr (AHEAD) {
+                    static_for<Q>([&](auto ic) {
+                        constexpr int i = decltype(ic)::value;
+                        h1[i] = q1[i];
+                        h2[i] = q2[i];
+                    });
+                } else if constexpr (STAGE) {
                     // staged in the ring when psi of this node's plane was formed
                     const int sl = base[2] + CEN;
                     static_for<Q>([&](auto ic) {
@@ -783,7 +835,7 @@ void k_main(const typename Codec<STORE>::T *__restrict__ src,
     const int k = ((S / MAIN_XCD_GROUP) * 8 + r) * MAIN_XCD_GROUP + S % MAIN_XCD_GROUP;
     if (k < n_items)
         main_item<DIM, STORE, PSRC, TX, TY, W, ZC, KEEPB>(src, dst, type, psi, ref, g, ph, bd, tiles_x, tiles_y,
-                                                          item_list[k], flag, qacc);
+                                                          item_list ? item_list[k] : k, flag, qacc);
 }
 
 // ---------------------------------------------------------------------------

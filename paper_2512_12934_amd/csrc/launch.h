@@ -47,6 +47,7 @@ constexpr TileCfg CFG3[] = {
     {1, 32, 8, 4, 4, 1},
     {1, 64, 4, 4, 4, 1},
     {1, 32, 8, 2, 2, 1},
+    {1, 32, 8, 1, 1, 1},
 };
 constexpr int NCFG2 = sizeof(CFG2) / sizeof(CFG2[0]);
 constexpr int NCFG3 = sizeof(CFG3) / sizeof(CFG3[0]);

@@ -752,7 +752,9 @@ StepArgs step_args(const lbm_ctx *c, double *orho = nullptr, double *ou = nullpt
     a.tiles_x = L.tiles[0];
     a.tiles_y = L.tiles[1];
     a.items = (int)L.nblocks_main;
-    a.item_list = (const int *)(c->ws + L.o_items);
+    // every tile live: the work item is the tile, no list to read
+    a.item_list = L.nblocks_main == (int64_t)L.tiles[0] * L.tiles[1] * L.tiles[2] ? nullptr
+                                                                                 : (const int *)(c->ws + L.o_items);
     a.grid = (unsigned)L.grid_main;
     a.orho = orho;
     a.ou = ou;
