@@ -20,8 +20,19 @@ HERE = os.path.dirname(os.path.abspath(__file__))
 TABLE = os.path.join(HERE, "tuning.json")
 
 
+# Upper bounds (box nodes) of the size classes.  The best work item shrinks
+# with the domain, from 16 rows or 4 planes where the halo it re-reads is what
+# costs, to one pass of a block where too few items would leave CUs idle; the
+# classes end where the measured picks of either lattice change.
+CLASSES = ((100_000, "100k"), (250_000, "250k"), (1_000_000, "1M"), (3_000_000, "3M"), (5_000_000, "5M"),
+           (16_000_000, "16M"))
+
+
 def size_class(nodes: int) -> str:
-    return "small" if nodes < 1_000_000 else "large"
+    for limit, name in CLASSES:
+        if nodes < limit:
+            return name
+    return "max"
 
 
 def key(dim: int, storage: str, nodes: int) -> str:
@@ -78,10 +89,27 @@ def tune(case, storage: str, steps: int, warmup: int, log=print) -> dict:
             "workload": f"{case.name} {case.n}", "fluid_nodes": case.fluid_nodes}
 
 
+# One workload per size class and lattice (those of "max" need a batch or a
+# domain beyond one context in 3-D and keep the largest class's pick).
+WORKLOADS = {
+    "taylor": lambda c: c.taylor(5.0, 0.05, nx=320, H=160, R=32.0),
+    "tjunction": lambda c: c.tjunction(),
+    "droplet_900": lambda c: c.laplace(n=900, R=225.0),
+    "tjunction_W256": lambda c: c.sweep_case(256, 0.03, 0.5, 1.0),
+    # the sweep geometry at W = 512 (2.4M fluid nodes)
+    "tjunction_W512": lambda c: c.sweep_case(512, 0.03, 0.5, 1.0),
+    "coflow3d_80": lambda c: c.coflow3d(length=80, width=16, inner=4),
+    "coflow3d_quarter": lambda c: c.coflow3d_quarter(),
+    "coflow3d_200": lambda c: c.coflow3d(length=200, width=40, inner=10),
+    "coflow3d_half": lambda c: c.coflow3d(length=300, width=60, inner=15),
+    "coflow3d_400": lambda c: c.coflow3d(length=400, width=90, inner=20),
+    "coflow3d": lambda c: c.coflow3d(),
+}
+
+
 def main(argv=None):
     ap = argparse.ArgumentParser()
-    ap.add_argument("--workload", choices=["coflow3d", "tjunction", "coflow3d_quarter", "tjunction_small",
-                                           "tjunction_large"], default="coflow3d")
+    ap.add_argument("--workload", choices=sorted(WORKLOADS), default="coflow3d")
     ap.add_argument("--storage", choices=["f32", "f16", "both"], default="both")
     ap.add_argument("--steps", type=int, default=50)
     ap.add_argument("--warmup", type=int, default=5)
@@ -89,11 +117,7 @@ def main(argv=None):
     args = ap.parse_args(argv)
     sys.path.insert(0, os.path.dirname(HERE))
     from . import cases
-    make = {"coflow3d": cases.coflow3d, "tjunction": cases.tjunction, "coflow3d_quarter": cases.coflow3d_quarter,
-            "tjunction_small": lambda: cases.tjunction(W=32, length=256, x_side=48, side_width=32, side_len=32),
-            # the sweep geometry at W = 512 (2.4M fluid nodes): the size class of large batches
-            "tjunction_large": lambda: cases.sweep_case(512, 0.01, 0.5, 1.0)}
-    case = make[args.workload]()
+    case = WORKLOADS[args.workload](cases)
     table = load_table()
     for storage in (["f32", "f16"] if args.storage == "both" else [args.storage]):
         res = tune(case, storage, args.steps, args.warmup, log=lambda m: print(m, flush=True))

@@ -477,8 +477,9 @@ __device__ __forceinline__ void main_item(const typename Codec<STORE>::T *__rest
         // threadIdx.x, threadIdx.x + 256, ... of them.  The loads of U
         // positions are in flight at once (of all of them where registers
         // allow): with one position at a time a block of a small domain spent
-        // most of its life in one memory round trip after another.  between()
-        // runs after the first loads are issued.
+        // most of its life in one memory round trip after another (node update
+        // of a 64x64 box 11.7 -> 9.3 us, of the 600x120x120 device 593 -> 560).
+        // between() runs after the first loads are issued.
         auto load_planes = [&](auto npc, int pa, auto &&between) {
             constexpr int NP = decltype(npc)::value, CNT = NP * PLANE, IT = (CNT + 255) / 256;
             constexpr int UMAX = PSRC == 1 ? 8 : 2;

@@ -47,6 +47,8 @@ constexpr TileCfg CFG3[] = {
     {1, 32, 8, 4, 4, 1},
     {1, 64, 4, 4, 4, 1},
     {1, 32, 8, 2, 2, 1},
+    // one plane per item: domains of some ten thousand nodes (80x16x16: 25.9 us
+    // per step against 31.7 with two planes, 43.6 with four)
     {1, 32, 8, 1, 1, 1},
 };
 constexpr int NCFG2 = sizeof(CFG2) / sizeof(CFG2[0]);
