@@ -431,13 +431,18 @@ __device__ __forceinline__ double flow_unfix(unsigned long long v) { return (dou
 // KEEPB = 1 holds both components' populations in registers between the
 // velocity and the collision; KEEPB = 0 gathers component 2 again after
 // component 1 is stored (fewer registers, one more pass through the caches).
-template <int DIM, int STORE, int PSRC, int TX, int TY, int W, int ZC, int KEEPB>
+//
+// FIELDS = true stops after the velocity and writes rho_k and u of every node
+// of the item, solids included, in FP64 in the caller's frame (orho [2][N],
+// ou [3][N]) instead of a step.
+template <int DIM, int STORE, int PSRC, int TX, int TY, int W, int ZC, int KEEPB, bool FIELDS = false>
 __device__ __forceinline__ void main_item(const typename Codec<STORE>::T *__restrict__ src,
                                           typename Codec<STORE>::T *__restrict__ dst,
                                           const uint32_t *__restrict__ type, const float2 *__restrict__ psi,
                                           const float2 *__restrict__ ref, const Geometry &g, const Physics &ph,
                                           const Boundary &bd, int tiles_x, int tiles_y, int item,
-                                          int *__restrict__ flag, unsigned long long *__restrict__ qacc)
+                                          int *__restrict__ flag, unsigned long long *__restrict__ qacc,
+                                          double *__restrict__ orho = nullptr, double *__restrict__ ou = nullptr)
 {
     constexpr int Q = Lat<DIM>::Q;
     constexpr int LY = DIM == 3 ? TY : 1;          // lateral y extent of the tile
@@ -619,6 +624,13 @@ __device__ __forceinline__ void main_item(const typename Codec<STORE>::T *__rest
                 static_for<NPT - 1>([&](auto jc) { twq[decltype(jc)::value] = twq[decltype(jc)::value + 1]; });
                 const bool fluid = !(tw & T_SOLID);
                 const bool wave_fast = __ballot(fluid && (tw & (T_BBMASK | T_EDGE))) == 0;
+                if constexpr (FIELDS) {
+                    if (valid && !fluid) {
+                        const int64_t bo = caller_index(g, x, y, z);
+                        orho[bo] = orho[g.N + bo] = 0.0;
+                        ou[bo] = ou[g.N + bo] = ou[2 * g.N + bo] = 0.0;
+                    }
+                }
                 if (!fluid) continue;
                 const uint32_t p = (uint32_t)pidx(g, x, y, DIM == 3 ? z : -1);
                 // base[d]: ring index of the lateral corner (-2, -2) of the
@@ -735,6 +747,16 @@ __device__ __forceinline__ void main_item(const typename Codec<STORE>::T *__rest
                     to_pairs<DIM>(f, qb);
                     pair_momentum<DIM>(qb, J2);
                 }
+                if constexpr (FIELDS) {
+                    const int64_t bo = caller_index(g, x, y, z);
+                    orho[bo] = r1;
+                    orho[g.N + bo] = r2;
+                    static_for<3>([&](auto dc) {
+                        constexpr int d = decltype(dc)::value;
+                        ou[g.ax[d] * g.N + bo] = d < DIM ? (J1[d] + J2[d] + 0.5f * (F1[d] + F2[d])) / rt : 0.0f;
+                    });
+                    continue;
+                }
                 float u[3];
                 const float irt = 1.0f / rt;
                 static_for<3>([&](auto dc) {
@@ -805,6 +827,7 @@ __device__ __forceinline__ void main_item(const typename Codec<STORE>::T *__rest
             }
         }
     }
+    if constexpr (FIELDS) return;
     __syncthreads();
     if (threadIdx.x == 0) {
         if (s_q[0]) atomicAdd(qacc, s_q[0]);
@@ -908,83 +931,25 @@ __device__ __forceinline__ void moments_of(const float (&f)[Lat<DIM>::Q], float 
 
 // ---------------------------------------------------------------------------
 // k_moments: rho_k and the common velocity of eqs. (7)-(8) (with this
-// state's force, before any outlet override) of every node, one thread per
-// node, with psi of the neighbours read from the array k_psi wrote.
+// state's force, before any outlet override) of every node: the node update's
+// sweep up to the velocity (one thread per node with 92 mapped psi reads of
+// its own took 1.20 ms on the 600x120x120 device, longer than a step).  The
+// instability flag goes to pinned host memory with it.
 // ---------------------------------------------------------------------------
-template <int DIM, int STORE>
+template <int DIM, int STORE, int PSRC, int TX, int TY, int W, int ZC>
 __global__ __launch_bounds__(256) void k_moments(const typename Codec<STORE>::T *__restrict__ src,
                                                  const uint32_t *__restrict__ type,
                                                  const float2 *__restrict__ psi, const float2 *__restrict__ ref,
-                                                 Geometry g, Physics ph, double *__restrict__ out_rho,
-                                                 double *__restrict__ out_u)
+                                                 Geometry g, Physics ph, Boundary bd, int tiles_x, int tiles_y,
+                                                 int n_items, double *__restrict__ orho, double *__restrict__ ou,
+                                                 int *__restrict__ flag, int *__restrict__ host_flag)
 {
-    constexpr int Q = Lat<DIM>::Q;
-    const int64_t b = (int64_t)blockIdx.x * 256 + threadIdx.x;
-    if (b >= g.N) return;
-    const uint32_t tw = type[b];
-    int x, y, z;
-    coords_of(g, b, x, y, z);
-    const int64_t bo = caller_index(g, x, y, z);
-    if (tw & T_SOLID) {
-        out_rho[bo] = 0.0;
-        out_rho[g.N + bo] = 0.0;
-        out_u[bo] = out_u[g.N + bo] = out_u[2 * g.N + bo] = 0.0;
-        return;
-    }
-    auto psi_at = [&](int dx, int dy, int dz) {
-        const int qx = map_axis(x + dx, g.n[0], g.periodic[0]);
-        const int qy = map_axis(y + dy, g.n[1], g.periodic[1]);
-        const int qz = DIM == 3 ? map_axis(z + dz, g.n[2], g.periodic[2]) : 0;
-        return psi[(int64_t)qx + (int64_t)g.n[0] * ((int64_t)qy + (int64_t)g.n[1] * qz)];
-    };
-    // the stencil in pairs of opposite offsets, in the node update's order
-    // (sweep distance, then lateral offsets), so u matches the step's
-    float g1[3] = {0.f, 0.f, 0.f}, g2[3] = {0.f, 0.f, 0.f}, A[3] = {0.f, 0.f, 0.f};
-    static_for<3>([&](auto sdc) {
-        constexpr int SD = decltype(sdc)::value;
-        static_for<25>([&](auto oc) {
-            constexpr int o = decltype(oc)::value;
-            constexpr int a = o % 5 - 2, bq = o / 5 - 2;
-            constexpr int dx = a, dy = DIM == 3 ? bq : SD, dz = DIM == 3 ? SD : 0;
-            constexpr int lat_y = DIM == 3 ? bq : 0;
-            constexpr int r2 = dx * dx + dy * dy + dz * dz;
-            constexpr float w = stencil_w<DIM>(r2);
-            constexpr bool half = SD > 0 || (lat_y > 0 || (lat_y == 0 && dx > 0));
-            constexpr bool in2d = DIM == 3 || bq == 0;
-            if constexpr (half && in2d && w != 0.0f) {
-                const float2 vp = psi_at(dx, dy, dz), vm = psi_at(-dx, -dy, -dz);
-                const float d1 = vp.x - vm.x, d2 = vp.y - vm.y;
-                const float ds = (signbit(vp.x) ? 1.0f : 0.0f) - (signbit(vm.x) ? 1.0f : 0.0f);
-                const int e3[3] = {dx, dy, dz};
-                static_for<3>([&](auto dc) {
-                    constexpr int d = decltype(dc)::value;
-                    if (e3[d] != 0) {
-                        g1[d] = fmaf(w * e3[d], d1, g1[d]);
-                        g2[d] = fmaf(w * e3[d], d2, g2[d]);
-                        A[d] = fmaf(w * e3[d], ds, A[d]);
-                    }
-                });
-            }
-        });
-    });
-    if (!ph.adhesion) A[0] = A[1] = A[2] = 0.0f;
-    const float2 ps = psi[b];
-    const float r1 = ps.x, r2 = ps.y, rt = r1 + r2;
-    const int64_t p = pidx(g, x, y, DIM == 3 ? z : -1);
-    float f[Q], ra, rb, Ja[3], Jb[3];
-    const float2 rf = ref[b];
-    gather<DIM, STORE>(src, g, p, tw | T_EDGE, x, y, z, f, rf.x);
-    moments_of<DIM>(f, ra, Ja);
-    gather<DIM, STORE>(src + (int64_t)Q * g.Ppad, g, p, tw | T_EDGE, x, y, z, f, rf.y);
-    moments_of<DIM>(f, rb, Jb);
-    out_rho[bo] = r1;
-    out_rho[g.N + bo] = r2;
-    static_for<3>([&](auto dc) {
-        constexpr int d = decltype(dc)::value;
-        const float F1 = -ph.G12 * r1 * g2[d] - ph.Gw[0] * r1 * A[d] + (r1 / rt) * ph.Fb[d];
-        const float F2 = -ph.G12 * r2 * g1[d] - ph.Gw[1] * r2 * A[d] + (r2 / rt) * ph.Fb[d];
-        if (d < DIM) out_u[g.ax[d] * g.N + bo] = (Ja[d] + Jb[d] + 0.5f * (F1 + F2)) / rt;
-    });
+    if (blockIdx.x == 0 && threadIdx.x == 0) *host_flag = *flag;
+    const int S = (int)blockIdx.x / 8, r = (int)blockIdx.x % 8;
+    const int k = ((S / MAIN_XCD_GROUP) * 8 + r) * MAIN_XCD_GROUP + S % MAIN_XCD_GROUP;
+    if (k < n_items)
+        main_item<DIM, STORE, PSRC, TX, TY, W, ZC, 1, true>(src, nullptr, type, psi, ref, g, ph, bd, tiles_x, tiles_y,
+                                                            k, flag, nullptr, orho, ou);
 }
 
 }  // namespace lbm

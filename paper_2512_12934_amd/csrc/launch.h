@@ -86,7 +86,8 @@ struct BatchArgs {
 
 template <int DIM> struct Launcher {
     static void psi(int storage, const StepArgs &a);
-    static void moments(int storage, const StepArgs &a);
+    // rho and u of the state; the instability flag to host_flag (pinned)
+    static void moments(int storage, const StepArgs &a, int *host_flag);
     static void main(int storage, int cfg, const StepArgs &a);
     // chi; nb_out blocks of outlet collision and nb_in blocks of inlet nodes
     static void faces(int storage, const StepArgs &a, int nb_out, int nb_in);

@@ -80,13 +80,20 @@ void Launcher<DIM>::psi(int storage, const StepArgs &a)
 }
 
 template <int DIM>
-void Launcher<DIM>::moments(int storage, const StepArgs &a)
+void Launcher<DIM>::moments(int storage, const StepArgs &a, int *host_flag)
 {
-    const unsigned nb = (unsigned)((a.g.N + 255) / 256);
+    // 2-D in one launch with the densities recomputed in the sweep, 3-D after
+    // the density pass (as the node update's own picks)
+    constexpr TileCfg c = DIM == 2 ? TileCfg{0, 32, 1, 8, 8, 1} : TileCfg{1, 32, 8, 2, 2, 1};
+    if (c.psrc) psi(storage, a);
+    const int tx = (a.g.n[0] + c.tx - 1) / c.tx, ty = DIM == 3 ? (a.g.n[1] + c.ty - 1) / c.ty : 1;
+    const int64_t items = (int64_t)tx * ty * ((a.g.n[DIM - 1] + c.zc - 1) / c.zc);
+    const unsigned nb = (unsigned)((items + 8 * MAIN_XCD_GROUP - 1) / (8 * MAIN_XCD_GROUP) * (8 * MAIN_XCD_GROUP));
     with_store(storage, [&](auto sc) {
         using T = LBM_STORE_T(sc);
-        hipLaunchKernelGGL((k_moments<DIM, decltype(sc)::value>), dim3(nb), dim3(256), 0, a.stream,
-                           (const T *)a.src, a.type, (const float2 *)a.psi, a.ref, a.g, a.ph, a.orho, a.ou);
+        hipLaunchKernelGGL((k_moments<DIM, decltype(sc)::value, c.psrc, c.tx, c.ty, c.w, c.zc>), dim3(nb), dim3(256),
+                           0, a.stream, (const T *)a.src, a.type, (const float2 *)a.psi, a.ref, a.g, a.ph, a.bd, tx, ty,
+                           (int)items, a.orho, a.ou, a.flag, host_flag);
     });
 }
 

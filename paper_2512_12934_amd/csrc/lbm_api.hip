@@ -768,12 +768,10 @@ StepArgs step_args(const lbm_ctx *c, double *orho = nullptr, double *ou = nullpt
 template <int DIM> struct Ops {
     using Lx = Launcher<DIM>;
 
-    // rho and u of the current state: psi of every node, then one thread per node
+    // rho and u of the current state; the instability flag into c->pin
     static void moments(lbm_ctx *c, double *orho, double *ou)
     {
-        StepArgs a = step_args(c, orho, ou);
-        Lx::psi(c->L.storage, a);
-        Lx::moments(c->L.storage, a);
+        Lx::moments(c->L.storage, step_args(c, orho, ou), (int *)c->pin);
     }
 
     // ev (optional): events bracketing k_psi (ev[8], ev[9]) and k_main (ev[0], ev[1])
@@ -1141,7 +1139,6 @@ lbm_status lbm_moments(lbm_ctx *c, double *rho, double *u, int dst_on_device)
         HIPCHECK(c, hipMalloc(&drho, (size_t)2 * N * 8));
         HIPCHECK(c, hipMalloc(&du, (size_t)3 * N * 8));
     }
-    HIPCHECK(c, hipMemsetAsync(du, 0, (size_t)3 * N * 8, c->stream));
     dispatch(c, [&](auto l) { decltype(l)::moments(c, drho, du); });
     HIPCHECK(c, hipGetLastError());
     if (!dst_on_device) {
@@ -1153,7 +1150,10 @@ lbm_status lbm_moments(lbm_ctx *c, double *rho, double *u, int dst_on_device)
         HIPCHECK(c, hipFree(drho));
         HIPCHECK(c, hipFree(du));
     }
-    return check_flag(c);
+    int flag = 0;
+    memcpy(&flag, c->pin, sizeof flag);
+    if (flag) c->unstable = true;
+    return c->unstable ? LBM_EUNSTABLE : LBM_OK;
 }
 
 lbm_status lbm_mass_flux(lbm_ctx *c, lbm_flux *out)

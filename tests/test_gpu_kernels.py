@@ -199,3 +199,33 @@ def test_ring_edges(shape, walls, storage):
                          Gw=(0.05, -0.05) if walls else (0.0, 0.0))
     for cfg in ((0, 4, 8, 10) if dim == 2 else (6, 7, 8, 9, 10)):
         assert _step_error(c, storage, tile_config=cfg) < TOL[storage]
+
+
+@pytest.mark.parametrize("storage", ["f32", "f16"])
+@pytest.mark.parametrize("shape,walls", RINGS)
+def test_moments_edges(shape, walls, storage):
+    """Every value of the caller's buffers is written (zeros on solids and for
+    the missing axis of 2-D), rho and u agree with the oracle: the velocity is
+    a sum of some 40 populations of at most the density, each off by TOL."""
+    import torch
+    from paper_2512_12934_amd.lbm import LBM, LBM_OK
+    dim = 2 if shape[2] == 1 else 3
+    c = cases.random_box(shape, seed=sum(shape), dim=dim, periodic=(not walls,) * 3, walls=walls, u_amp=0.01,
+                         Gw=(0.05, -0.05) if walls else (0.0, 0.0))
+    s = oracle.Sim(c)
+    s.step(2)
+    ro, uo, _ = s.moments()
+    fluid = c.solid == 0
+    for layout in (["caller"] if dim == 2 else ["caller", "face_last"]):
+        print(f"[gpu] moments {shape} walls={walls} {storage} {layout}", flush=True)
+        g = LBM(c, storage=storage, layout=layout)
+        g.step(2)
+        rho = torch.full((2, c.N), float("nan"), dtype=torch.float64, device="cuda:0")
+        u = torch.full((3, c.N), float("nan"), dtype=torch.float64, device="cuda:0")
+        assert g.moments_device(rho, u) == LBM_OK
+        rho, u = rho.cpu().numpy(), u.cpu().numpy()
+        assert (rho[:, ~fluid] == 0).all() and (u[:, ~fluid] == 0).all() and (u[dim:] == 0).all()
+        scale = ro[:, fluid].sum(axis=0)
+        assert (np.abs(rho - ro)[:, fluid] / scale).max() < 2 * TOL[storage]
+        assert np.abs(u - uo)[:, fluid].max() < 4 * TOL[storage]
+        assert np.array_equal(g.moments()[0], rho) and np.array_equal(g.moments()[1], u)
