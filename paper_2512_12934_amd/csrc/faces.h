@@ -193,12 +193,12 @@ __device__ __forceinline__ double chi_from(const Boundary &bd, const unsigned lo
     return chi;
 }
 
-// First record of pass l of this wave in block blk (see FACE_NT).
+// First record of this wave in block blk.
 template <int DIM>
-__device__ __forceinline__ int face_first(int blk, int passes, int l)
+__device__ __forceinline__ int face_first(int blk)
 {
     constexpr int WPB = FACE_NT / 64, NPW = FaceMap<DIM>::NPW;
-    return ((blk * passes + l) * WPB + ((int)threadIdx.x >> 6)) * NPW;
+    return (blk * WPB + ((int)threadIdx.x >> 6)) * NPW;
 }
 
 // ---------------------------------------------------------------------------
@@ -215,50 +215,48 @@ __device__ __forceinline__ void outlet_body(int blk, const typename Codec<STORE>
     const FaceLane<DIM> L;
     const Rates rates = {L.k == 0 ? ph.se[0] : ph.se[1], L.k == 0 ? ph.seps[0] : ph.seps[1], ph.sq,
                          L.k == 0 ? ph.snu[0] : ph.snu[1]};
-    for (int l = 0; l < bd.face_pass; l++) {
-        const int r0 = face_first<DIM>(blk, bd.face_pass, l);
-        if (r0 >= bd.n_out) return;                     // uniform over the wave
-        const bool live = r0 + L.sub < bd.n_out;
-        const int r = live ? r0 + L.sub : r0;
-        const OutletRec rec = bd.out[r];
-        const int *tab = bd.out_tab + (int64_t)r * (3 * Q);
-        float rr = 0.0f, rd = 0.0f;
-        const int slot = tab[L.j];
-        if constexpr (Codec<STORE>::REF) {
-            const float2 a = ref[rec.bN], b = psi[tab[2 * Q + L.j]];
-            rr = L.k == 0 ? a.x : a.y;
-            rd = L.k == 0 ? b.x : b.y;
-        }
-        const float raw = Codec<STORE>::ld(src + (int64_t)L.k * Q * g.Ppad + slot, L.w, rr);
-        const float *fF = bd.faceF + (int64_t)rec.slotN * 6 + 3 * L.k;
-        const float F[3] = {fF[0], fF[1], fF[2]};
-        const float up = rec.slotP >= 0 ? bd.faceU[rec.slotP] : 0.0f;
-        const float f = L.on ? raw : 0.0f;
-        float rho, J[3], u[3];
-        lane_moments<DIM>(L, f, rho, J);
-        const float sa = lane_sum<DIM>(L.axial ? f : 0.0f), f0 = lane_sum<DIM>(L.rest ? f : 0.0f);
-        const float rt = rho + lane_other<DIM>(rho);
+    const int r0 = face_first<DIM>(blk);
+    if (r0 >= bd.n_out) return;                     // uniform over the wave
+    const bool live = r0 + L.sub < bd.n_out;
+    const int r = live ? r0 + L.sub : r0;
+    const OutletRec rec = bd.out[r];
+    const int *tab = bd.out_tab + (int64_t)r * (3 * Q);
+    float rr = 0.0f, rd = 0.0f;
+    const int slot = tab[L.j];
+    if constexpr (Codec<STORE>::REF) {
+        const float2 a = ref[rec.bN], b = psi[tab[2 * Q + L.j]];
+        rr = L.k == 0 ? a.x : a.y;
+        rd = L.k == 0 ? b.x : b.y;
+    }
+    const float raw = Codec<STORE>::ld(src + (int64_t)L.k * Q * g.Ppad + slot, L.w, rr);
+    const float *fF = bd.faceF + (int64_t)rec.slotN * 6 + 3 * L.k;
+    const float F[3] = {fF[0], fF[1], fF[2]};
+    const float up = rec.slotP >= 0 ? bd.faceU[rec.slotP] : 0.0f;
+    const float f = L.on ? raw : 0.0f;
+    float rho, J[3], u[3];
+    lane_moments<DIM>(L, f, rho, J);
+    const float sa = lane_sum<DIM>(L.axial ? f : 0.0f), f0 = lane_sum<DIM>(L.rest ? f : 0.0f);
+    const float rt = rho + lane_other<DIM>(rho);
+    static_for<3>([&](auto dc) {
+        constexpr int d = decltype(dc)::value;
+        const float m = J[d] + 0.5f * F[d];
+        u[d] = (m + lane_other<DIM>(m)) / rt;
+    });
+    if (rec.slotP >= 0) {
+        // eq. (22): the outward velocity is chi times that of x_{N-1}
+        const float un = (float)(chi * (double)up) * bd.out_sign;
         static_for<3>([&](auto dc) {
             constexpr int d = decltype(dc)::value;
-            const float m = J[d] + 0.5f * F[d];
-            u[d] = (m + lane_other<DIM>(m)) / rt;
+            u[d] = bd.out_axis == d ? un : u[d];
         });
-        if (rec.slotP >= 0) {
-            // eq. (22): the outward velocity is chi times that of x_{N-1}
-            const float un = (float)(chi * (double)up) * bd.out_sign;
-            static_for<3>([&](auto dc) {
-                constexpr int d = decltype(dc)::value;
-                u[d] = bd.out_axis == d ? un : u[d];
-            });
-        }
-        if (live && (!(rt > 0.0f) || !isfinite(rt) || !isfinite(u[0] + u[1] + u[2]))) *flag = 1;
-        float fs = lane_collide<DIM>(L, f, rho, sa, f0, J, u, F, rates);
-        // the rest population is the residual of the density (see collide_pairs)
-        const float moving = lane_sum<DIM>(L.on && !L.rest ? fs : 0.0f);
-        if (L.rest) fs = rho - moving;
-        if (live && L.on)
-            Codec<STORE>::st(dst + ((int64_t)L.k * Q + L.dir) * g.Ppad + rec.pN, fs, L.w, rd);
     }
+    if (live && (!(rt > 0.0f) || !isfinite(rt) || !isfinite(u[0] + u[1] + u[2]))) *flag = 1;
+    float fs = lane_collide<DIM>(L, f, rho, sa, f0, J, u, F, rates);
+    // the rest population is the residual of the density (see collide_pairs)
+    const float moving = lane_sum<DIM>(L.on && !L.rest ? fs : 0.0f);
+    if (L.rest) fs = rho - moving;
+    if (live && L.on)
+        Codec<STORE>::st(dst + ((int64_t)L.k * Q + L.dir) * g.Ppad + rec.pN, fs, L.w, rd);
 }
 
 // ---------------------------------------------------------------------------
@@ -271,60 +269,58 @@ __device__ __forceinline__ void inlet_body(int blk, typename Codec<STORE>::T *__
     constexpr int Q = Lat<DIM>::Q;
     const FaceLane<DIM> L;
     typename Codec<STORE>::T *dk = dst + (int64_t)L.k * Q * g.Ppad;
-    for (int l = 0; l < bd.face_pass; l++) {
-        const int r0 = face_first<DIM>(blk, bd.face_pass, l);
-        if (r0 >= bd.n_in) return;                      // uniform over the wave
-        const bool live = r0 + L.sub < bd.n_in;
-        const int r = live ? r0 + L.sub : r0;
-        const InletRec rec = bd.in[r];
-        const int *tab = bd.in_tab + (int64_t)r * (2 * Q);
-        const int slot1 = tab[L.j], slot2 = tab[Q + L.j];
-        const Patch pt = bd.patch[rec.patch];
-        // f(t+1) is read with psi(t) as the reference density
-        float rr1 = 0.0f, rr2 = 0.0f;
-        if constexpr (Codec<STORE>::REF) {
-            const float2 a = psi[rec.b1], b = psi[rec.b2];
-            rr1 = L.k == 0 ? a.x : a.y;
-            rr2 = L.k == 0 ? b.x : b.y;
-        }
-        const float *fF1 = bd.faceF + (int64_t)rec.slot1 * 6 + 3 * L.k;
-        const float F1[3] = {fF1[0], fF1[1], fF1[2]};
-        const float ea = lane_pick(L.e, pt.axis);
-        const bool enter = ea * (float)pt.sign > 0.0f;
-        // the populations that leave x1 (the entering ones are replaced, and
-        // their slots are not read) and all those of x2
-        const float raw1 = L.on && !enter ? Codec<STORE>::ld(dk + slot1, L.w, rr1) : 0.0f;
-        const bool x2 = rec.x2_fluid != 0;
-        const float f2 = L.on && x2 ? Codec<STORE>::ld(dk + slot2, L.w, rr2) : 0.0f;
-        const float *fF2 = bd.faceF + (int64_t)rec.slot2 * 6 + 3 * L.k;
-        const float F2[3] = {fF2[0], fF2[1], fF2[2]};
-        float rho2, J2[3], u2[3];
-        lane_moments<DIM>(L, f2, rho2, J2);
-        const float rt = rho2 + lane_other<DIM>(rho2);
-        static_for<3>([&](auto dc) {
-            constexpr int d = decltype(dc)::value;
-            const float m = J2[d] + 0.5f * F2[d];
-            u2[d] = (m + lane_other<DIM>(m)) / rt;
-        });
-        // eq. (13)/(14) on the populations entering the domain
-        const float un = (float)pt.sign * pt.u_n;
-        const float up[3] = {pt.axis == 0 ? un : 0.0f, pt.axis == 1 ? un : 0.0f, pt.axis == 2 ? un : 0.0f};
-        const float rho_p = L.k == 0 ? pt.rho[0] : pt.rho[1];
-        const float neq = x2 ? f2 - lane_feq<DIM>(L, rho2, u2) : 0.0f;
-        float f1 = enter ? lane_feq<DIM>(L, rho_p, up) + neq : raw1;
-        // eqs. (15)-(19): alpha_i = w_i sum_d e_id dJ_d / D_d over the entering
-        // set, dJ = rho_k^p u^p - (sum_i e_i f_i + F^k/2); D is the sum of the
-        // entering weights with e_id != 0: 1/6 along the normal, 1/18 across
-        float rr, J[3], a = 0.0f;
-        lane_moments<DIM>(L, f1, rr, J);
-        static_for<DIM>([&](auto dc) {
-            constexpr int d = decltype(dc)::value;
-            const float dJ = rho_p * up[d] - (J[d] + 0.5f * F1[d]);
-            a += L.e[d] * dJ * (pt.axis == d ? 6.0f : 18.0f);
-        });
-        if (pt.alpha_on) f1 += L.w * a;
-        if (live && enter) Codec<STORE>::st(dk + slot1, f1, L.w, rr1);
+    const int r0 = face_first<DIM>(blk);
+    if (r0 >= bd.n_in) return;                      // uniform over the wave
+    const bool live = r0 + L.sub < bd.n_in;
+    const int r = live ? r0 + L.sub : r0;
+    const InletRec rec = bd.in[r];
+    const int *tab = bd.in_tab + (int64_t)r * (2 * Q);
+    const int slot1 = tab[L.j], slot2 = tab[Q + L.j];
+    const Patch pt = bd.patch[rec.patch];
+    // f(t+1) is read with psi(t) as the reference density
+    float rr1 = 0.0f, rr2 = 0.0f;
+    if constexpr (Codec<STORE>::REF) {
+        const float2 a = psi[rec.b1], b = psi[rec.b2];
+        rr1 = L.k == 0 ? a.x : a.y;
+        rr2 = L.k == 0 ? b.x : b.y;
     }
+    const float *fF1 = bd.faceF + (int64_t)rec.slot1 * 6 + 3 * L.k;
+    const float F1[3] = {fF1[0], fF1[1], fF1[2]};
+    const float ea = lane_pick(L.e, pt.axis);
+    const bool enter = ea * (float)pt.sign > 0.0f;
+    // the populations that leave x1 (the entering ones are replaced, and
+    // their slots are not read) and all those of x2
+    const float raw1 = L.on && !enter ? Codec<STORE>::ld(dk + slot1, L.w, rr1) : 0.0f;
+    const bool x2 = rec.x2_fluid != 0;
+    const float f2 = L.on && x2 ? Codec<STORE>::ld(dk + slot2, L.w, rr2) : 0.0f;
+    const float *fF2 = bd.faceF + (int64_t)rec.slot2 * 6 + 3 * L.k;
+    const float F2[3] = {fF2[0], fF2[1], fF2[2]};
+    float rho2, J2[3], u2[3];
+    lane_moments<DIM>(L, f2, rho2, J2);
+    const float rt = rho2 + lane_other<DIM>(rho2);
+    static_for<3>([&](auto dc) {
+        constexpr int d = decltype(dc)::value;
+        const float m = J2[d] + 0.5f * F2[d];
+        u2[d] = (m + lane_other<DIM>(m)) / rt;
+    });
+    // eq. (13)/(14) on the populations entering the domain
+    const float un = (float)pt.sign * pt.u_n;
+    const float up[3] = {pt.axis == 0 ? un : 0.0f, pt.axis == 1 ? un : 0.0f, pt.axis == 2 ? un : 0.0f};
+    const float rho_p = L.k == 0 ? pt.rho[0] : pt.rho[1];
+    const float neq = x2 ? f2 - lane_feq<DIM>(L, rho2, u2) : 0.0f;
+    float f1 = enter ? lane_feq<DIM>(L, rho_p, up) + neq : raw1;
+    // eqs. (15)-(19): alpha_i = w_i sum_d e_id dJ_d / D_d over the entering
+    // set, dJ = rho_k^p u^p - (sum_i e_i f_i + F^k/2); D is the sum of the
+    // entering weights with e_id != 0: 1/6 along the normal, 1/18 across
+    float rr, J[3], a = 0.0f;
+    lane_moments<DIM>(L, f1, rr, J);
+    static_for<DIM>([&](auto dc) {
+        constexpr int d = decltype(dc)::value;
+        const float dJ = rho_p * up[d] - (J[d] + 0.5f * F1[d]);
+        a += L.e[d] * dJ * (pt.axis == d ? 6.0f : 18.0f);
+    });
+    if (pt.alpha_on) f1 += L.w * a;
+    if (live && enter) Codec<STORE>::st(dk + slot1, f1, L.w, rr1);
 }
 
 // ---------------------------------------------------------------------------
@@ -339,9 +335,8 @@ __device__ __forceinline__ void uc_body(int blk, const typename Codec<STORE>::T 
     __shared__ double s_red[2 * FACE_NT / 64];
     const FaceLane<DIM> L;
     double su = 0.0, cnt = 0.0;
-    for (int l = 0; l < bd.face_pass; l++) {
-        const int r0 = face_first<DIM>(blk, bd.face_pass, l);
-        if (r0 >= bd.n_out) break;                      // uniform over the wave
+    const int r0 = face_first<DIM>(blk);
+    if (r0 < bd.n_out) {                                // uniform over the wave
         const bool live = r0 + L.sub < bd.n_out;
         const int r = live ? r0 + L.sub : r0;
         const OutletRec rec = bd.out[r];
@@ -362,8 +357,8 @@ __device__ __forceinline__ void uc_body(int blk, const typename Codec<STORE>::T 
         const float un = bd.out_sign * (m + lane_other<DIM>(m)) / rt;
         // one lane per node carries its term
         if (live && x1 && L.k == 0 && L.on && L.j == 0) {
-            su += (double)un;
-            cnt += 1.0;
+            su = (double)un;
+            cnt = 1.0;
         }
     }
     block_sum2<FACE_NT>(su, cnt, s_red);

@@ -215,58 +215,71 @@ __device__ __forceinline__ void gather(const typename Codec<STORE>::T *__restric
 // products out of the node loop: held there, they took 19 scalar registers,
 // the kernel ran out of them, and every access then read its offset back
 // from a vector-register lane (v_readlane) and waited five cycles before
-// the memory instruction could use it.
+// the memory instruction could use it.  (The readfirstlane states that the
+// stride is uniform, which the compiler does not see in every place; it
+// leaves no instruction.)
 template <int STORE>
 __device__ __forceinline__ int plane_bytes(const Geometry &g, int i)
 {
-    int s = (int)((uint32_t)g.Ppad * Buf<STORE>::SZ);
+    int s = __builtin_amdgcn_readfirstlane((int)((uint32_t)g.Ppad * Buf<STORE>::SZ));
     asm volatile("" : "+s"(s));
     return s * i;
 }
 
 // Where the populations that stream into node p (pull) are stored, as byte
 // offsets within one component: a[i] per lane, plus the wave-uniform offset
-// so_i that uniform_plane() gives.  The wave takes the cheapest of three
-// address forms that is valid for all its nodes:
+// so_i that uniform_plane() gives.  The wave takes the cheaper of two address
+// forms that is valid for all its nodes:
 // * no bounce-back and no periodic wrap (wave_fast): population i sits at
 //   plane_i + p - off_i, so a[i] is the shifted lane offset and the plane is
 //   the wave-uniform offset;
-// * walls but no wrap: per lane the streamed slot or the node's own slot of
-//   the opposite direction (bounce-back), selected without branches, with
-//   the plane in a[i];
-// * otherwise the slot of every direction from its own rule.
+// * otherwise, per lane, the streamed slot (one step back along each axis,
+//   around a periodic axis' end) or the node's own slot of the opposite
+//   direction (bounce-back), selected without branches, with the plane in
+//   a[i].  Slots formed one direction at a time from wrapped coordinates
+//   cost a wave of a periodic 64x64 box 11,000 cycles, more than the rest of
+//   its step.
 // Only the addresses depend on the form; the loads are then issued in one
 // straight run for both components, so no load is pending across a join of
-// the three forms (such a join would make the loads wait for earlier ones).
+// the forms (such a join would make the loads wait for earlier ones).
 template <int DIM, int STORE>
 __device__ __forceinline__ void gather_addr(const Geometry &g, uint32_t p, uint32_t tw, int x, int y, int z,
                                             bool wave_fast, uint32_t (&a)[Lat<DIM>::Q])
 {
     constexpr uint32_t SZ = Buf<STORE>::SZ;
-    const uint32_t vb = (p - 1u) * SZ;
     const uint32_t sy = (uint32_t)g.P[0] * SZ, sz = (uint32_t)g.P[0] * (uint32_t)g.P[1] * SZ;
-    auto shifted = [&](auto ic) -> uint32_t {
-        constexpr int i = decltype(ic)::value;
-        constexpr int ex = Lat<DIM>::E[i][0], ey = Lat<DIM>::E[i][1], ez = Lat<DIM>::E[i][2];
-        uint32_t vo = vb + (uint32_t)(1 - ex) * SZ;
-        if constexpr (ey == 1) vo -= sy;
-        if constexpr (ey == -1) vo += sy;
-        if constexpr (ez == 1) vo -= sz;
-        if constexpr (ez == -1) vo += sz;
-        return vo;
-    };
     if (wave_fast) {
-        static_for<Lat<DIM>::Q>([&](auto ic) { a[decltype(ic)::value] = shifted(ic); });
-    } else if (__ballot(tw & T_EDGE) == 0) {
+        const uint32_t vb = (p - 1u) * SZ;
         static_for<Lat<DIM>::Q>([&](auto ic) {
             constexpr int i = decltype(ic)::value;
-            const uint32_t own = p * SZ + (uint32_t)plane_bytes<STORE>(g, Lat<DIM>::OPP[i]);
-            a[i] = ((tw >> i) & 1u) ? own : shifted(ic) + (uint32_t)plane_bytes<STORE>(g, i);
+            constexpr int ex = Lat<DIM>::E[i][0], ey = Lat<DIM>::E[i][1], ez = Lat<DIM>::E[i][2];
+            uint32_t vo = vb + (uint32_t)(1 - ex) * SZ;
+            if constexpr (ey == 1) vo -= sy;
+            if constexpr (ey == -1) vo += sy;
+            if constexpr (ez == 1) vo -= sz;
+            if constexpr (ez == -1) vo += sz;
+            a[i] = vo;
         });
     } else {
+        // bytes from a node to its source for e = +1 and e = -1 on each axis
+        auto back = [](int v, int n, int per, uint32_t st) { return per && v == 0 ? (uint32_t)(n - 1) * st : 0u - st; };
+        auto fore = [](int v, int n, int per, uint32_t st) { return per && v == n - 1 ? (uint32_t)(1 - n) * st : st; };
+        const uint32_t bx = back(x, g.n[0], g.periodic[0], SZ), fx = fore(x, g.n[0], g.periodic[0], SZ);
+        const uint32_t by = back(y, g.n[1], g.periodic[1], sy), fy = fore(y, g.n[1], g.periodic[1], sy);
+        uint32_t bz = 0u, fz = 0u;
+        if constexpr (DIM == 3) {
+            bz = back(z, g.n[2], g.periodic[2], sz);
+            fz = fore(z, g.n[2], g.periodic[2], sz);
+        }
+        const uint32_t own = p * SZ, stride = (uint32_t)plane_bytes<STORE>(g, 1);
         static_for<Lat<DIM>::Q>([&](auto ic) {
             constexpr int i = decltype(ic)::value;
-            a[i] = (uint32_t)slot_of<DIM>(g, (int64_t)p, tw, x, y, z, i) * SZ;
+            constexpr int ex = Lat<DIM>::E[i][0], ey = Lat<DIM>::E[i][1], ez = Lat<DIM>::E[i][2];
+            uint32_t vo = own;
+            if constexpr (ex != 0) vo += ex == 1 ? bx : fx;
+            if constexpr (ey != 0) vo += ey == 1 ? by : fy;
+            if constexpr (ez != 0) vo += ez == 1 ? bz : fz;
+            a[i] = ((tw >> i) & 1u) ? own + stride * (uint32_t)Lat<DIM>::OPP[i] : vo + stride * (uint32_t)i;
         });
     }
 }
@@ -877,26 +890,28 @@ __device__ __forceinline__ void psi_body(int blk, const typename Codec<STORE>::T
     const bool valid = b < g.N;
     const uint32_t tw = valid ? type[b] : T_SOLID;
     const bool fluid = !(tw & T_SOLID);
-    const bool wave_fast = __ballot(fluid && (tw & (T_BBMASK | T_EDGE))) == 0;
-    if (!valid) return;
-    if (!fluid) {
-        psi[b] = make_float2(-0.0f, -0.0f);
+    if (__ballot(fluid) == 0) {
+        if (valid) psi[b] = make_float2(-0.0f, -0.0f);
         return;
     }
-    int x, y, z;
-    coords_of(g, b, x, y, z);
+    // the other lanes gather the first interior node, unused, so that the
+    // gathers run with the whole wave
+    const uint32_t t = fluid ? tw : 0u;
+    const bool wave_fast = __ballot((t & (T_BBMASK | T_EDGE)) != 0) == 0;
+    int x = 1, y = 1, z = DIM == 3 ? 1 : 0;
+    if (fluid) coords_of(g, b, x, y, z);
     const uint32_t p = (uint32_t)pidx(g, x, y, DIM == 3 ? z : -1);
     float f[Q], r1 = 0.0f, r2 = 0.0f;
     float2 rf = make_float2(0.0f, 0.0f);
-    if constexpr (Codec<STORE>::REF) rf = ref[b];
+    if constexpr (Codec<STORE>::REF) rf = ref[fluid ? b : 0];
     typename Buf<STORE>::Raw h1[Q], h2[Q];
-    bgather2_raw<DIM, STORE>(comp_rsrc<STORE>(src, 0, Q, g.Ppad), comp_rsrc<STORE>(src, 1, Q, g.Ppad), g, p, tw, x,
+    bgather2_raw<DIM, STORE>(comp_rsrc<STORE>(src, 0, Q, g.Ppad), comp_rsrc<STORE>(src, 1, Q, g.Ppad), g, p, t, x,
                              y, z, wave_fast, h1, h2);
     decode<DIM, STORE>(h1, f, rf.x);
     static_for<Q>([&](auto ic) { r1 += f[decltype(ic)::value]; });
     decode<DIM, STORE>(h2, f, rf.y);
     static_for<Q>([&](auto ic) { r2 += f[decltype(ic)::value]; });
-    psi[b] = make_float2(r1, r2);
+    if (valid) psi[b] = fluid ? make_float2(r1, r2) : make_float2(-0.0f, -0.0f);
 }
 
 template <int DIM, int STORE>

@@ -40,7 +40,6 @@ struct Layout {
     int64_t n_slots = 0, n_in = 0, n_out = 0;
     int nb_in = 0, nb_out = 0;     // face-kernel blocks of the inlet nodes and of the outlet column
     int nb_fill = 0;               // blocks of the outlet fill
-    int face_pass = 1;             // see FACE_NT
     int nb_mass = 0;
     bool boundary = false;
     // byte offsets into the workspace
@@ -567,8 +566,7 @@ Layout make_layout(const Canon &k, const Maps &m)
     for (auto s : m.bslot) L.n_slots = std::max<int64_t>(L.n_slots, s + 1);
     L.moving = m.moving;
     L.boundary = L.n_in > 0 || c->has_outlet;
-    L.face_pass = std::max(L.n_in, L.n_out) > FACE_WIDE ? 4 : 1;
-    const int per_block = FACE_NT / 64 * (c->dim == 3 ? FaceMap<3>::NPW : FaceMap<2>::NPW) * L.face_pass;
+    const int per_block = FACE_NT / 64 * (c->dim == 3 ? FaceMap<3>::NPW : FaceMap<2>::NPW);
     const int per_fill = c->dim == 3 ? FillMap<3>::NPB : FillMap<2>::NPB;
     L.nb_in = (int)((L.n_in + per_block - 1) / per_block);
     L.nb_out = (int)((L.n_out + per_block - 1) / per_block);
@@ -1013,7 +1011,6 @@ lbm_status create_ctx(const lbm_config *cfg, void *dev_ws, size_t ws_bytes, void
     bd.out_tab = (const int *)(ws + L.o_out_tab);
     bd.out_enter = cfg->dim == 2 ? entering_lanes<2>(bd.out_axis, bd.out_sign)
                                  : entering_lanes<3>(bd.out_axis, bd.out_sign);
-    bd.face_pass = L.face_pass;
     std::vector<int> in_tab, out_tab;
     if (cfg->dim == 2) face_tables<2>(L.g, m, in_tab, out_tab);
     else face_tables<3>(L.g, m, in_tab, out_tab);

@@ -88,7 +88,6 @@ struct Boundary {
     // x_N stores
     const int *in_tab, *out_tab;
     uint64_t out_enter;       // byte m: lane of the m-th direction entering through the outlet
-    int face_pass;            // records per wave of the face kernels (see FACE_NT)
     const int *bslot;         // [N] face-buffer slot of role nodes, -1 elsewhere
     int n_xp;                 // fluid x_{N-1} nodes; face slots [0, n_in) are the inlet nodes and
                               // [n_in, n_in + n_xp) the x_{N-1} nodes, both in record order
@@ -114,13 +113,11 @@ struct Boundary {
     const float *wallc;
 };
 
-// Threads per block of the face kernels.  A block takes FACE_NT / 64 x
-// face_pass records (twice that in 2-D); face_pass is 1 for faces of up to
-// FACE_WIDE nodes, which then spread over the most CUs, and 4 above, where
-// every CU has work either way and each block of the outlet fill sums the
-// partial sums that all blocks left.
+// Threads per block of the face kernels, which take FACE_NT / 64 nodes in 3-D
+// and twice that in 2-D (several nodes per wave in turn, for fewer blocks on
+// faces of thousands of nodes, was slower up to 3600 nodes and no faster at
+// 14,400).
 constexpr int FACE_NT = 256;
-constexpr int FACE_WIDE = 2048;
 // Lanes per component and node of a face wave, and nodes per wave.
 template <int DIM> struct FaceMap {
     static constexpr int GL = DIM == 3 ? 32 : 16;
