@@ -472,7 +472,12 @@ __device__ __forceinline__ void main_item(const typename Codec<STORE>::T *__rest
     // stream into each ring node, gathered once for its psi and read back by
     // the node update (the same loads, so the same bits).  FP32 would need
     // 39 KB of LDS per block and lose more occupancy than it saves.
-    constexpr bool STAGE = DIM == 2 && PSRC == 0 && STORE != 0;
+    constexpr bool ONE = ZC == W;              // one window: its planes and the halo's are loaded at once
+    // 2-D fused mode, one window: each thread forms psi of its own nodes and
+    // keeps what it gathered for their update; the halo positions follow
+    // (binary16 keeps them in LDS for 32-wide tiles, see STAGE)
+    constexpr bool OWN = DIM == 2 && PSRC == 0 && ONE && KEEPB && (STORE == 0 || TX > 32);
+    constexpr bool STAGE = DIM == 2 && PSRC == 0 && STORE != 0 && !OWN;
     __shared__ typename Buf<STORE>::Raw s_fr[STAGE ? R * PLANE * 2 * Q : 1];
 
     const __amdgpu_buffer_rsrc_t rs0 = comp_rsrc<STORE>(src, 0, Q, g.Ppad);
@@ -593,9 +598,9 @@ __device__ __forceinline__ void main_item(const typename Codec<STORE>::T *__rest
         };
         // the populations of the window's node, where a thread has one node per
         // window: gathered between the ring's loads and their use
-        constexpr bool AHEAD = NPT == 1 && KEEPB && !STAGE;
-        typename Buf<STORE>::Raw q1[Q], q2[Q];
-        constexpr bool ONE = ZC == W;              // one window: its planes and the halo's at once
+        constexpr bool AHEAD = NPT == 1 && KEEPB && !STAGE && !OWN;
+        constexpr int NQ = OWN ? NPT : 1;
+        typename Buf<STORE>::Raw q1[NQ][Q], q2[NQ][Q];
         if constexpr (!ONE) load_planes(std::integral_constant<int, 4>{}, s0 - 2, [] {});
         for (int w0 = s0; w0 < s1; w0 += W) {
             if constexpr (!ONE) __syncthreads();  // ring slots of w0-6..w0-3 are free
@@ -604,7 +609,8 @@ __device__ __forceinline__ void main_item(const typename Codec<STORE>::T *__rest
             // would each wait for the previous node's stores to complete (the
             // memory counter also counts stores)
             uint32_t twq[NPT];
-            static_for<NPT>([&](auto jc) { twq[decltype(jc)::value] = type_of(sweep_of(w0, decltype(jc)::value)); });
+            if constexpr (!OWN)
+                static_for<NPT>([&](auto jc) { twq[decltype(jc)::value] = type_of(sweep_of(w0, decltype(jc)::value)); });
             auto ahead = [&] {
                 if constexpr (AHEAD) {
                     // lanes off the fluid gather a valid node, unused
@@ -614,10 +620,82 @@ __device__ __forceinline__ void main_item(const typename Codec<STORE>::T *__rest
                     const int x = fluid ? x0 + lx : 1, y = fluid ? (DIM == 3 ? y0 + ly : sv) : 1, z = DIM == 3 ? (fluid ? sv : 1) : 0;
                     const bool wave_fast = __ballot((t & (T_BBMASK | T_EDGE)) != 0) == 0;
                     bgather2_raw<DIM, STORE>(rs0, rs1, g, (uint32_t)pidx(g, x, y, DIM == 3 ? z : -1), t, x, y, z,
-                                             wave_fast, q1, q2);
+                                             wave_fast, q1[0], q2[0]);
                 }
             };
-            if constexpr (ONE) load_planes(std::integral_constant<int, W + 4>{}, w0 - 2, ahead);
+            if constexpr (OWN) {
+                // HC halo positions: the rows below and above the window, then
+                // two columns on either side of its rows; thread t takes
+                // t, t + 256, ... of them after its own NPT nodes
+                constexpr int HC = (W + 4) * HX - 256 * NPT, HP = (HC + 255) / 256, U = NPT + HP;
+                static_assert(HC == 4 * HX + 4 * W, "halo of the window");
+                int col[U], row[U], gx[U], gy[U];
+                bool have[U], need[U];
+                static_for<U>([&](auto uc) {
+                    constexpr int u = decltype(uc)::value;
+                    have[u] = true;
+                    if constexpr (u < NPT) {
+                        col[u] = lx + 2;
+                        row[u] = 2 + u * RP + (int)threadIdx.x / TX;
+                    } else {
+                        const int h = (int)threadIdx.x + 256 * (u - NPT), e = h - 4 * HX;
+                        have[u] = h < HC;
+                        const int r4 = h / HX;
+                        row[u] = e < 0 ? (r4 < 2 ? r4 : r4 + W) : 2 + e / 4;
+                        col[u] = e < 0 ? h % HX : (e % 4 < 2 ? e % 4 : e % 4 + TX);
+                    }
+                    const int x = x0 - 2 + col[u], y = w0 - 2 + row[u];
+                    need[u] = have[u] && x < g.n[0] + 2 && y < g.n[1] + 2;
+                    gx[u] = need[u] ? map_axis(x, g.n[0], g.periodic[0]) : 0;
+                    gy[u] = need[u] ? map_axis(y, g.n[1], g.periodic[1]) : 0;
+                });
+                uint32_t tw[U];
+                float2 rf[U];
+                typename Buf<STORE>::Raw g1[HP][Q], g2[HP][Q];
+                static_for<U>([&](auto uc) {
+                    constexpr int u = decltype(uc)::value;
+                    const uint32_t b = (uint32_t)gx[u] + (uint32_t)g.n[0] * (uint32_t)gy[u];
+                    tw[u] = type[b];
+                    rf[u] = make_float2(0.0f, 0.0f);
+                    if constexpr (Codec<STORE>::REF) rf[u] = ref[b];
+                });
+                static_for<U>([&](auto uc) {
+                    constexpr int u = decltype(uc)::value;
+                    // lanes off the fluid gather a valid node, unused, so that
+                    // no load waits at the end of a branch
+                    const bool fluid = need[u] && !(tw[u] & T_SOLID);
+                    tw[u] = fluid ? tw[u] : T_SOLID;
+                    const uint32_t t = fluid ? tw[u] : 0u;
+                    const int ax = fluid ? gx[u] : 1, ay = fluid ? gy[u] : 1;
+                    const bool wave_fast = __ballot((t & (T_BBMASK | T_EDGE)) != 0) == 0;
+                    const uint32_t pp = (uint32_t)pidx(g, ax, ay, -1);
+                    if constexpr (u < NPT)
+                        bgather2_raw<DIM, STORE>(rs0, rs1, g, pp, t, ax, ay, 0, wave_fast, q1[u], q2[u]);
+                    else
+                        bgather2_raw<DIM, STORE>(rs0, rs1, g, pp, t, ax, ay, 0, wave_fast, g1[u - NPT], g2[u - NPT]);
+                });
+                static_for<U>([&](auto uc) {
+                    constexpr int u = decltype(uc)::value;
+                    if (!have[u]) return;
+                    const bool fluid = !(tw[u] & T_SOLID);
+                    float f[Q], p1 = 0.0f, p2 = 0.0f;
+                    if constexpr (u < NPT) decode<DIM, STORE>(q1[u], f, rf[u].x);
+                    else decode<DIM, STORE>(g1[u - NPT], f, rf[u].x);
+                    static_for<Q>([&](auto ic) { p1 += f[decltype(ic)::value]; });
+                    if constexpr (u < NPT) decode<DIM, STORE>(q2[u], f, rf[u].y);
+                    else decode<DIM, STORE>(g2[u - NPT], f, rf[u].y);
+                    static_for<Q>([&](auto ic) { p2 += f[decltype(ic)::value]; });
+                    const int slot = ((w0 - 2 + row[u] + 4 * R) % R) * PLANE + col[u];
+                    s_psi[slot] = fluid ? make_float2(p1, p2) : make_float2(0.0f, 0.0f);
+                    s_sol[slot] = fluid ? 0 : 1;
+                });
+                // own positions outside the item's nodes are halo to others
+                static_for<NPT>([&](auto jc) {
+                    constexpr int j = decltype(jc)::value;
+                    const int sv = sweep_of(w0, j);
+                    twq[j] = x0 + lx < g.n[0] && sv < s1 ? tw[j] : T_SOLID;
+                });
+            } else if constexpr (ONE) load_planes(std::integral_constant<int, W + 4>{}, w0 - 2, ahead);
             else load_planes(std::integral_constant<int, W>{}, w0 + 2, ahead);
             __syncthreads();
             // settle the type loads here, once per window: an empty statement
@@ -644,7 +722,18 @@ __device__ __forceinline__ void main_item(const typename Codec<STORE>::T *__rest
                         ou[bo] = ou[g.N + bo] = ou[2 * g.N + bo] = 0.0;
                     }
                 }
-                if (!fluid) continue;
+                if (!fluid) {
+                    if constexpr (OWN && NPT > 1)
+                        static_for<Q>([&](auto ic) {
+                            constexpr int i = decltype(ic)::value;
+                            static_for<NQ - 1>([&](auto jc) {
+                                constexpr int j = decltype(jc)::value;
+                                q1[j][i] = q1[j + 1][i];
+                                q2[j][i] = q2[j + 1][i];
+                            });
+                        });
+                    continue;
+                }
                 const uint32_t p = (uint32_t)pidx(g, x, y, DIM == 3 ? z : -1);
                 // base[d]: ring index of the lateral corner (-2, -2) of the
                 // node's neighbourhood in sweep plane sv + d - 2, so every
@@ -659,11 +748,16 @@ __device__ __forceinline__ void main_item(const typename Codec<STORE>::T *__rest
                 // the populations of the node: loads issued here, before the
                 // force stencil, so the LDS work below hides their latency
                 typename Buf<STORE>::Raw h1[Q], h2[Q];
-                if constexpr (AHEAD) {
+                if constexpr (AHEAD || OWN) {
                     static_for<Q>([&](auto ic) {
                         constexpr int i = decltype(ic)::value;
-                        h1[i] = q1[i];
-                        h2[i] = q2[i];
+                        h1[i] = q1[0][i];
+                        h2[i] = q2[0][i];
+                        static_for<NQ - 1>([&](auto jc) {
+                            constexpr int j = decltype(jc)::value;
+                            q1[j][i] = q1[j + 1][i];
+                            q2[j][i] = q2[j + 1][i];
+                        });
                     });
                 } else if constexpr (STAGE) {
                     // staged in the ring when psi of this node's plane was formed
@@ -864,12 +958,13 @@ void k_main(const typename Codec<STORE>::T *__restrict__ src,
                                               int *__restrict__ flag, unsigned long long *__restrict__ qacc)
 {
     // blocks go round-robin to the 8 XCDs (blockIdx % 8); each XCD takes
-    // groups of MAIN_XCD_GROUP consecutive work items, so that all XCDs sweep
+    // groups of G consecutive work items (see xcd_group), so that all XCDs sweep
     // nearby addresses at the same time while x-neighbour tiles still share
     // an L2 (measured faster than both one item per XCD turn and contiguous
-    // ranges per XCD); the grid is a multiple of 8 * MAIN_XCD_GROUP blocks
+    // ranges per XCD); the grid is a multiple of 8 G blocks
+    constexpr int G = xcd_group(DIM, PSRC, W == ZC);
     const int S = (int)blockIdx.x / 8, r = (int)blockIdx.x % 8;
-    const int k = ((S / MAIN_XCD_GROUP) * 8 + r) * MAIN_XCD_GROUP + S % MAIN_XCD_GROUP;
+    const int k = ((S / G) * 8 + r) * G + S % G;
     if (k < n_items)
         main_item<DIM, STORE, PSRC, TX, TY, W, ZC, KEEPB>(src, dst, type, psi, ref, g, ph, bd, tiles_x, tiles_y,
                                                           item_list ? item_list[k] : k, flag, qacc);
@@ -960,8 +1055,9 @@ __global__ __launch_bounds__(256) void k_moments(const typename Codec<STORE>::T 
                                                  int *__restrict__ flag, int *__restrict__ host_flag)
 {
     if (blockIdx.x == 0 && threadIdx.x == 0) *host_flag = *flag;
+    constexpr int G = 4;
     const int S = (int)blockIdx.x / 8, r = (int)blockIdx.x % 8;
-    const int k = ((S / MAIN_XCD_GROUP) * 8 + r) * MAIN_XCD_GROUP + S % MAIN_XCD_GROUP;
+    const int k = ((S / G) * 8 + r) * G + S % G;
     if (k < n_items)
         main_item<DIM, STORE, PSRC, TX, TY, W, ZC, 1, true>(src, nullptr, type, psi, ref, g, ph, bd, tiles_x, tiles_y,
                                                             k, flag, nullptr, orho, ou);
@@ -1159,17 +1255,18 @@ __global__ __launch_bounds__(256) void k_psi_batch(BatchTab t, int cur)
 // Persistent node update over the concatenated work items of all members.
 // The blocks (a multiple of 8) step through virtual block indices v; v % 8 is
 // the XCD of the block, and the items are dealt to the XCDs as in k_main, in
-// groups of MAIN_XCD_GROUP consecutive items per turn.
+// groups of G consecutive items per turn.
 template <int DIM, int STORE, int PSRC, int TX, int TY, int W, int ZC, int KEEPB>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(STORE != 0 ? 4 : 1)))
 void k_main_batch(BatchTab t, int cur)
 {
     using T = typename Codec<STORE>::T;
     const int total = t.item0[t.n];
-    const int span = (total + 8 * MAIN_XCD_GROUP - 1) / (8 * MAIN_XCD_GROUP) * (8 * MAIN_XCD_GROUP);
+    constexpr int G = xcd_group(DIM, PSRC, W == ZC);
+    const int span = (total + 8 * G - 1) / (8 * G) * (8 * G);
     for (int v = (int)blockIdx.x; v < span; v += (int)gridDim.x) {
         const int S = v / 8, r = v % 8;
-        const int w = ((S / MAIN_XCD_GROUP) * 8 + r) * MAIN_XCD_GROUP + S % MAIN_XCD_GROUP;
+        const int w = ((S / G) * 8 + r) * G + S % G;
         if (w >= total) continue;
         const int i = __builtin_amdgcn_readfirstlane(t.item_mem[w]);
         CMember *m = (CMember *)(t.m + i);

@@ -88,7 +88,7 @@ void Launcher<DIM>::moments(int storage, const StepArgs &a, int *host_flag)
     if (c.psrc) psi(storage, a);
     const int tx = (a.g.n[0] + c.tx - 1) / c.tx, ty = DIM == 3 ? (a.g.n[1] + c.ty - 1) / c.ty : 1;
     const int64_t items = (int64_t)tx * ty * ((a.g.n[DIM - 1] + c.zc - 1) / c.zc);
-    const unsigned nb = (unsigned)((items + 8 * MAIN_XCD_GROUP - 1) / (8 * MAIN_XCD_GROUP) * (8 * MAIN_XCD_GROUP));
+    const unsigned nb = (unsigned)((items + 31) / 32 * 32);
     with_store(storage, [&](auto sc) {
         using T = LBM_STORE_T(sc);
         hipLaunchKernelGGL((k_moments<DIM, decltype(sc)::value, c.psrc, c.tx, c.ty, c.w, c.zc>), dim3(nb), dim3(256),

@@ -36,7 +36,8 @@ struct Layout {
     int tiles[3] = {1, 1, 1};      // lateral x tiles, lateral y tiles, sweep chunks
     int64_t nblocks_main = 0;      // work items of the node update (tiles holding fluid)
     std::vector<int> item_list;    // their tile indices
-    int64_t grid_main = 0;         // launched blocks (a multiple of 8 * MAIN_XCD_GROUP)
+    bool plain_items = false;      // the list is 0, 1, 2, ...
+    int64_t grid_main = 0;         // launched blocks (a multiple of 8 * xcd_group)
     int64_t n_slots = 0, n_in = 0, n_out = 0;
     int nb_in = 0, nb_out = 0;     // face-kernel blocks of the inlet nodes and of the outlet column
     int nb_fill = 0;               // blocks of the outlet fill
@@ -554,12 +555,25 @@ Layout make_layout(const Canon &k, const Maps &m)
                     live[it] = 1;
                 }
         L.item_list.clear();
-        for (int64_t it = 0; it < all; it++)
-            if (live[it]) L.item_list.push_back((int)it);
+        if (xcd_blocks(c->dim, tc.psrc, tc.w == tc.zc)) {
+            // blocks of tiles, see xcd_group
+            for (int by = 0; by < L.tiles[2]; by += XCD_BLOCK)
+                for (int bx = 0; bx < L.tiles[0]; bx += XCD_BLOCK)
+                    for (int y = by; y < std::min(by + XCD_BLOCK, L.tiles[2]); y++)
+                        for (int x = bx; x < std::min(bx + XCD_BLOCK, L.tiles[0]); x++) {
+                            const int64_t it = x + (int64_t)L.tiles[0] * y;
+                            if (live[it]) L.item_list.push_back((int)it);
+                        }
+        } else {
+            for (int64_t it = 0; it < all; it++)
+                if (live[it]) L.item_list.push_back((int)it);
+        }
     }
+    const int64_t turn = 8 * xcd_group(c->dim, tc.psrc, tc.w == tc.zc);
     L.nblocks_main = (int64_t)L.item_list.size();
-    L.grid_main = std::max<int64_t>((L.nblocks_main + 8 * MAIN_XCD_GROUP - 1) / (8 * MAIN_XCD_GROUP) *
-                                        (8 * MAIN_XCD_GROUP), 8 * MAIN_XCD_GROUP);
+    L.plain_items = L.nblocks_main == (int64_t)L.tiles[0] * L.tiles[1] * L.tiles[2] &&
+                    !xcd_blocks(c->dim, tc.psrc, tc.w == tc.zc);
+    L.grid_main = std::max<int64_t>((L.nblocks_main + turn - 1) / turn * turn, turn);
     L.n_in = (int64_t)m.in.size();
     L.n_out = (int64_t)m.out.size();
     L.n_slots = 0;
@@ -750,9 +764,8 @@ StepArgs step_args(const lbm_ctx *c, double *orho = nullptr, double *ou = nullpt
     a.tiles_x = L.tiles[0];
     a.tiles_y = L.tiles[1];
     a.items = (int)L.nblocks_main;
-    // every tile live: the work item is the tile, no list to read
-    a.item_list = L.nblocks_main == (int64_t)L.tiles[0] * L.tiles[1] * L.tiles[2] ? nullptr
-                                                                                 : (const int *)(c->ws + L.o_items);
+    // every tile live and in tile order: the work item is the tile, no list to read
+    a.item_list = L.plain_items ? nullptr : (const int *)(c->ws + L.o_items);
     a.grid = (unsigned)L.grid_main;
     a.orho = orho;
     a.ou = ou;

@@ -185,10 +185,11 @@ def test_surrogate_predict(members, n):
 
 
 # boxes below, at and just over the tiles (32 and 64 wide, 8 rows) and the
-# sweep windows of the configurations whose ring is filled at once (2-D 8 and
-# 10, 3-D 7 to 10) and window by window (2-D 0 and 4, 3-D 6)
+# sweep windows of the configurations whose ring is filled at once (2-D 8, 10
+# and 11, 3-D 7 to 10) and window by window (2-D 0 and 4, 3-D 6); 9 x 9 tiles
+# of the work list in blocks
 RINGS = [((3, 3, 1), False), ((5, 9, 1), False), ((31, 8, 1), True), ((33, 9, 1), False), ((64, 17, 1), True),
-         ((66, 16, 1), False), ((3, 3, 3), False), ((33, 9, 3), False), ((31, 8, 5), False), ((32, 16, 9), True)]
+         ((66, 16, 1), False), ((290, 70, 1), True), ((3, 3, 3), False), ((33, 9, 3), False), ((31, 8, 5), False), ((32, 16, 9), True)]
 
 
 @pytest.mark.parametrize("storage", ["f32", "f16"])
@@ -197,7 +198,7 @@ def test_ring_edges(shape, walls, storage):
     dim = 2 if shape[2] == 1 else 3
     c = cases.random_box(shape, seed=sum(shape), dim=dim, periodic=(not walls,) * 3, walls=walls, u_amp=0.01,
                          Gw=(0.05, -0.05) if walls else (0.0, 0.0))
-    for cfg in ((0, 4, 8, 10) if dim == 2 else (6, 7, 8, 9, 10)):
+    for cfg in ((0, 4, 8, 10, 11) if dim == 2 else (6, 7, 8, 9, 10)):
         assert _step_error(c, storage, tile_config=cfg) < TOL[storage]
 
 
