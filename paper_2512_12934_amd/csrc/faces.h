@@ -202,25 +202,24 @@ __device__ __forceinline__ int face_first(int blk)
 }
 
 // ---------------------------------------------------------------------------
-// The collision of the outlet column with eq. (22) for a given chi (eq. 23).
+// The collision of the outlet column with eq. (22) for a given chi (eq. 23):
+// outlet record r by this wave (live: the lane's node exists and is this
+// block's to store).  Returns the lane's population as a reader of the stored
+// value gets it.
 // ---------------------------------------------------------------------------
 template <int DIM, int STORE>
-__device__ __forceinline__ void outlet_body(int blk, const typename Codec<STORE>::T *__restrict__ src,
-                                            typename Codec<STORE>::T *__restrict__ dst,
-                                            const float2 *__restrict__ psi, const float2 *__restrict__ ref,
-                                            const Geometry &g, const Physics &ph, const Boundary &bd,
-                                            int *__restrict__ flag, double chi)
+__device__ __forceinline__ float outlet_collide(const FaceLane<DIM> &L, int r, bool live,
+                                                const typename Codec<STORE>::T *__restrict__ src,
+                                                typename Codec<STORE>::T *__restrict__ dst,
+                                                const float2 *__restrict__ psi, const float2 *__restrict__ ref,
+                                                const Geometry &g, const Physics &ph, const Boundary &bd,
+                                                int *__restrict__ flag, double chi)
 {
     constexpr int Q = Lat<DIM>::Q;
-    const FaceLane<DIM> L;
     const Rates rates = {L.k == 0 ? ph.se[0] : ph.se[1], L.k == 0 ? ph.seps[0] : ph.seps[1], ph.sq,
                          L.k == 0 ? ph.snu[0] : ph.snu[1]};
-    const int r0 = face_first<DIM>(blk);
-    if (r0 >= bd.n_out) return;                     // uniform over the wave
-    const bool live = r0 + L.sub < bd.n_out;
-    const int r = live ? r0 + L.sub : r0;
     const OutletRec rec = bd.out[r];
-    const int *tab = bd.out_tab + (int64_t)r * (3 * Q);
+    const int *tab = bd.out_tab + (int64_t)r * (4 * Q);
     float rr = 0.0f, rd = 0.0f;
     const int slot = tab[L.j];
     if constexpr (Codec<STORE>::REF) {
@@ -255,8 +254,22 @@ __device__ __forceinline__ void outlet_body(int blk, const typename Codec<STORE>
     // the rest population is the residual of the density (see collide_pairs)
     const float moving = lane_sum<DIM>(L.on && !L.rest ? fs : 0.0f);
     if (L.rest) fs = rho - moving;
-    if (live && L.on)
-        Codec<STORE>::st(dst + ((int64_t)L.k * Q + L.dir) * g.Ppad + rec.pN, fs, L.w, rd);
+    if (live && L.on) Codec<STORE>::st(dst + ((int64_t)L.k * Q + L.dir) * g.Ppad + rec.pN, fs, L.w, rd);
+    return Codec<STORE>::held(fs, L.w, rd);
+}
+
+template <int DIM, int STORE>
+__device__ __forceinline__ void outlet_body(int blk, const typename Codec<STORE>::T *__restrict__ src,
+                                            typename Codec<STORE>::T *__restrict__ dst,
+                                            const float2 *__restrict__ psi, const float2 *__restrict__ ref,
+                                            const Geometry &g, const Physics &ph, const Boundary &bd,
+                                            int *__restrict__ flag, double chi)
+{
+    const FaceLane<DIM> L;
+    const int r0 = face_first<DIM>(blk);
+    if (r0 >= bd.n_out) return;                         // uniform over the wave
+    const bool live = r0 + L.sub < bd.n_out;
+    (void)outlet_collide<DIM, STORE>(L, live ? r0 + L.sub : r0, live, src, dst, psi, ref, g, ph, bd, flag, chi);
 }
 
 // ---------------------------------------------------------------------------
@@ -324,48 +337,103 @@ __device__ __forceinline__ void inlet_body(int blk, typename Codec<STORE>::T *__
 }
 
 // ---------------------------------------------------------------------------
-// eq. (21): the block's partial sum of the outward normal velocity over
-// x_{N-1}, and how many nodes it holds.
+// eq. (21): the outward normal velocity at x' of record rec from the
+// populations f its lanes hold.
 // ---------------------------------------------------------------------------
+template <int DIM>
+__device__ __forceinline__ float xprime_un(const FaceLane<DIM> &L, const OutletRec &rec, float f, const Boundary &bd)
+{
+    const float Fn = rec.slotP >= 0 ? bd.faceF[(int64_t)rec.slotP * 6 + 3 * L.k + bd.out_axis] : 0.0f;
+    const float d = f - lane_opp(f);
+    const float rho = lane_sum<DIM>(f);
+    const float J = 0.5f * lane_sum<DIM>(lane_pick(L.e, bd.out_axis) * d);
+    const float rt = rho + lane_other<DIM>(rho);
+    const float m = J + 0.5f * Fn;
+    return bd.out_sign * (m + lane_other<DIM>(m)) / rt;
+}
+
+// The block's partial sum, and how many nodes it holds.  One lane per node
+// carries its term.
+template <int DIM>
+__device__ __forceinline__ void uc_store(const FaceLane<DIM> &L, int blk, bool term, float un, const Boundary &bd)
+{
+    __shared__ double s_red[2 * FACE_NT / 64];
+    const bool carry = term && L.k == 0 && L.on && L.j == 0;
+    double su = carry ? (double)un : 0.0, cnt = carry ? 1.0 : 0.0;
+    block_sum2<FACE_NT>(su, cnt, s_red);
+    if (threadIdx.x == 0) {
+        bd.ucpart[2 * blk] = su;
+        bd.ucpart[2 * blk + 1] = cnt;
+    }
+}
+
 template <int DIM, int STORE>
 __device__ __forceinline__ void uc_body(int blk, const typename Codec<STORE>::T *__restrict__ dst,
                                         const float2 *__restrict__ psi, const Geometry &g, const Boundary &bd)
 {
     constexpr int Q = Lat<DIM>::Q;
-    __shared__ double s_red[2 * FACE_NT / 64];
     const FaceLane<DIM> L;
-    double su = 0.0, cnt = 0.0;
+    float un = 0.0f;
+    bool term = false;
     const int r0 = face_first<DIM>(blk);
     if (r0 < bd.n_out) {                                // uniform over the wave
         const bool live = r0 + L.sub < bd.n_out;
         const int r = live ? r0 + L.sub : r0;
         const OutletRec rec = bd.out[r];
         const bool x1 = rec.slotP >= 0;
-        const int slot = bd.out_tab[(int64_t)r * (3 * Q) + Q + L.j];
+        const int slot = bd.out_tab[(int64_t)r * (4 * Q) + Q + L.j];
         float rr = 0.0f;
         if constexpr (Codec<STORE>::REF) {
             const float2 a = psi[rec.bP];
             rr = L.k == 0 ? a.x : a.y;
         }
-        const float raw = L.on && x1 ? Codec<STORE>::ld(dst + (int64_t)L.k * Q * g.Ppad + slot, L.w, rr) : 0.0f;
-        const float Fn = x1 ? bd.faceF[(int64_t)rec.slotP * 6 + 3 * L.k + bd.out_axis] : 0.0f;
-        const float d = raw - lane_opp(raw);
-        const float rho = lane_sum<DIM>(raw);
-        const float J = 0.5f * lane_sum<DIM>(lane_pick(L.e, bd.out_axis) * d);
-        const float rt = rho + lane_other<DIM>(rho);
-        const float m = J + 0.5f * Fn;
-        const float un = bd.out_sign * (m + lane_other<DIM>(m)) / rt;
-        // one lane per node carries its term
-        if (live && x1 && L.k == 0 && L.on && L.j == 0) {
-            su = (double)un;
-            cnt = 1.0;
-        }
+        un = xprime_un<DIM>(L, rec, L.on && x1 ? Codec<STORE>::ld(dst + (int64_t)L.k * Q * g.Ppad + slot, L.w, rr) : 0.0f,
+                            bd);
+        term = live && x1;
     }
-    block_sum2<FACE_NT>(su, cnt, s_red);
-    if (threadIdx.x == 0) {
-        bd.ucpart[2 * blk] = su;
-        bd.ucpart[2 * blk + 1] = cnt;
+    uc_store<DIM>(L, blk, term, un, bd);
+}
+
+// ---------------------------------------------------------------------------
+// Outlet collision and eq. (21) sums in one launch (2-D, see UcMap).  What x'
+// takes from the outlet column comes through LDS, as the stored value reads;
+// the rest was stored by the node update and is loaded with the outlet's own
+// populations.  Saves the launch that summed eq. (21) (4.4 of 18.3 us of the
+// 800x100 T-junction's step).
+// ---------------------------------------------------------------------------
+template <int STORE>
+__device__ __forceinline__ void outlet_uc_body(int blk, const typename Codec<STORE>::T *__restrict__ src,
+                                               typename Codec<STORE>::T *__restrict__ dst,
+                                               const float2 *__restrict__ psi, const float2 *__restrict__ ref,
+                                               const Geometry &g, const Physics &ph, const Boundary &bd,
+                                               int *__restrict__ flag, double chi)
+{
+    constexpr int Q = Lat<2>::Q;
+    __shared__ float s_f[UcMap::NS * 2 * Q];
+    const FaceLane<2> L;
+    const int s = ((int)threadIdx.x >> 6) * FaceMap<2>::NPW + L.sub;      // node of the block
+    const int first = blk * UcMap::INNER - 1, want = first + s;
+    const bool mine = s >= 1 && s <= UcMap::INNER && want < bd.n_out;
+    const int r = min(max(want, 0), bd.n_out - 1);
+    const OutletRec rec = bd.out[r];
+    const bool x1 = rec.slotP >= 0;
+    const int *tab = bd.out_tab + (int64_t)r * (4 * Q);
+    const int from = bd.chi_on ? tab[3 * Q + L.j] : -1;
+    float rr = 0.0f;
+    if constexpr (Codec<STORE>::REF) {
+        const float2 a = psi[rec.bP];
+        rr = L.k == 0 ? a.x : a.y;
     }
+    float f = 0.0f;
+    if (L.on && x1 && from < 0) f = Codec<STORE>::ld(dst + (int64_t)L.k * Q * g.Ppad + tab[Q + L.j], L.w, rr);
+    if (bd.chi_on) {                                    // else the node update collided the outlet column
+        const float h = outlet_collide<2, STORE>(L, r, mine, src, dst, psi, ref, g, ph, bd, flag, chi);
+        if (L.on) s_f[(s * 2 + L.k) * Q + L.j] = h;
+        __syncthreads();
+        if (L.on && x1 && from >= 0 && mine) f = s_f[((from - first) * 2 + L.k) * Q + L.j];
+    }
+    const float un = xprime_un<2>(L, rec, f, bd);
+    uc_store<2>(L, blk, mine && x1, un, bd);
 }
 
 // ---------------------------------------------------------------------------
@@ -391,7 +459,7 @@ __device__ __forceinline__ void outlet_fill_body(int blk, typename Codec<STORE>:
         const int i = lane_dir<DIM>(j);
         w = j < 2 * DIM ? weight<DIM>(1) : 1.0f / 36.0f;      // an entering direction is never at rest
         const OutletRec rec = bd.out[r];
-        const int *tab = bd.out_tab + (int64_t)r * (3 * Q) + j;
+        const int *tab = bd.out_tab + (int64_t)r * (4 * Q) + j;
         typename Codec<STORE>::T *dk = dst + (int64_t)k * Q * g.Ppad;
         inside = rec.slotP >= 0;
         at = dk + tab[0];
@@ -432,8 +500,8 @@ __global__ __launch_bounds__(FACE_NT) void k_outlet_fill(typename Codec<STORE>::
 
 // ---------------------------------------------------------------------------
 // k_faces: the first launch after the node update.  chi from this step's
-// sums; blocks [0, nb_out) collide the outlet column, blocks [nb_out,
-// nb_out + nb_in) rebuild inlet nodes (only when no inlet node pulls from the
+// sums; blocks [0, nb_out) collide the outlet column (and sum eq. 21 where
+// bd.uc_early), blocks [nb_out, nb_out + nb_in) rebuild inlet nodes (only when no inlet node pulls from the
 // outlet column, checked at creation, so the two sets are independent).
 // ---------------------------------------------------------------------------
 template <int DIM, int STORE>
@@ -447,6 +515,12 @@ __device__ __forceinline__ void faces_body(int blk, const typename Codec<STORE>:
     if (blk < nb_out || blk == 0) {
         const double chi = chi_from(bd, acc, next, blk == 0 && threadIdx.x == 0);
         if (blk < nb_out) {
+            if constexpr (DIM == 2) {
+                if (bd.uc_early) {
+                    outlet_uc_body<STORE>(blk, src, dst, psi, ref, g, ph, bd, flag, chi);
+                    return;
+                }
+            }
             outlet_body<DIM, STORE>(blk, src, dst, psi, ref, g, ph, bd, flag, chi);
             return;
         }
@@ -467,7 +541,7 @@ __global__ __launch_bounds__(FACE_NT) void k_faces(const typename Codec<STORE>::
 
 // ---------------------------------------------------------------------------
 // k_inlet: blocks [0, nb_in) take the inlet nodes that k_faces did not,
-// blocks [nb_in, ...) the partial sums of eq. (21).
+// blocks [nb_in, ...) the partial sums of eq. (21) (neither: not launched).
 // ---------------------------------------------------------------------------
 template <int DIM, int STORE>
 __device__ __forceinline__ void inlet_uc_body(int blk, typename Codec<STORE>::T *__restrict__ dst,

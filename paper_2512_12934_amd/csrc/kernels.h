@@ -58,18 +58,30 @@ template <> struct Codec<0> {
     static constexpr bool REF = false;
     static __device__ __forceinline__ float ld(const T *p, float w, float) { return *p + w; }
     static __device__ __forceinline__ void st(T *p, float v, float w, float) { *p = v - w; }
+    // what a reader of the stored value gets
+    static __device__ __forceinline__ float held(float v, float w, float) { return (v - w) + w; }
 };
 template <> struct Codec<1> {
     using T = __half;
     static constexpr bool REF = true;
     static __device__ __forceinline__ float ld(const T *p, float w, float r) { return __half2float(*p) + w * r; }
     static __device__ __forceinline__ void st(T *p, float v, float w, float r) { *p = __float2half_rn(v - w * r); }
+    static __device__ __forceinline__ float held(float v, float w, float r)
+    {
+        const T h = __float2half_rn(v - w * r);
+        return __half2float(h) + w * r;
+    }
 };
 template <> struct Codec<2> {
     using T = __half;
     static constexpr bool REF = false;
     static __device__ __forceinline__ float ld(const T *p, float w, float) { return __half2float(*p) + w; }
     static __device__ __forceinline__ void st(T *p, float v, float w, float) { *p = __float2half_rn(v - w); }
+    static __device__ __forceinline__ float held(float v, float w, float)
+    {
+        const T h = __float2half_rn(v - w);
+        return __half2float(h) + w;
+    }
 };
 
 // Raw buffer access for the node update: one descriptor per component array

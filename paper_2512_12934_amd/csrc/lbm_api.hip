@@ -40,6 +40,8 @@ struct Layout {
     int64_t grid_main = 0;         // launched blocks (a multiple of 8 * xcd_group)
     int64_t n_slots = 0, n_in = 0, n_out = 0;
     int nb_in = 0, nb_out = 0;     // face-kernel blocks of the inlet nodes and of the outlet column
+    bool uc_early = false;         // eq. (21) in the outlet collision's launch (see UcMap)
+    int nb_coll = 0, nb_uc = 0;    // outlet blocks of the first face launch and of the second
     int nb_fill = 0;               // blocks of the outlet fill
     int nb_mass = 0;
     bool boundary = false;
@@ -62,6 +64,7 @@ struct Maps {
     std::vector<InletRec> in;
     std::vector<OutletRec> out;
     int n_xp = 0;                  // fluid x_{N-1} nodes (slots n_in .. n_in + n_xp)
+    bool uc_neighbours = true;         // x' streams from its outlet node and that one's neighbours in record order only
     bool inlet_pulls_outlet = false;   // an inlet node x1 or x2 streams from an outlet node
 };
 
@@ -184,6 +187,28 @@ std::string canonicalize(const lbm_config *in, Canon &k)
     // rho0 / u0 stay in the caller's frame: the initial state is built there
     // and scattered through the frame map
     return "";
+}
+
+// The outlet record whose collision supplies population i of box node b (it
+// streams from that outlet node), or -1.
+int outlet_source(const lbm_config *c, const Maps &m, int64_t b, int i)
+{
+    if ((m.type[b] >> i) & 1u) return -1;               // bounce-back: its own
+    int e[3];
+    dir(c->dim, i, e);
+    int x[3] = {(int)(b % c->n[0]), (int)((b / c->n[0]) % c->n[1]), (int)(b / ((int64_t)c->n[0] * c->n[1]))};
+    for (int a = 0; a < c->dim; a++) {
+        x[a] -= e[a];
+        if (x[a] >= 0 && x[a] < c->n[a]) continue;
+        if (!c->periodic[a]) return -1;
+        x[a] = (x[a] + c->n[a]) % c->n[a];
+    }
+    const int64_t sb = (int64_t)x[0] + (int64_t)c->n[0] * ((int64_t)x[1] + (int64_t)c->n[1] * x[2]);
+    if (!(m.type[sb] & T_OUTLET)) return -1;
+    // the records are in box order
+    const auto it = std::lower_bound(m.out.begin(), m.out.end(), sb,
+                                     [](const OutletRec &r, int64_t v) { return r.bN < v; });
+    return (int)(it - m.out.begin());
 }
 
 // Validates the configuration and builds the node maps.  Returns an empty
@@ -408,6 +433,11 @@ std::string build_maps(const lbm_config *c, Maps &m)
         r.slotP = r.bP >= 0 ? m.bslot[r.bP] : -1;
         if (r.bP < 0) r.bP = r.bN;
     }
+    for (size_t r = 0; r < m.out.size() && c->dim == 2; r++)
+        for (int i = 0; i < Q && m.out[r].slotP >= 0; i++) {
+            const int from = outlet_source(c, m, m.out[r].bP, i);
+            if (from >= 0 && std::abs(from - (int)r) > 1) m.uc_neighbours = false;
+        }
     return "";
 }
 
@@ -421,7 +451,7 @@ int default_cfg(const lbm_config *c)
 
 // Fills the records' padded indices and the slot tables of the face kernels.
 template <int DIM>
-void face_tables(const Geometry &g, Maps &m, std::vector<int> &in_tab, std::vector<int> &out_tab)
+void face_tables(const lbm_config *c, const Geometry &g, Maps &m, std::vector<int> &in_tab, std::vector<int> &out_tab)
 {
     constexpr int Q = Lat<DIM>::Q;
     auto coords = [&](int b, int *x) {
@@ -460,7 +490,7 @@ void face_tables(const Geometry &g, Maps &m, std::vector<int> &in_tab, std::vect
         return x[0] + g.n[0] * (x[1] + g.n[1] * x[2]);
     };
     in_tab.resize(m.in.size() * 2 * Q);
-    out_tab.resize(m.out.size() * 3 * Q);
+    out_tab.resize(m.out.size() * 4 * Q);
     for (size_t r = 0; r < m.in.size(); r++)
         for (int j = 0; j < Q; j++) {
             in_tab[(2 * r) * Q + j] = slot(m.in[r].b1, lane_dir<DIM>(j));
@@ -471,9 +501,10 @@ void face_tables(const Geometry &g, Maps &m, std::vector<int> &in_tab, std::vect
         coords(m.out[r].bN, x);
         m.out[r].pN = (int)padded(x);
         for (int j = 0; j < Q; j++) {
-            out_tab[(3 * r) * Q + j] = slot(m.out[r].bN, lane_dir<DIM>(j));
-            out_tab[(3 * r + 1) * Q + j] = slot(m.out[r].bP, lane_dir<DIM>(j));
-            out_tab[(3 * r + 2) * Q + j] = reader(m.out[r].bN, lane_dir<DIM>(j));
+            out_tab[(4 * r) * Q + j] = slot(m.out[r].bN, lane_dir<DIM>(j));
+            out_tab[(4 * r + 1) * Q + j] = slot(m.out[r].bP, lane_dir<DIM>(j));
+            out_tab[(4 * r + 2) * Q + j] = reader(m.out[r].bN, lane_dir<DIM>(j));
+            out_tab[(4 * r + 3) * Q + j] = m.out[r].slotP >= 0 ? outlet_source(c, m, m.out[r].bP, lane_dir<DIM>(j)) : -1;
         }
     }
 }
@@ -583,7 +614,11 @@ Layout make_layout(const Canon &k, const Maps &m)
     const int per_block = FACE_NT / 64 * (c->dim == 3 ? FaceMap<3>::NPW : FaceMap<2>::NPW);
     const int per_fill = c->dim == 3 ? FillMap<3>::NPB : FillMap<2>::NPB;
     L.nb_in = (int)((L.n_in + per_block - 1) / per_block);
-    L.nb_out = (int)((L.n_out + per_block - 1) / per_block);
+    L.uc_early = c->dim == 2 && m.uc_neighbours;
+    const int per_out = L.uc_early ? UcMap::INNER : per_block;
+    L.nb_out = (int)((L.n_out + per_out - 1) / per_out);
+    L.nb_coll = L.uc_early || (c->has_outlet && c->outlet.chi_on) ? L.nb_out : 0;
+    L.nb_uc = L.uc_early ? 0 : L.nb_out;
     L.nb_fill = (int)((L.n_out + per_fill - 1) / per_fill);
     L.inlet_early = !(c->has_outlet && c->outlet.chi_on) || !m.inlet_pulls_outlet;
     L.nb_mass = (int)std::min<int64_t>(1024, (g.N + 255) / 256);
@@ -599,7 +634,7 @@ Layout make_layout(const Canon &k, const Maps &m)
     L.o_in = take((size_t)L.n_in * sizeof(InletRec));
     L.o_out = take((size_t)L.n_out * sizeof(OutletRec));
     L.o_in_tab = take((size_t)L.n_in * 2 * L.Q * 4);
-    L.o_out_tab = take((size_t)L.n_out * 3 * L.Q * 4);
+    L.o_out_tab = take((size_t)L.n_out * 4 * L.Q * 4);
     L.o_qacc = take(4 * sizeof(unsigned long long));
     L.o_ucpart = take((size_t)std::max(L.nb_out, 1) * 16);
     L.o_scal = take(SC_COUNT * 8);
@@ -808,16 +843,15 @@ template <int DIM> struct Ops {
         if (L.boundary) {
             const StepArgs a = step_args(c);
             // chi, the outlet collision and (when independent of it) the inlet nodes
-            const int nb_coll = c->bd.has_outlet && c->bd.chi_on ? L.nb_out : 0;
             const int nb_in_early = L.inlet_early ? L.nb_in : 0;
             if (ev) (void)hipEventRecord(ev[2], c->stream);
-            Lx::faces(L.storage, a, nb_coll, nb_in_early);
+            Lx::faces(L.storage, a, L.nb_coll, nb_in_early);
             if (ev) (void)hipEventRecord(ev[3], c->stream);
-            // the remaining inlet nodes, then the U_c partial sums of eq. (21)
+            // the remaining inlet nodes and U_c partial sums of eq. (21)
             const int nb_in_late = L.nb_in - nb_in_early;
-            if (nb_in_late + L.nb_out > 0) {
+            if (nb_in_late + L.nb_uc > 0) {
                 if (ev) (void)hipEventRecord(ev[4], c->stream);
-                Lx::inlet(L.storage, a, (unsigned)(nb_in_late + L.nb_out), nb_in_late);
+                Lx::inlet(L.storage, a, (unsigned)(nb_in_late + L.nb_uc), nb_in_late);
                 if (ev) (void)hipEventRecord(ev[5], c->stream);
             }
             if (L.nb_out > 0) {
@@ -1020,13 +1054,14 @@ lbm_status create_ctx(const lbm_config *cfg, void *dev_ws, size_t ws_bytes, void
     bd.qacc = (unsigned long long *)(ws + L.o_qacc);
     bd.ucpart = (double *)(ws + L.o_ucpart);
     bd.n_ucpart = L.nb_out;
+    bd.uc_early = L.uc_early ? 1 : 0;
     bd.in_tab = (const int *)(ws + L.o_in_tab);
     bd.out_tab = (const int *)(ws + L.o_out_tab);
     bd.out_enter = cfg->dim == 2 ? entering_lanes<2>(bd.out_axis, bd.out_sign)
                                  : entering_lanes<3>(bd.out_axis, bd.out_sign);
     std::vector<int> in_tab, out_tab;
-    if (cfg->dim == 2) face_tables<2>(L.g, m, in_tab, out_tab);
-    else face_tables<3>(L.g, m, in_tab, out_tab);
+    if (cfg->dim == 2) face_tables<2>(cfg, L.g, m, in_tab, out_tab);
+    else face_tables<3>(cfg, L.g, m, in_tab, out_tab);
     bd.scal = (double *)(ws + L.o_scal);
     bd.patch = (const Patch *)(ws + L.o_patch);
     bd.hist = (float *)(ws + L.o_hist);
@@ -1231,7 +1266,7 @@ lbm_status lbm_time_kernels(lbm_ctx *c, int64_t n, double *ms)
     HIPCHECK(c, hipStreamSynchronize(c->stream));
     c->steps += n;
     const bool used[5] = {true, c->L.boundary,
-                          c->L.boundary && (c->L.inlet_early ? 0 : c->L.nb_in) + c->L.nb_out > 0,
+                          c->L.boundary && (c->L.inlet_early ? 0 : c->L.nb_in) + c->L.nb_uc > 0,
                           c->L.boundary && c->L.nb_out > 0, c->L.psi_mode != 0};
     for (int k = 0; k < 5; k++) {
         double acc = 0.0;
@@ -1450,7 +1485,7 @@ lbm_status lbm_batch_create(const lbm_config *cfgs, int n, void *dev_ws, size_t 
         M.tiles_y = L.tiles[1];
         M.n_items = (int)L.nblocks_main;
         M.item_list = (const int *)(c->ws + L.o_items);
-        M.nb_coll = c->bd.has_outlet && c->bd.chi_on ? L.nb_out : 0;
+        M.nb_coll = L.nb_coll;
         M.nb_in_early = L.inlet_early ? L.nb_in : 0;
         M.nb_in_late = L.nb_in - M.nb_in_early;
         M.flag = c->flag();
@@ -1459,7 +1494,7 @@ lbm_status lbm_batch_create(const lbm_config *cfgs, int n, void *dev_ws, size_t 
         // at least one block of the first face launch: it records the eq. 23
         // sums and clears the next ones
         fac0[i + 1] = fac0[i] + (L.boundary ? std::max(1, M.nb_coll + M.nb_in_early) : 0);
-        inl0[i + 1] = inl0[i] + (L.boundary ? M.nb_in_late + L.nb_out : 0);
+        inl0[i + 1] = inl0[i] + (L.boundary ? M.nb_in_late + L.nb_uc : 0);
         fill0[i + 1] = fill0[i] + (L.boundary ? L.nb_fill : 0);
     }
     char *t = ws + off;

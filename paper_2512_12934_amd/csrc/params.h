@@ -83,10 +83,11 @@ struct Boundary {
     const InletRec *in;
     const OutletRec *out;
     // population slots within one component array, in lane order (lane_dir):
-    // [n_in][2][Q] those that stream into x1 and x2, [n_out][3][Q] those that
-    // stream into x_N and x', and the box index of the node that reads what
-    // x_N stores
+    // [n_in][2][Q] those that stream into x1 and x2; [n_out][4][Q] those that
+    // stream into x_N and x', the box index of the node that reads what x_N
+    // stores, and the outlet record whose collision supplies x' (-1: none)
     const int *in_tab, *out_tab;
+    int uc_early;             // eq. (21) summed in the outlet collision's launch (see UcMap)
     uint64_t out_enter;       // byte m: lane of the m-th direction entering through the outlet
     const int *bslot;         // [N] face-buffer slot of role nodes, -1 elsewhere
     int n_xp;                 // fluid x_{N-1} nodes; face slots [0, n_in) are the inlet nodes and
@@ -122,6 +123,14 @@ constexpr int FACE_NT = 256;
 template <int DIM> struct FaceMap {
     static constexpr int GL = DIM == 3 ? 32 : 16;
     static constexpr int NPW = 64 / (2 * GL);
+};
+// The outlet collision with the eq. (21) sums in the same launch (2-D faces
+// whose x' nodes stream from their own outlet node and its two neighbours in
+// record order): a block collides NS consecutive outlet nodes and sums x' of
+// the inner ones, so its neighbours repeat two of them.
+struct UcMap {
+    static constexpr int NS = FACE_NT / 64 * FaceMap<2>::NPW;
+    static constexpr int INNER = NS - 2;
 };
 // The outlet fill: entering directions, lanes per component and node, nodes
 // per block.
