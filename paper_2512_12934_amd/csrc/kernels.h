@@ -966,7 +966,7 @@ void k_main(const typename Codec<STORE>::T *__restrict__ src,
                                               const uint32_t *__restrict__ type,
                                               const float2 *__restrict__ psi, const float2 *__restrict__ ref,
                                               Geometry g, Physics ph, Boundary bd, int tiles_x, int tiles_y,
-                                              int n_items, const int *__restrict__ item_list,
+                                              int n_items, int reverse, const int *__restrict__ item_list,
                                               int *__restrict__ flag, unsigned long long *__restrict__ qacc)
 {
     // blocks go round-robin to the 8 XCDs (blockIdx % 8); each XCD takes
@@ -976,10 +976,11 @@ void k_main(const typename Codec<STORE>::T *__restrict__ src,
     // ranges per XCD); the grid is a multiple of 8 G blocks
     constexpr int G = xcd_group(DIM, PSRC, W == ZC);
     const int S = (int)blockIdx.x / 8, r = (int)blockIdx.x % 8;
-    const int k = ((S / G) * 8 + r) * G + S % G;
-    if (k < n_items)
-        main_item<DIM, STORE, PSRC, TX, TY, W, ZC, KEEPB>(src, dst, type, psi, ref, g, ph, bd, tiles_x, tiles_y,
-                                                          item_list ? item_list[k] : k, flag, qacc);
+    int k = ((S / G) * 8 + r) * G + S % G;
+    if (k >= n_items) return;
+    if (reverse) k = n_items - 1 - k;
+    main_item<DIM, STORE, PSRC, TX, TY, W, ZC, KEEPB>(src, dst, type, psi, ref, g, ph, bd, tiles_x, tiles_y,
+                                                      item_list ? item_list[k] : k, flag, qacc);
 }
 
 // ---------------------------------------------------------------------------

@@ -72,6 +72,7 @@ struct StepArgs {
     Boundary bd;
     int tiles_x, tiles_y, items;
     const int *item_list;
+    int reverse;        // the node update takes its work items last to first
     unsigned grid;
     double *orho, *ou;
     int *flag;

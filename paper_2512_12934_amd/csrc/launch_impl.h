@@ -22,7 +22,7 @@ void launch_cfg(const StepArgs &a)
     using T = typename Codec<STORE>::T;
     hipLaunchKernelGGL((k_main<DIM, STORE, c.psrc, c.tx, c.ty, c.w, c.zc, c.keepb>), dim3(a.grid), dim3(256), 0,
                        a.stream, (const T *)a.src, (T *)a.dst, a.type, (const float2 *)a.psi, a.ref, a.g, a.ph,
-                       a.bd, a.tiles_x, a.tiles_y, a.items, a.item_list, a.flag, a.qacc);
+                       a.bd, a.tiles_x, a.tiles_y, a.items, a.reverse, a.item_list, a.flag, a.qacc);
 }
 
 template <int DIM, int STORE, int... I>

@@ -25,6 +25,7 @@ using namespace lbm;
 namespace {
 
 constexpr size_t ALIGN = 256;
+constexpr size_t LAST_LEVEL_CACHE = (size_t)256 << 20;
 
 thread_local std::string g_create_error;
 
@@ -799,6 +800,14 @@ StepArgs step_args(const lbm_ctx *c, double *orho = nullptr, double *ou = nullpt
     a.tiles_x = L.tiles[0];
     a.tiles_y = L.tiles[1];
     a.items = (int)L.nblocks_main;
+    // The density pass leaves the end of the populations in the 256 MB last
+    // level cache, so the node update after it starts there, and the next
+    // density pass starts where the node update ended.  Populations that fit
+    // are all still there and go first to last, ahead of the update's own
+    // stores.  us per step, first to last / last to first: 600x120x120 FP32
+    // (1.40 GB) 932 / 916, 400x90x90 (0.57 GB) 384 / 373, 300x60x60 (0.20 GB)
+    // 135 / 139.
+    a.reverse = L.psi_mode && L.o_fB - L.o_fA > LAST_LEVEL_CACHE;
     // every tile live and in tile order: the work item is the tile, no list to read
     a.item_list = L.plain_items ? nullptr : (const int *)(c->ws + L.o_items);
     a.grid = (unsigned)L.grid_main;

@@ -236,6 +236,21 @@ def test_ring_edges(shape, walls, storage):
         assert _step_error(c, storage, tile_config=cfg) < TOL[storage]
 
 
+@pytest.mark.parametrize("storage,nz", [("f32", 70), ("f16", 140)])
+@pytest.mark.parametrize("walls", [False, True])
+def test_large_domain_order(storage, nz, walls):
+    """Populations beyond the last level cache: the node update takes its work
+    items last to first, with a work list (walls) and without one; in a batch
+    it takes the same ones first to last.  Equal to the bit."""
+    from paper_2512_12934_amd.lbm import LBM, Batch
+    c = cases.random_box((300, 90, nz), seed=3, dim=3, periodic=(not walls,) * 3, walls=walls, u_amp=0.01)
+    print(f"[gpu] {c.n} {storage} walls={walls}", flush=True)
+    g, b = LBM(c, storage=storage, tile_config=6), Batch([c], storage=storage, tile_config=6)
+    g.step(2)
+    b.step(2)
+    assert np.array_equal(g.get_state(), b.members[0].get_state())
+
+
 @pytest.mark.parametrize("storage", ["f32", "f16"])
 @pytest.mark.parametrize("shape,walls", RINGS)
 def test_moments_edges(shape, walls, storage):
