@@ -1027,7 +1027,9 @@ __global__ __launch_bounds__(256) void k_psi(const typename Codec<STORE>::T *__r
                                              const uint32_t *__restrict__ type, Geometry g,
                                              float2 *__restrict__ psi, const float2 *__restrict__ ref)
 {
-    psi_body<DIM, STORE>((int)blockIdx.x, src, type, g, psi, ref);
+    constexpr int G = PSI_GROUP;
+    const int S = (int)blockIdx.x / 8, r = (int)blockIdx.x % 8;
+    psi_body<DIM, STORE>(((S / G) * 8 + r) * G + S % G, src, type, g, psi, ref);
 }
 
 // Density and momentum of the populations of one component.  The momentum is

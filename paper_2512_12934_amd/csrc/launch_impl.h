@@ -71,7 +71,8 @@ template <typename F> void with_store(int storage, F &&f)
 template <int DIM>
 void Launcher<DIM>::psi(int storage, const StepArgs &a)
 {
-    const unsigned nb = (unsigned)((a.g.N + 255) / 256);
+    constexpr unsigned turn = 8 * PSI_GROUP;
+    const unsigned nb = ((unsigned)((a.g.N + 255) / 256) + turn - 1) / turn * turn;
     with_store(storage, [&](auto sc) {
         using T = LBM_STORE_T(sc);
         hipLaunchKernelGGL((k_psi<DIM, decltype(sc)::value>), dim3(nb), dim3(256), 0, a.stream, (const T *)a.src,

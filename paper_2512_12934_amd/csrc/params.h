@@ -154,6 +154,14 @@ constexpr int xcd_group(int dim, int psrc, bool one_window)
     return xcd_blocks(dim, psrc, one_window) ? XCD_BLOCK * XCD_BLOCK : 4;
 }
 
+// The density pass: consecutive blocks of 256 nodes that one XCD takes per
+// turn.  A block's ends share their memory lines with the next block's, which
+// one block per turn fetched into two L2s (binary16, with 64 populations a
+// line, read 1.28 times the populations of the 600x120x120 device, now 1.10;
+// FP32 1.21, now 1.06).  300x60x60 binary16 23.0 -> 20.1 us, 250x51x51 15.7
+// -> 14.1, FP32 and larger domains within 1%; 4 and 64 blocks are no better.
+constexpr int PSI_GROUP = 16;
+
 // One member of a batch: what a single context passes to its step kernels.
 struct Member {
     void *f[2];                // population arrays A and B
