@@ -516,20 +516,51 @@ __device__ __forceinline__ void main_item(const typename Codec<STORE>::T *__rest
         // of a 64x64 box 11.7 -> 9.3 us, of the 600x120x120 device 593 -> 560).
         // between() runs after the first loads are issued.
         auto load_planes = [&](auto npc, int pa, auto &&between) {
-            constexpr int NP = decltype(npc)::value, CNT = NP * PLANE, IT = (CNT + 255) / 256;
+            constexpr int NP = decltype(npc)::value;
+            // PSRC 1 in 3-D: a thread keeps its lateral positions from plane to
+            // plane (NL of them), so that a load's address is the plane's
+            // (scalar) and the position's; the last 256 positions of a plane
+            // are dealt like that if at least half are there, and otherwise
+            // counted through all planes like every position of the other modes
+            // (which form each position's coordinates anew, some 35 operations;
+            // that took the binary16 node update of the 600x120x120 device from
+            // 378 to 412 us and of 300x60x60 from 63 to 70, FP32 of the latter
+            // from 75.6 to 78.5)
+            constexpr int NL = DIM == 3 && PSRC == 1 ? (PLANE + 127) / 256 : 0;
+            constexpr int LAT = NL * 256, REST = LAT < PLANE ? PLANE - LAT : 0;
+            constexpr int CNT = NP * REST, ITL = NP * NL, IT = ITL + (CNT + 255) / 256;
             constexpr int UMAX = PSRC == 1 ? 8 : 2;
             constexpr int U = (IT + (IT + UMAX - 1) / UMAX - 1) / ((IT + UMAX - 1) / UMAX);
+            int lat[NL ? NL : 1];
+            static_for<NL>([&](auto jc) {
+                constexpr int j = decltype(jc)::value;
+                const int r = min((int)threadIdx.x + 256 * j, PLANE - 1);
+                const int x = x0 - 2 + r % HX, y = y0 - 2 + r / HX;
+                const bool in = x < g.n[0] + 2 && y < g.n[1] + 2;
+                lat[j] = in ? map_axis(x, g.n[0], g.periodic[0]) + g.n[0] * map_axis(y, g.n[1], g.periodic[1]) : 0;
+            });
             static_for<(IT + U - 1) / U>([&](auto cc) {
                 constexpr int C = decltype(cc)::value;
                 int slot[U], gx[U], gy[U], gz[U];
                 bool have[U], need[U];
                 static_for<U>([&](auto uc) {
-                    constexpr int u = decltype(uc)::value;
-                    const int h = (int)threadIdx.x + 256 * (C * U + u);
-                    const int pl = pa + h / PLANE, r = h % PLANE;
+                    constexpr int u = decltype(uc)::value, it = C * U + u;
+                    if constexpr (it < ITL) {
+                        constexpr int j = it % NL;
+                        const int pl = pa + it / NL;
+                        have[u] = 256 * (j + 1) <= PLANE || (int)threadIdx.x + 256 * j < PLANE;
+                        need[u] = pl < g.n[2] + 2;
+                        slot[u] = ((pl + 4 * R) % R) * PLANE + (int)threadIdx.x + 256 * j;
+                        gx[u] = lat[j];
+                        gy[u] = 0;
+                        gz[u] = need[u] ? map_axis(pl, g.n[2], g.periodic[2]) : 0;
+                        return;
+                    }
+                    const int h = (int)threadIdx.x + 256 * (it - ITL);
+                    const int pl = pa + h / (REST ? REST : 1), r = LAT + h % (REST ? REST : 1);
                     const int lx = r % HX, ly = r / HX;
-                    have[u] = C * U + u + 1 < IT ? true : h < CNT;
-                    if (C * U + u >= IT) have[u] = false;
+                    have[u] = it + 1 < IT ? true : h < CNT;
+                    if (it >= IT) have[u] = false;
                     int x = x0 - 2 + lx, y = DIM == 3 ? y0 - 2 + ly : pl, z = DIM == 3 ? pl : 0;
                     need[u] = have[u] && x < g.n[0] + 2 && y < g.n[1] + 2 && (DIM == 2 || z < g.n[2] + 2);
                     slot[u] = ((pl + 4 * R) % R) * PLANE + r;
@@ -545,7 +576,13 @@ __device__ __forceinline__ void main_item(const typename Codec<STORE>::T *__rest
                     // psi of this step from k_psi; solids carry -0.0 (zero in
                     // every sum, and the sign marks them for the adhesion stencil)
                     float2 v[U];
-                    static_for<U>([&](auto uc) { v[decltype(uc)::value] = psi[box(decltype(uc)::value)]; });
+                    static_for<U>([&](auto uc) {
+                        constexpr int u = decltype(uc)::value;
+                        if constexpr (C * U + u < ITL)
+                            v[u] = (psi + (int64_t)g.n[0] * g.n[1] * gz[u])[(uint32_t)gx[u]];
+                        else
+                            v[u] = psi[box(u)];
+                    });
                     if constexpr (C == 0) between();
                     static_for<U>([&](auto uc) {
                         constexpr int u = decltype(uc)::value;
