@@ -251,7 +251,7 @@ __device__ __forceinline__ float outlet_collide(const FaceLane<DIM> &L, int r, b
     }
     if (live && (!(rt > 0.0f) || !isfinite(rt) || !isfinite(u[0] + u[1] + u[2]))) *flag = 1;
     float fs = lane_collide<DIM>(L, f, rho, sa, f0, J, u, F, rates);
-    // the rest population is the residual of the density (see collide_pairs)
+    // the rest population is the residual of the density (see collide_pairs2)
     const float moving = lane_sum<DIM>(L.on && !L.rest ? fs : 0.0f);
     if (L.rest) fs = rho - moving;
     if (live && L.on) Codec<STORE>::st(dst + ((int64_t)L.k * Q + L.dir) * g.Ppad + rec.pN, fs, L.w, rd);
