@@ -945,14 +945,32 @@ __device__ __forceinline__ void main_item(const typename Codec<STORE>::T *__rest
                 const uint32_t vo = p * Buf<STORE>::SZ;
                 // reference density of the node that reads population i next
                 // step: the destination x + e_i, or x itself on bounce-back
-                auto dest_psi = [&](auto ic) -> float2 {
+                auto dest_psi = [&](auto inc, auto ic) -> float2 {
                     constexpr int i = decltype(ic)::value;
                     constexpr int ex = Lat<DIM>::E[i][0], ey = Lat<DIM>::E[i][1], ez = Lat<DIM>::E[i][2];
-                    if ((tw >> Lat<DIM>::OPP[i]) & 1u) return ps;
+                    if constexpr (!decltype(inc)::value)
+                        if ((tw >> Lat<DIM>::OPP[i]) & 1u) return ps;
                     if constexpr (DIM == 3) return s_psi[base[2 + ez] + CEN + ey * HX + ex];
                     else return s_psi[base[2 + ey] + CEN + ex];
                 };
                 float fo[Q];
+                // fo of one component to rd.  Waves without bounce-back (most) skip
+                // its test, which costs binary16 three operations a population
+                // (node update of the 300x60x60 device 60.5 -> 58 us, of
+                // 600x120x120 363 -> 357; 2-D, less bound by VALU issue, lost
+                // up to 1%)
+                auto put = [&](__amdgpu_buffer_rsrc_t rd, auto &&ref_of) {
+                    auto all = [&](auto inc) {
+                        static_for<Q>([&](auto ic) {
+                            constexpr int i = decltype(ic)::value;
+                            float rp = 0.0f;
+                            if constexpr (Codec<STORE>::REF) rp = ref_of(inc, ic);
+                            Buf<STORE>::st(rd, vo, plane_bytes<STORE>(g, i), fo[i], weight<DIM>(i), rp);
+                        });
+                    };
+                    if (DIM == 3 && Codec<STORE>::REF && wave_fast) all(std::true_type{});
+                    else all(std::false_type{});
+                };
                 // a moving wall: the populations that bounce back from it take
                 // its momentum, -2 w_j rho_k (e_j . u_w) / cs^2, stored with
                 // them (only this node reads them)
@@ -960,12 +978,7 @@ __device__ __forceinline__ void main_item(const typename Codec<STORE>::T *__rest
                 const Rates ra = {ph.se[0], ph.seps[0], ph.sq, ph.snu[0]};
                 collide_pairs<DIM, STORE == 0>(qa, r1, J1, u, F1, ra, fo);
                 if (cw) static_for<Q>([&](auto ic) { fo[decltype(ic)::value] = fmaf(cw[decltype(ic)::value], r1, fo[decltype(ic)::value]); });
-                static_for<Q>([&](auto ic) {
-                    constexpr int i = decltype(ic)::value;
-                    float rd = 0.0f;
-                    if constexpr (Codec<STORE>::REF) rd = dest_psi(ic).x;
-                    Buf<STORE>::st(rd0, vo, plane_bytes<STORE>(g, i), fo[i], weight<DIM>(i), rd);
-                });
+                put(rd0, [&](auto inc, auto ic) { return dest_psi(inc, ic).x; });
                 if constexpr (!KEEPB) {
                     float f[Q];
                     bgather<DIM, STORE>(rs1, g, p, tw, x, y, z, wave_fast, f, rf.y);
@@ -974,12 +987,7 @@ __device__ __forceinline__ void main_item(const typename Codec<STORE>::T *__rest
                 const Rates rb = {ph.se[1], ph.seps[1], ph.sq, ph.snu[1]};
                 collide_pairs<DIM, STORE == 0>(qb, r2, J2, u, F2, rb, fo);
                 if (cw) static_for<Q>([&](auto ic) { fo[decltype(ic)::value] = fmaf(cw[decltype(ic)::value], r2, fo[decltype(ic)::value]); });
-                static_for<Q>([&](auto ic) {
-                    constexpr int i = decltype(ic)::value;
-                    float rd = 0.0f;
-                    if constexpr (Codec<STORE>::REF) rd = dest_psi(ic).y;
-                    Buf<STORE>::st(rd1, vo, plane_bytes<STORE>(g, i), fo[i], weight<DIM>(i), rd);
-                });
+                put(rd1, [&](auto inc, auto ic) { return dest_psi(inc, ic).y; });
             }
         }
     }
