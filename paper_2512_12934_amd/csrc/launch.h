@@ -51,9 +51,14 @@ constexpr TileCfg CFG3[] = {
     {1, 32, 8, 4, 4, 1},
     {1, 64, 4, 4, 4, 1},
     {1, 32, 8, 2, 2, 1},
-    // one plane per item: domains of some ten thousand nodes (80x16x16: 25.9 us
-    // per step against 31.7 with two planes, 43.6 with four)
+    // one plane per item: up to 250 thousand nodes (80x16x16: 24.1 us per step
+    // against 29.0 with two planes, 38.6 with four; 150x30x30: 34.9, 38.0, 45.1)
     {1, 32, 8, 1, 1, 1},
+    // two planes, 64 wide: FP32 from there on (600x120x120 901 us against 908
+    // with 32x8 and 911 with four planes, 400x90x90 367, 370, 373) and binary16
+    // at some million nodes (above 3M the four planes are better, 634 against
+    // 644)
+    {1, 64, 4, 2, 2, 1},
 };
 constexpr int NCFG2 = sizeof(CFG2) / sizeof(CFG2[0]);
 constexpr int NCFG3 = sizeof(CFG3) / sizeof(CFG3[0]);

@@ -232,7 +232,7 @@ def test_ring_edges(shape, walls, storage):
     dim = 2 if shape[2] == 1 else 3
     c = cases.random_box(shape, seed=sum(shape), dim=dim, periodic=(not walls,) * 3, walls=walls, u_amp=0.01,
                          Gw=(0.05, -0.05) if walls else (0.0, 0.0))
-    for cfg in ((0, 4, 8, 10, 11) if dim == 2 else (6, 7, 8, 9, 10)):
+    for cfg in ((0, 4, 8, 10, 11) if dim == 2 else (6, 7, 8, 9, 10, 11)):
         assert _step_error(c, storage, tile_config=cfg) < TOL[storage]
 
 
