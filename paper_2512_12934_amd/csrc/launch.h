@@ -46,8 +46,9 @@ constexpr TileCfg CFG3[] = {
     {1, 32, 8, 8, 16, 1},
     {0, 32, 8, 4, 16, 1},
     // shallow chunks: four (eight) times the work items of the 16-plane
-    // shapes, so the last wave of blocks leaves fewer CUs idle (the picks for
-    // the co-flow device at full and at quarter scale)
+    // shapes, so the last wave of blocks leaves fewer CUs idle (64x4 is the
+    // pick of the 600x120x120 device in binary16, 32x8 with two planes that of
+    // half a million nodes)
     {1, 32, 8, 4, 4, 1},
     {1, 64, 4, 4, 4, 1},
     {1, 32, 8, 2, 2, 1},

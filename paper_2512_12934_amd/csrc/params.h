@@ -158,7 +158,7 @@ constexpr int xcd_group(int dim, int psrc, bool one_window)
 // turn.  A block's ends share their memory lines with the next block's, which
 // one block per turn fetched into two L2s (binary16, with 64 populations a
 // line, read 1.28 times the populations of the 600x120x120 device, now 1.10;
-// FP32 1.21, now 1.06).  300x60x60 binary16 23.0 -> 20.1 us, 250x51x51 15.7
+// FP32 1.16, now 1.06).  300x60x60 binary16 23.0 -> 20.1 us, 250x51x51 15.7
 // -> 14.1, FP32 and larger domains within 1%; 4 and 64 blocks are no better.
 constexpr int PSI_GROUP = 16;
 
