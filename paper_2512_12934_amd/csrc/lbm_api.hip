@@ -442,12 +442,19 @@ std::string build_maps(const lbm_config *c, Maps &m)
     return "";
 }
 
-// Default node-update configuration: the measured best of the tuning space
-// for the lattice (see the autotuner), entry 0 otherwise.
-int default_cfg(const lbm_config *c)
+// Node-update configuration where the caller names none: by lattice, storage
+// and box nodes, at the sizes where the measured picks change (finer classes
+// in the autotuner's table).  Small domains take few-plane items, whose number
+// keeps the CUs busy; entry 0, sixteen rows or planes an item, was the choice
+// for all.  us per step, entry 0 / here: 64x64 box FP32 15.7 / 5.9, 320x160 17.3 / 7.2,
+// 150x30x30 103.5 / 34.7, 300x60x60 binary16 160 / 94, 600x120x120 FP32 965 / 899.
+int default_cfg(int dim, int storage, int64_t nodes)
 {
-    (void)c;
-    return 0;
+    const bool f32 = storage == LBM_STORE_F32;
+    if (dim == 2) return f32 ? (nodes < 250000 ? 10 : 11) : (nodes < 5000000 ? 10 : (nodes < 16000000 ? 11 : 4));
+    if (nodes < 250000) return 10;
+    if (f32) return 11;
+    return nodes < 1000000 ? 9 : (nodes < 3000000 ? 11 : 8);
 }
 
 // Fills the records' padded indices and the slot tables of the face kernels.
@@ -559,7 +566,7 @@ Layout make_layout(const Canon &k, const Maps &m)
             }
         }
     }
-    L.cfg = c->tile_config >= 0 ? c->tile_config : default_cfg(c);
+    L.cfg = c->tile_config >= 0 ? c->tile_config : default_cfg(c->dim, c->storage, g.N);
     const TileCfg &tc = tile_cfg(c->dim, L.cfg);
     L.psi_mode = tc.psrc;
     if (c->dim == 2) {
@@ -1367,7 +1374,13 @@ std::string batch_plan(const lbm_config *cfgs, int n, std::vector<lbm_config> &m
     if (!cfgs || n < 1 || n > (1 << 20)) return "bad member count";
     mc.assign(cfgs, cfgs + n);
     bytes.assign(n, 0);
-    const int cfg = cfgs[0].tile_config;
+    int cfg = cfgs[0].tile_config;
+    if (cfg == -1) {                                   // one for all members, by their total
+        double nodes = 0;                              // sizes are checked below
+        for (int i = 0; i < n; i++) nodes += (double)cfgs[i].n[0] * cfgs[i].n[1] * (cfgs[i].dim == 3 ? cfgs[i].n[2] : 1);
+        if (cfgs[0].dim == 2 || cfgs[0].dim == 3)
+            cfg = default_cfg(cfgs[0].dim, cfgs[0].storage, (int64_t)std::min(nodes, 1e15));
+    }
     total = 0;
     int64_t items = 0;
     for (int i = 0; i < n; i++) {

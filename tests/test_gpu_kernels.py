@@ -251,6 +251,28 @@ def test_large_domain_order(storage, nz, walls):
     assert np.array_equal(g.get_state(), b.members[0].get_state())
 
 
+@pytest.mark.parametrize("storage", ["f32", "f16", "f16fixed"])
+@pytest.mark.parametrize("shapes", [((20, 30, 1), (500, 500, 1)), ((8, 9, 10), (64, 64, 62))])
+def test_default_tiles(shapes, storage):
+    """No tile configuration named: the pick goes by size, for a batch by its
+    members' total (here another class than its small member's own), and
+    changes no bit of the result."""
+    from paper_2512_12934_amd.lbm import LBM, Batch
+    dim = 2 if shapes[0][2] == 1 else 3
+    cs = [cases.random_box(s, seed=5, dim=dim, periodic=(True,) * 3, walls=False, u_amp=0.01) for s in shapes]
+    print(f"[gpu] default tiles {shapes} {storage}", flush=True)
+    b = Batch(cs, storage=storage, tile_config=-1)
+    b.step(2)
+    for c, m in zip(cs, b.members):
+        got = []
+        for cfg in (-1, 0):
+            g = LBM(c, storage=storage, tile_config=cfg)
+            g.step(2)
+            got.append(g.get_state())
+        assert np.array_equal(got[0], got[1])
+        assert np.array_equal(got[0], m.get_state())
+
+
 @pytest.mark.parametrize("storage", ["f32", "f16"])
 @pytest.mark.parametrize("shape,walls", RINGS)
 def test_moments_edges(shape, walls, storage):
