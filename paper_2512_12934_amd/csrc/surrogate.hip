@@ -355,8 +355,11 @@ __global__ __launch_bounds__(FT) void k_grad(float *__restrict__ params, float *
     if (tile) w2t[(int64_t)m * H * H + (p - O_W2) % H * H + (p - O_W2) / H] = nw;
 }
 
-// W2 of every member transposed, as the forward product of training reads it
-// (k_grad keeps it up to date)
+// W2 of every member transposed, as the forward product of training reads it.
+// It follows every change of the weights on the context's stream (surr_create,
+// surr_set_params, and k_grad at each update): nothing on the host remembers
+// whether it does, so a gradient pass that the caller captured reads the
+// weights of its replay, not those of its capture.
 __global__ void k_w2_transpose(const float *__restrict__ params, int members, float *__restrict__ w2t)
 {
     const int64_t t = (int64_t)blockIdx.x * 256 + threadIdx.x;
@@ -500,7 +503,6 @@ struct surr_ctx {
     uint16_t *w2 = nullptr;
     int64_t adam_t = 0;
     bool w2_fresh = false;     // w2 holds the current weights
-    bool w2t_fresh = false;    // w2t does
     std::string err;
 };
 
@@ -554,16 +556,20 @@ bool args_ok(int members, int hidden, int max_n)
     return members >= 1 && members <= 64 && hidden == H && max_n >= 1 && max_n <= (1 << 22);
 }
 
+// the copies of W2 that kernels read, from the parameters
+lbm_status derive_w2(surr_ctx *c)
+{
+    const int64_t ne = (int64_t)c->members * H * H;
+    hipLaunchKernelGGL(k_w2_transpose, dim3((unsigned)((ne + 255) / 256)), dim3(256), 0, c->stream, c->params,
+                       c->members, c->w2t);
+    SHIPCHECK(c, hipGetLastError());
+    return LBM_OK;
+}
+
 // forward + backward over n samples; gradients summed (and copied to gout if
 // given), Adam step if update
 lbm_status pass(surr_ctx *c, const float *X, const float *Y, int n, float lr, bool update, float *gout)
 {
-    if (!c->w2t_fresh) {
-        const int64_t ne = (int64_t)c->members * H * H;
-        hipLaunchKernelGGL(k_w2_transpose, dim3((unsigned)((ne + 255) / 256)), dim3(256), 0, c->stream, c->params,
-                           c->members, c->w2t);
-        c->w2t_fresh = true;
-    }
     Adam ad{lr, 0.9f, 0.999f, 1e-8f, 1.0f, 1.0f};
     if (update) {
         c->adam_t++;
@@ -622,7 +628,7 @@ lbm_status surr_create(int members, int hidden, int max_n, uint64_t seed, void *
     const int64_t np = (int64_t)members * P;
     hipLaunchKernelGGL(k_init, dim3((unsigned)((np + 255) / 256)), dim3(256), 0, c->stream, c->params, c->am, c->av,
                        members, seed);
-    if (hipGetLastError() != hipSuccess || hipStreamSynchronize(c->stream) != hipSuccess) {
+    if (hipGetLastError() != hipSuccess || derive_w2(c) != LBM_OK || hipStreamSynchronize(c->stream) != hipSuccess) {
         delete c;
         return sfail(nullptr, LBM_EDEVICE, "initialisation failed");
     }
@@ -690,9 +696,10 @@ lbm_status surr_set_params(surr_ctx *c, const float *host, size_t bytes)
 {
     if (!c || !host || bytes != (size_t)c->members * P * 4) return sfail(c, LBM_EINVAL, "bad arguments to surr_set_params");
     SHIPCHECK(c, hipMemcpyAsync(c->params, host, bytes, hipMemcpyHostToDevice, c->stream));
+    const lbm_status st = derive_w2(c);
+    if (st != LBM_OK) return st;
     SHIPCHECK(c, hipStreamSynchronize(c->stream));
     c->w2_fresh = false;
-    c->w2t_fresh = false;
     return LBM_OK;
 }
 

@@ -117,3 +117,57 @@ def test_surrogate_gain_over_lbm():
     assert kept >= 4
     assert h["mape_kept"][0] < 0.08 and h["mape_kept"][1] < 0.12
     assert h["mape_kept"][0] <= h["mape_all"][0] + 1e-12 and h["mape_kept"][1] <= h["mape_all"][1] + 1e-12
+
+
+def _captured(s, call):
+    """``call`` enqueued into a torch graph on the ensemble's stream."""
+    import torch
+    g = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(g, stream=s.stream):
+        call()
+    return g
+
+
+@pytest.mark.parametrize("eager_first", [True, False])
+def test_captured_gradient_reads_the_weights_of_its_replay(eager_first):
+    """A gradient pass that the caller captured, with or without an eager pass
+    before the capture, gives the bits of an eager pass over the weights that
+    the ensemble holds at each replay: those put in from outside and those an
+    eager update left."""
+    import torch
+    from paper_2512_12934_amd.lbm import lib
+    from paper_2512_12934_amd.surrogate import Surrogate
+    print(f"[gpu] captured gradient, eager_first={eager_first}", flush=True)
+    X, Y = _data(100, 6)
+    Xd, Yd = torch.from_numpy(X).cuda(), torch.from_numpy(Y).cuda()
+    s = Surrogate(members=2, max_n=100, seed=1, stream=torch.cuda.Stream())
+    ref = Surrogate(members=2, max_n=100, seed=2)
+    grad, loss = torch.zeros((2, s.P), device="cuda:0"), torch.zeros(2, device="cuda:0")
+
+    def enqueue():
+        s._check(lib().surr_forward_backward(s._h, Xd.data_ptr(), Yd.data_ptr(), 100, grad.data_ptr(),
+                                             loss.data_ptr()))
+
+    def result():
+        torch.cuda.synchronize()
+        out = grad.cpu().numpy(), loss.cpu().numpy()
+        grad.zero_()
+        loss.zero_()
+        torch.cuda.synchronize()
+        return out
+
+    if eager_first:
+        enqueue()
+    result()
+    g = _captured(s, enqueue)
+    for r in range(3):
+        ref.set_params(s.get_params())
+        want = ref.forward_backward(X, Y)
+        # eager passes between the replays, the first after or before the first
+        for call in (g.replay, enqueue) if eager_first else (enqueue, g.replay):
+            call()
+            assert all(np.array_equal(a, b) for a, b in zip(want, result())), r
+        if r == 0:
+            s.set_params(Surrogate(members=2, max_n=16, seed=9).get_params())
+        else:
+            s.train(X, Y, epochs=3, lr=1e-2)
