@@ -738,6 +738,17 @@ __global__ __launch_bounds__(256) void k_lab_order(const CompStat *__restrict__ 
 // back (a copy into pageable memory costs a second staging step).
 constexpr size_t PIN_BYTES = 1024;
 
+// hipHostFree, allowed while any stream of the process is being captured: in
+// the default capture modes it is a forbidden call, and a context that is
+// released in the middle of somebody's capture would break that capture.
+void free_pinned(void *p)
+{
+    hipStreamCaptureMode mode = hipStreamCaptureModeRelaxed;
+    (void)hipThreadExchangeStreamCaptureMode(&mode);
+    (void)hipHostFree(p);
+    (void)hipThreadExchangeStreamCaptureMode(&mode);
+}
+
 }  // namespace
 
 struct lbm_ctx {
@@ -766,7 +777,7 @@ struct lbm_ctx {
         for (auto &g : gx)
             if (g) (void)hipGraphExecDestroy(g);
         if (cap) (void)hipStreamDestroy(cap);
-        if (own_pin) (void)hipHostFree(pin);
+        if (own_pin) free_pinned(pin);
     }
     void *fsrc() const { return ws + (cur == 0 ? L.o_fA : L.o_fB); }
     void *fdst() const { return ws + (cur == 0 ? L.o_fB : L.o_fA); }
@@ -1344,7 +1355,7 @@ struct lbm_batch {
             if (g) (void)hipGraphExecDestroy(g);
         if (cap) (void)hipStreamDestroy(cap);
         for (auto *c : m) delete c;
-        if (pin) (void)hipHostFree(pin);
+        if (pin) free_pinned(pin);
     }
 };
 

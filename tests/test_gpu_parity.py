@@ -367,3 +367,30 @@ def test_couette_steady_state(dim):
     err = np.abs(prof[1:-1] - ua[1:-1]).max()
     print(f"  Couette max |u - u_exact| {err:.2e}", flush=True)
     assert err < 1e-6
+
+
+@pytest.mark.parametrize("mode", ["thread_local", "global"])
+@pytest.mark.parametrize("kind", ["context", "batch"])
+def test_release_during_a_capture(kind, mode):
+    """A context or batch released while another context's steps are being
+    captured leaves that capture whole: its replays give the eager bits."""
+    import torch
+    from paper_2512_12934_amd.lbm import LBM, Batch
+    c = cases.random_box((20, 17, 1), seed=2)
+    print(f"[gpu] release of a {kind} during a {mode} capture", flush=True)
+    a, b = LBM(c, stream=torch.cuda.Stream()), LBM(c)
+    other = LBM(c) if kind == "context" else Batch([c, c])
+    for s in (a, b):
+        s.set_graph_steps(0)
+        s.step(2)
+    other.step(2)
+    torch.cuda.synchronize()
+    g = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(g, stream=a.stream, capture_error_mode=mode):
+        a.step(2)
+        other.close()
+    for r in range(3):
+        g.replay()
+        torch.cuda.synchronize()
+        b.step(2)
+        assert np.array_equal(a.get_state(), b.get_state()), r
