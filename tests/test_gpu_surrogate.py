@@ -171,3 +171,47 @@ def test_captured_gradient_reads_the_weights_of_its_replay(eager_first):
             s.set_params(Surrogate(members=2, max_n=16, seed=9).get_params())
         else:
             s.train(X, Y, epochs=3, lr=1e-2)
+
+
+@pytest.mark.parametrize("eager_first", [True, False])
+def test_captured_prediction_reads_the_weights_of_its_replay(eager_first):
+    """The same for a prediction: the bits of an eager prediction by the
+    weights that the ensemble holds at each replay."""
+    import torch
+    from paper_2512_12934_amd.lbm import lib
+    from paper_2512_12934_amd.surrogate import Surrogate
+    print(f"[gpu] captured prediction, eager_first={eager_first}", flush=True)
+    X, Y = _data(100, 6)
+    Xd = torch.from_numpy(X).cuda()
+    s = Surrogate(members=6, max_n=100, seed=1, stream=torch.cuda.Stream())
+    ref = Surrogate(members=6, max_n=100, seed=2)
+    mean, sd = torch.zeros((100, 2), device="cuda:0"), torch.zeros((100, 2), device="cuda:0")
+    fb = torch.zeros(100, dtype=torch.uint8, device="cuda:0")
+
+    def enqueue():
+        s._check(lib().surr_predict(s._h, Xd.data_ptr(), 100, mean.data_ptr(), sd.data_ptr(), fb.data_ptr(), 0.05,
+                                    None, None))
+
+    def result():
+        torch.cuda.synchronize()
+        out = [t.cpu().numpy() for t in (mean, sd, fb)]
+        for t in (mean, sd, fb):
+            t.zero_()
+        torch.cuda.synchronize()
+        return out
+
+    if eager_first:
+        enqueue()
+    result()
+    g = _captured(s, enqueue)
+    for r in range(3):
+        ref.set_params(s.get_params())
+        want = [t.cpu().numpy() for t in ref.predict(X, threshold=0.05)]
+        # eager predictions between the replays, the first after or before the first
+        for call in (g.replay, enqueue) if eager_first else (enqueue, g.replay):
+            call()
+            assert all(np.array_equal(a, b) for a, b in zip(want, result())), r
+        if r == 0:
+            s.set_params(Surrogate(members=6, max_n=16, seed=9).get_params())
+        else:
+            s.train(X, Y, epochs=3, lr=1e-2)
