@@ -184,10 +184,12 @@ template <int DIM>
 void Launcher<DIM>::probe(int storage, const StepArgs &a, int k, const Box3 &bx, float thr, unsigned long long *out)
 {
     const int64_t vol = (int64_t)(bx.hi[0] - bx.lo[0]) * (bx.hi[1] - bx.lo[1]) * (bx.hi[2] - bx.lo[2]);
-    // a cross-section of a channel (hundreds of nodes, the usual probe) is a
-    // few passes of one block, less than the launch that would clear the
-    // count for many blocks; from PROBE_ONE nodes on the passes cost more
-    constexpr int64_t PROBE_ONE = 2048;
+    // One block that writes the count saves the launch that clears it for many
+    // blocks, and pays a memory round trip for every pass over the box but its
+    // first: 1.6 us in 2-D, 3.3 to 7 in 3-D.  us per probe, one block / two
+    // launches: 2-D 512 nodes 5.4 / 8.3, 1024 nodes 8.3 / 8.2; 3-D 256 nodes
+    // 5.6 / 8.1, 512 nodes 8.8 / 8.4, 2048 nodes 30 to 55 / 8.3.
+    constexpr int64_t PROBE_ONE = DIM == 3 ? 256 : 512;
     const bool one = vol <= PROBE_ONE;
     if (!one) hipLaunchKernelGGL(k_zero64, dim3(1), dim3(1), 0, a.stream, out);
     const unsigned nb = one ? 1u : (unsigned)((vol + 255) / 256);
