@@ -1560,8 +1560,14 @@ static __global__ __launch_bounds__(256) void k_lab_roots(Box3 bx, int *lab, int
 // Sizes, first nodes and bounding boxes.  A wave takes a strip of 64 nodes in
 // x and LAB_ROWS consecutive rows, and adds what it holds of one component to
 // its record at once (integer atomics: the result does not depend on their
-// order).
-constexpr int LAB_ROWS = 4;
+// order), for up to LAB_TURNS components.  A wave that holds more (specks,
+// thin stripes) has few nodes of each: its lanes then add what each of them
+// holds, side by side (the 128 components a wave holds of a checkerboard,
+// reduced in turn, took about 100 us: 8192 components 280 us a call, now 177).
+constexpr int LAB_ROWS = 4, LAB_TURNS = 8;
+struct LabPart {
+    int first, lo[3], hi[3];
+};
 __device__ __forceinline__ int wave_min(int v)
 {
 #pragma unroll
@@ -1586,42 +1592,60 @@ static __global__ __launch_bounds__(256) void k_lab_stats(Geometry g, Box3 bx, c
         sl[i] = l >= 0 ? slot[l] : -1;
         if (sl[i] >= cap) sl[i] = -1;
     }
-    while (true) {
-        // the next component: the first one a lane still holds
-        int mine = -1;
+    // the first component this lane still holds, or -1
+    auto next = [&] {
+        int s = -1;
 #pragma unroll
-        for (int i = LAB_ROWS - 1; i >= 0; i--) mine = sl[i] >= 0 ? sl[i] : mine;
+        for (int i = LAB_ROWS - 1; i >= 0; i--) s = sl[i] >= 0 ? sl[i] : s;
+        return s;
+    };
+    // takes the lane's nodes of component s: how many, and their extent
+    auto take = [&](int s, LabPart &p) {
+        p = {0x7fffffff, {0x7fffffff, 0x7fffffff, 0x7fffffff}, {-1, -1, -1}};
+        int n = 0;
+#pragma unroll
+        for (int i = 0; i < LAB_ROWS; i++) {
+            if (sl[i] != s) continue;
+            sl[i] = -1;
+            n++;
+            const int row = row0 + i, zz = row / ey, mc[3] = {bx.lo[0] + x, bx.lo[1] + row - zz * ey, bx.lo[2] + zz};
+            p.first = min(p.first, (int)caller_index(g, mc[0], mc[1], mc[2]));
+            for (int a = 0; a < 3; a++) {
+                p.lo[a] = min(p.lo[a], mc[a]);
+                p.hi[a] = max(p.hi[a], mc[a] + 1);
+            }
+        }
+        return n;
+    };
+    auto add = [&](int s, int size, const LabPart &p) {
+        CompStat *c = st + s;
+        atomicAdd(&c->size, (unsigned long long)size);
+        atomicMin(&c->first, (unsigned long long)p.first);
+        for (int a = 0; a < 3; a++) {
+            atomicMin(&c->lo[g.ax[a]], p.lo[a]);
+            atomicMax(&c->hi[g.ax[a]], p.hi[a]);
+        }
+    };
+    LabPart p;
+    for (int turn = 0; turn < LAB_TURNS; turn++) {
+        const int mine = next();
         const unsigned long long have = __ballot(mine >= 0);
         if (!have) return;
         const int s = __shfl(mine, __ffsll((long long)have) - 1, 64);
-        int size = 0, first = 0x7fffffff, lo[3] = {0x7fffffff, 0x7fffffff, 0x7fffffff}, hi[3] = {-1, -1, -1};
+        int size = 0;
 #pragma unroll
-        for (int i = 0; i < LAB_ROWS; i++) {
-            const bool hit = sl[i] == s;
-            size += __popcll(__ballot(hit));
-            if (!hit) continue;
-            sl[i] = -1;
-            const int row = row0 + i, zz = row / ey, mc[3] = {bx.lo[0] + x, bx.lo[1] + row - zz * ey, bx.lo[2] + zz};
-            first = min(first, (int)caller_index(g, mc[0], mc[1], mc[2]));
-            for (int a = 0; a < 3; a++) {
-                lo[a] = min(lo[a], mc[a]);
-                hi[a] = max(hi[a], mc[a] + 1);
-            }
-        }
-        first = wave_min(first);
+        for (int i = 0; i < LAB_ROWS; i++) size += __popcll(__ballot(sl[i] == s));
+        take(s, p);
+        p.first = wave_min(p.first);
         for (int a = 0; a < 3; a++) {
-            lo[a] = wave_min(lo[a]);
-            hi[a] = -wave_min(-hi[a]);
+            p.lo[a] = wave_min(p.lo[a]);
+            p.hi[a] = -wave_min(-p.hi[a]);
         }
-        if (lane == 0) {
-            CompStat *c = st + s;
-            atomicAdd(&c->size, (unsigned long long)size);
-            atomicMin(&c->first, (unsigned long long)first);
-            for (int a = 0; a < 3; a++) {
-                atomicMin(&c->lo[g.ax[a]], lo[a]);
-                atomicMax(&c->hi[g.ax[a]], hi[a]);
-            }
-        }
+        if (lane == 0) add(s, size, p);
+    }
+    for (int s = next(); s >= 0; s = next()) {
+        const int n = take(s, p);
+        add(s, n, p);
     }
 }
 

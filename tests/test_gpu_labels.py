@@ -179,3 +179,35 @@ def test_probe_of_any_box(shape):
         cost[ex, ey, ez] = 1e4 * min(times)
     print("[gpu] us per probe", {k: round(v, 1) for k, v in cost.items()}, flush=True)
     assert max(cost.values()) < 1.4 * cost[64, 64, 1]
+
+
+def test_many_components():
+    """Checkerboards of 32 to 8192 components, a domain's corner of them, and
+    a full output or a short one: the records equal a CPU labelling, through
+    both entry points, and 2048 components cost at most three times what 32 do
+    (the same launches over a few thousand nodes).  Each time is the least of
+    twenty calls."""
+    import time
+    from paper_2512_12934_amd.lbm import LBM
+    cost = {}
+    for n in (8, 64, 90, 91, 128):
+        y, x = np.meshgrid(np.arange(n), np.arange(n), indexing="ij")
+        rho = np.where(((x + y) % 2 == 0).reshape(-1), 1.0, 0.2)
+        c = cases.Case("checker", 2, (n, n, 1), (True, True, True), (0.1, 0.1), 0.9, solid=np.zeros(n * n, np.uint8),
+                       rho0=np.stack([rho, 1.2 - rho]))
+        g = LBM(c)
+        ref = [{"first": j * n + i, "size": 1, "lo": (i, j, 0), "hi": (i + 1, j + 1, 1)}
+               for j in range(n) for i in range(n) if (i + j) % 2 == 0]
+        for static in ([False, True] if len(ref) <= 4096 else [False]):
+            assert g.components(0, (0, 0, 0), c.n, 0.6, max_out=len(ref), static=static) == (ref, len(ref))
+            part, count = g.components(0, (0, 0, 0), c.n, 0.6, max_out=30, static=static)
+            assert part == ref[:30] and count == len(ref)
+            times = []
+            for _ in range(20):
+                t0 = time.perf_counter()
+                g.components(0, (0, 0, 0), c.n, 0.6, max_out=16, static=static)
+                times.append(time.perf_counter() - t0)
+            cost[len(ref), static] = 1e6 * min(times)
+    print("[gpu] us per call", {k: round(v, 1) for k, v in cost.items()}, flush=True)
+    for static in (False, True):
+        assert cost[2048, static] < 3.0 * cost[32, static]
