@@ -12,6 +12,8 @@ storage and size class.  ``LBM(..., tile_config="auto")`` reads that table.
 from __future__ import annotations
 
 import argparse
+import copy
+import functools
 import json
 import os
 import sys
@@ -39,17 +41,30 @@ def key(dim: int, storage: str, nodes: int) -> str:
     return f"d{dim}-{storage}-{size_class(nodes)}"
 
 
+@functools.lru_cache(maxsize=1)
+def _parse(path: str, stamp: tuple) -> dict:
+    with open(path) as fh:
+        return json.load(fh)
+
+
+def _table() -> dict:
+    # every context that asks for a tuned tile looks it up: the file is parsed
+    # once per version of it (0.16 ms, a quarter of what the smallest context
+    # takes to create)
+    if not os.path.exists(TABLE):
+        return {}
+    st = os.stat(TABLE)
+    return _parse(TABLE, (st.st_mtime_ns, st.st_size, st.st_ino))
+
+
 def load_table() -> dict:
-    if os.path.exists(TABLE):
-        with open(TABLE) as fh:
-            return json.load(fh)
-    return {}
+    return copy.deepcopy(_table())
 
 
 def lookup(dim: int, storage: str, nodes: int) -> int:
     # both binary16 codecs move the same bytes: the fixed-offset form takes
     # the reference-density form's tuning
-    entry = load_table().get(key(dim, "f16" if storage == "f16fixed" else storage, nodes))
+    entry = _table().get(key(dim, "f16" if storage == "f16fixed" else storage, nodes))
     return int(entry["best"]) if entry else -1
 
 
