@@ -109,10 +109,12 @@ def tune(case, storage: str, steps: int, warmup: int, log=print) -> dict:
 WORKLOADS = {
     "taylor": lambda c: c.taylor(5.0, 0.05, nx=320, H=160, R=32.0),
     "tjunction": lambda c: c.tjunction(),
+    "tjunction_small": lambda c: c.tjunction(W=32, length=256, x_side=48, side_width=32, side_len=32),
     "droplet_900": lambda c: c.laplace(n=900, R=225.0),
     "tjunction_W256": lambda c: c.sweep_case(256, 0.03, 0.5, 1.0),
     # the sweep geometry at W = 512 (2.4M fluid nodes)
     "tjunction_W512": lambda c: c.sweep_case(512, 0.03, 0.5, 1.0),
+    "tjunction_large": lambda c: c.sweep_case(512, 0.01, 0.5, 1.0),
     "coflow3d_80": lambda c: c.coflow3d(length=80, width=16, inner=4),
     "coflow3d_quarter": lambda c: c.coflow3d_quarter(),
     "coflow3d_200": lambda c: c.coflow3d(length=200, width=40, inner=10),
