@@ -4,10 +4,15 @@ Every configuration of the tuning space (lattice-specific tile shape, sweep
 depth, psi source, register policy; see ``csrc/launch.h``) computes exactly
 the same arithmetic per node, so the tuner runs each one on a workload,
 checks that the state after the timed steps is bitwise equal to that of
-configuration 0, and records the fastest in ``tuning.json`` keyed by lattice,
-storage and size class.  ``LBM(..., tile_config="auto")`` reads that table.
+configuration 0, and records its pick (see ``pick``) in ``tuning.json`` keyed
+by lattice, storage and size class.  ``LBM(..., tile_config="auto")`` reads
+that table; a class it does not hold takes the library's own choice, which
+knows fewer classes.
 
     python -m paper_2512_12934_amd.autotune --workload coflow3d --steps 50
+
+    # the table
+    python -m paper_2512_12934_amd.autotune --workload table --steps 64 --write
 """
 from __future__ import annotations
 
@@ -68,44 +73,67 @@ def lookup(dim: int, storage: str, nodes: int) -> int:
     return int(entry["best"]) if entry else -1
 
 
-def tune(case, storage: str, steps: int, warmup: int, log=print) -> dict:
+def pick(times: dict, identical: dict, prefer=None):
+    """The fastest configuration whose state equals that of configuration 0.
+    Times within 2% count as equal (what runs of one configuration differ by on
+    one device), and of equals ``prefer``, the pick of the next larger size
+    class, is kept, so that the picks change with the size only where it gains."""
+    good = {c: t for c, t in times.items() if identical[c]}
+    best = min(good, key=good.get)
+    return prefer if prefer in good and good[prefer] <= 1.02 * good[best] else best
+
+
+def larger_class(dim: int, storage: str, nodes: int):
+    """Key of the next larger size class, or None for the largest."""
+    names = [name for _, name in CLASSES] + ["max"]
+    i = names.index(size_class(nodes)) + 1
+    return f"d{dim}-{storage}-{names[i]}" if i < len(names) else None
+
+
+def tune(work, storage: str, steps: int, warmup: int, prefer=None, log=print) -> dict:
+    """``work``: a case, or a list of them to be stepped as one batch."""
     import numpy as np
     import torch
 
-    from .lbm import LBM, tile_configs
+    from .lbm import LBM, Batch, tile_configs
 
+    batch = isinstance(work, list)
+    members = work if batch else [work]
+    name = f"batch of {len(work)} {work[0].name.split('_')[0]} members" if batch else f"{work.name} {work.n}"
     times, ok = {}, {}
     ref = None
-    for cfg in range(tile_configs(case.dim)):
-        sim = LBM(case, storage=storage, tile_config=cfg)
+    for cfg in range(tile_configs(members[0].dim)):
+        sim = (Batch if batch else LBM)(work, storage=storage, tile_config=cfg)
         # capture both step graphs before timing, so no configuration's time
         # includes a capture
         sim.set_graph_steps(16)
         sim.step(warmup)
-        torch.cuda.synchronize()
-        t0, t1 = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
-        t0.record(sim.stream)
-        sim.step(steps)
-        t1.record(sim.stream)
-        torch.cuda.synchronize()
-        ms = t0.elapsed_time(t1) / steps
-        state = sim.get_state() if case.N <= 4_000_000 else sim.moments()[0]
+        ms = float("inf")
+        for _ in range(3):
+            torch.cuda.synchronize()
+            t0, t1 = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+            t0.record(sim.stream)
+            sim.step(steps)
+            t1.record(sim.stream)
+            torch.cuda.synchronize()
+            ms = min(ms, t0.elapsed_time(t1) / steps)
+        # the first, middle and last member of a batch; of a large domain the densities
+        seen = sorted({0, len(members) // 2, len(members) - 1})
+        ctx = [sim.members[i] for i in seen] if batch else [sim]
+        state = [s.get_state() if s.N <= 4_000_000 else s.moments()[0] for s in ctx]
         if ref is None:
             ref = state
-        ok[cfg] = bool(np.array_equal(state, ref))
-        times[cfg] = ms
-        diff = float(np.abs(state - ref).max())
-        log(f"[autotune] {case.name} {storage} cfg {cfg}: {ms:.4f} ms/step, identical={ok[cfg]} max|diff|={diff:.3e}")
-        del sim
+        ok[cfg] = all(np.array_equal(a, b) for a, b in zip(state, ref))
+        times[cfg] = round(ms, 5)
+        diff = max(float(np.abs(a - b).max()) for a, b in zip(state, ref))
+        log(f"[autotune] {name} {storage} cfg {cfg}: {ms:.4f} ms/step, identical={ok[cfg]} max|diff|={diff:.3e}")
+        del sim, ctx
         torch.cuda.empty_cache()
-    good = [c for c in times if ok[c]]
-    best = min(good, key=lambda c: times[c])
-    return {"best": best, "ms_per_step": times, "identical": ok, "steps": steps,
-            "workload": f"{case.name} {case.n}", "fluid_nodes": case.fluid_nodes}
+    return {"best": pick(times, ok, prefer), "ms_per_step": times, "identical": ok, "steps": steps, "workload": name,
+            "fluid_nodes": sum(c.fluid_nodes for c in members)}
 
 
-# One workload per size class and lattice (those of "max" need a batch or a
-# domain beyond one context in 3-D and keep the largest class's pick).
+# Workloads by name: a case, or a list of cases for a batch.
 WORKLOADS = {
     "taylor": lambda c: c.taylor(5.0, 0.05, nx=320, H=160, R=32.0),
     "tjunction": lambda c: c.tjunction(),
@@ -115,18 +143,29 @@ WORKLOADS = {
     # the sweep geometry at W = 512 (2.4M fluid nodes)
     "tjunction_W512": lambda c: c.sweep_case(512, 0.03, 0.5, 1.0),
     "tjunction_large": lambda c: c.sweep_case(512, 0.01, 0.5, 1.0),
+    # the batched sweep, and a quarter of it
+    "sweep_64": lambda c: c.sweep(64),
+    "sweep_256": lambda c: c.sweep(256),
     "coflow3d_80": lambda c: c.coflow3d(length=80, width=16, inner=4),
     "coflow3d_quarter": lambda c: c.coflow3d_quarter(),
     "coflow3d_200": lambda c: c.coflow3d(length=200, width=40, inner=10),
+    "channel3d_250": lambda c: c.channel(250, 51, 0.02, nu=(0.17, 0.17), droplet=(45.0, 26.0, 26.0, 15), dim=3,
+                                         major=c.COEX_G09[0], minor=c.COEX_G09[1]),
     "coflow3d_half": lambda c: c.coflow3d(length=300, width=60, inner=15),
     "coflow3d_400": lambda c: c.coflow3d(length=400, width=90, inner=20),
     "coflow3d": lambda c: c.coflow3d(),
 }
+# The one that stands for each size class of the table, larger classes first
+# (a pick depends on the next larger one's).  3-D domains beyond 16M nodes have
+# none and take the library's choice.
+TABLE_WORKLOADS = ("sweep_256", "sweep_64", "tjunction_W512", "tjunction_W256", "droplet_900", "tjunction", "taylor",
+                   "coflow3d", "coflow3d_400", "coflow3d_half", "channel3d_250", "coflow3d_quarter", "coflow3d_80")
 
 
 def main(argv=None):
     ap = argparse.ArgumentParser()
-    ap.add_argument("--workload", choices=sorted(WORKLOADS), default="coflow3d")
+    ap.add_argument("--workload", choices=sorted(WORKLOADS) + ["table"], default="coflow3d",
+                    help="table: every workload of the table, in place of what it holds")
     ap.add_argument("--storage", choices=["f32", "f16", "both"], default="both")
     ap.add_argument("--steps", type=int, default=50)
     ap.add_argument("--warmup", type=int, default=5)
@@ -134,13 +173,20 @@ def main(argv=None):
     args = ap.parse_args(argv)
     sys.path.insert(0, os.path.dirname(HERE))
     from . import cases
-    case = WORKLOADS[args.workload](cases)
-    table = load_table()
-    for storage in (["f32", "f16"] if args.storage == "both" else [args.storage]):
-        res = tune(case, storage, args.steps, args.warmup, log=lambda m: print(m, flush=True))
-        k = key(case.dim, storage, case.N)
-        print(json.dumps({k: res}), flush=True)
-        table[k] = res
+    whole = args.workload == "table"
+    storages = ["f32", "f16"] if args.storage == "both" else [args.storage]
+    table = {k: v for k, v in load_table().items() if not (whole and k.split("-")[1] in storages)}
+    for name in TABLE_WORKLOADS if whole else [args.workload]:
+        work = WORKLOADS[name](cases)
+        members = work if isinstance(work, list) else [work]
+        dim, nodes = members[0].dim, sum(c.N for c in members)
+        for storage in storages:
+            above = table.get(larger_class(dim, storage, nodes))
+            res = tune(work, storage, args.steps, args.warmup, prefer=above and int(above["best"]),
+                       log=lambda m: print(m, flush=True))
+            k = key(dim, storage, nodes)
+            print(json.dumps({k: res}), flush=True)
+            table[k] = res
     if args.write:
         with open(TABLE, "w") as fh:
             json.dump(table, fh, indent=1, sort_keys=True)

@@ -33,8 +33,8 @@ constexpr TileCfg CFG2[] = {
     {1, 64, 1, 4, 8, 1},
     {0, 32, 1, 8, 8, 1},
     // one window, 64 wide, two nodes per thread: FP32 from a quarter million
-    // nodes on (4096x1026 T-junction 106 us per step, against 116 with 64x16 in
-    // four windows, 121 with 32x8, 114 with 32x16)
+    // nodes on (4096x1026 T-junction 106 us per step, against 115 with 64x16 in
+    // four windows, 120 with 32x8, 114 with 32x16)
     {0, 64, 1, 8, 8, 1},
 };
 constexpr TileCfg CFG3[] = {
@@ -47,18 +47,17 @@ constexpr TileCfg CFG3[] = {
     {0, 32, 8, 4, 16, 1},
     // shallow chunks: four (eight) times the work items of the 16-plane
     // shapes, so the last wave of blocks leaves fewer CUs idle (64x4 is the
-    // pick of the 600x120x120 device in binary16, 32x8 with two planes that of
-    // half a million nodes)
+    // binary16 pick from 3M nodes on)
     {1, 32, 8, 4, 4, 1},
     {1, 64, 4, 4, 4, 1},
     {1, 32, 8, 2, 2, 1},
-    // one plane per item: up to 250 thousand nodes (80x16x16: 24.1 us per step
-    // against 29.0 with two planes, 38.6 with four; 150x30x30: 34.9, 38.0, 45.1)
+    // one plane per item: up to 250 thousand nodes (80x16x16: 24.3 us per step
+    // against 29.2 with two planes, 38.5 with four; 150x30x30: 35.7, 38.1, 45.3)
     {1, 32, 8, 1, 1, 1},
-    // two planes, 64 wide: FP32 from there on (600x120x120 901 us against 908
-    // with 32x8 and 911 with four planes, 400x90x90 367, 370, 373) and binary16
-    // at some million nodes (above 3M the four planes are better, 634 against
-    // 644)
+    // two planes, 64 wide: FP32 from there on (600x120x120 896 us against 905
+    // with 32x8 and 908 with four planes, 400x90x90 364, 368, 371) and binary16
+    // up to 3M nodes (250x51x51 69.5, 70.1, 71.4; above, the four planes are
+    // better, 634 against 641)
     {1, 64, 4, 2, 2, 1},
 };
 constexpr int NCFG2 = sizeof(CFG2) / sizeof(CFG2[0]);

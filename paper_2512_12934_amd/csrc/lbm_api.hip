@@ -443,18 +443,19 @@ std::string build_maps(const lbm_config *c, Maps &m)
 }
 
 // Node-update configuration where the caller names none: by lattice, storage
-// and box nodes, at the sizes where the measured picks change (finer classes
-// in the autotuner's table).  Small domains take few-plane items, whose number
-// keeps the CUs busy; entry 0, sixteen rows or planes an item, was the choice
-// for all.  us per step, entry 0 / here: 64x64 box FP32 15.7 / 5.9, 320x160 17.3 / 7.2,
-// 150x30x30 103.5 / 34.7, 300x60x60 binary16 160 / 94, 600x120x120 FP32 965 / 899.
+// and box nodes, the autotuner's picks (its table has a class per line drawn
+// here and some between; beyond 16M nodes in 3-D it has none).  Small domains
+// take few-plane items, whose number keeps the CUs busy; entry 0, sixteen rows
+// or planes an item, was the choice for all.  us per step, entry 0 / here:
+// 64x64 box FP32 15.7 / 5.9, 320x160 17.4 / 7.5, 150x30x30 103 / 35.7,
+// 250x51x51 binary16 149 / 69.5 (32x8 with two planes 70.1), 300x60x60
+// binary16 160 / 94, 600x120x120 FP32 963 / 896.
 int default_cfg(int dim, int storage, int64_t nodes)
 {
     const bool f32 = storage == LBM_STORE_F32;
     if (dim == 2) return f32 ? (nodes < 250000 ? 10 : 11) : (nodes < 5000000 ? 10 : (nodes < 16000000 ? 11 : 4));
     if (nodes < 250000) return 10;
-    if (f32) return 11;
-    return nodes < 1000000 ? 9 : (nodes < 3000000 ? 11 : 8);
+    return f32 || nodes < 3000000 ? 11 : 8;
 }
 
 // Fills the records' padded indices and the slot tables of the face kernels.

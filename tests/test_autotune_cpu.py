@@ -39,3 +39,41 @@ def test_workloads_of_earlier_calls_are_accepted(monkeypatch):
         autotune.main(["--workload", name, "--storage", "f32"])
         got = seen.pop()
         assert got.n == c.n and got.nu == c.nu and (got.solid == c.solid).all(), name
+
+
+def test_table_is_what_the_tuner_makes():
+    """Every entry of the committed table belongs to one workload of the
+    tuner, holds a time of every configuration, all of them with the bits of
+    configuration 0, and its pick is the tuner's rule applied to its times."""
+    from paper_2512_12934_amd import cases
+    sources = open(os.path.join(autotune.HERE, "csrc", "launch.h")).read()
+    n_cfg = {d: sources[sources.index(f"constexpr TileCfg CFG{d}[]"):].split("};")[0].count("\n    {") for d in (2, 3)}
+    assert n_cfg[2] >= 12 and n_cfg[3] >= 12
+    table = autotune.load_table()
+    stood_for = {}
+    for name in autotune.TABLE_WORKLOADS:
+        work = autotune.WORKLOADS[name](cases)
+        members = work if isinstance(work, list) else [work]
+        for storage in ("f32", "f16"):
+            nodes = sum(c.N for c in members)
+            k = autotune.key(members[0].dim, storage, nodes)
+            assert k not in stood_for, (name, stood_for[k])
+            stood_for[k] = name
+            e = table[k]
+            times = {int(c): t for c, t in e["ms_per_step"].items()}
+            same = {int(c): v for c, v in e["identical"].items()}
+            assert sorted(times) == list(range(n_cfg[members[0].dim])) and all(same[c] for c in times), k
+            above = table.get(autotune.larger_class(members[0].dim, storage, nodes))
+            assert e["best"] == autotune.pick(times, same, above and above["best"]), k
+            assert e["fluid_nodes"] == sum(c.fluid_nodes for c in members), k
+    assert sorted(stood_for) == sorted(table)
+
+
+def test_pick():
+    """The fastest, unless the larger class's pick is within 2%; never one
+    whose state differs."""
+    t, ok = {0: 1.0, 1: 0.50, 2: 0.505, 3: 0.4}, {0: True, 1: True, 2: True, 3: False}
+    assert autotune.pick(t, ok) == 1
+    assert autotune.pick(t, ok, prefer=2) == 2
+    assert autotune.pick(t, ok, prefer=0) == 1
+    assert autotune.pick(t, ok, prefer=3) == 1
