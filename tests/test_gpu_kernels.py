@@ -301,3 +301,45 @@ def test_moments_edges(shape, walls, storage):
         assert (np.abs(rho - ro)[:, fluid] / scale).max() < 2 * TOL[storage]
         assert np.abs(u - uo)[:, fluid].max() < 4 * TOL[storage]
         assert np.array_equal(g.moments()[0], rho) and np.array_equal(g.moments()[1], u)
+
+
+@pytest.mark.parametrize("storage,nz", [("f32", 70), ("f16", 140)])
+@pytest.mark.parametrize("walls", [False, True])
+def test_large_domain_reversed(storage, nz, walls):
+    """As test_large_domain_order with a two-pass tile: only the two-pass node
+    update takes its items last to first, and only beyond the 256 MiB of the
+    last level cache.  A batch never does.  Equal to the bit."""
+    from paper_2512_12934_amd.lbm import LBM, Batch, tile_config_desc
+    c = cases.random_box((300, 90, nz), seed=3, dim=3, periodic=(not walls,) * 3, walls=walls, u_amp=0.01)
+    assert 2 * 19 * c.N * (4 if storage == "f32" else 2) > 256 << 20
+    for cfg in (8, 11):
+        assert tile_config_desc(3, cfg)["psrc"] == 1
+        print(f"[gpu] {c.n} {storage} walls={walls} tile {cfg}", flush=True)
+        g, b = LBM(c, storage=storage, tile_config=cfg), Batch([c], storage=storage, tile_config=cfg)
+        g.step(2)
+        b.step(2)
+        assert np.array_equal(g.get_state(), b.members[0].get_state())
+
+
+@pytest.mark.parametrize("storage", ["f32", "f16"])
+@pytest.mark.parametrize("shape,walls", RINGS)
+def test_moments_of_the_held_state(shape, walls, storage):
+    """rho and u against the oracle on the state that the GPU holds, so that no
+    rounding of storage is left to cover: a density is a sum of Q values
+    rounded to 2^-24 (19 * 6e-8 of it), a velocity two such sums of signed
+    values and a force whose 92 differences of densities carry weights that
+    add up to less than 2: below 1e-5 of u's unit with G = 0.9."""
+    from paper_2512_12934_amd.lbm import LBM
+    dim = 2 if shape[2] == 1 else 3
+    c = cases.random_box(shape, seed=sum(shape), dim=dim, periodic=(not walls,) * 3, walls=walls, u_amp=0.01,
+                         Gw=(0.05, -0.05) if walls else (0.0, 0.0))
+    fluid = c.solid == 0
+    g, s = LBM(c, storage=storage), oracle.Sim(c)
+    print(f"[gpu] moments of the held state {shape} walls={walls} {storage}", flush=True)
+    for steps in (0, 2):
+        g.step(steps)
+        s.set_f(g.get_state())
+        ro, uo, _ = s.moments()
+        rho, u = g.moments()
+        assert (np.abs(rho - ro)[:, fluid] / ro[:, fluid].sum(axis=0)).max() < 2e-6
+        assert np.abs(u - uo)[:, fluid].max() < 1e-5
