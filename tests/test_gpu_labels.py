@@ -211,3 +211,33 @@ def test_many_components():
     print("[gpu] us per call", {k: round(v, 1) for k, v in cost.items()}, flush=True)
     for static in (False, True):
         assert cost[2048, static] < 3.0 * cost[32, static]
+
+
+@pytest.mark.parametrize("storage", ["f32", "f16"])
+@pytest.mark.parametrize("name,k,make", [
+    ("tjunction", 0, lambda: cases.tjunction(W=20, length=90, x_side=30, side_width=14, side_len=18)),
+    # (starts full of component 1)
+    ("coflow", 1, lambda: cases.coflow3d(length=40, width=10, inner=4)),
+], ids=["2d", "3d"])
+def test_labels_between_steps_of_open_domains(name, k, make, storage):
+    """Labelling uses the population array that the next step writes, padding
+    slots of the open faces among it.  Runs labelled after every few steps, in
+    a context and as members of a batch, keep the bits of a run that is not."""
+    from paper_2512_12934_amd.lbm import LBM, Batch
+    c = make()
+    print(f"[gpu] labels between steps {name} {c.n} storage={storage}", flush=True)
+    thr = labels.threshold(c)
+    plain, looked = LBM(c, storage=storage), LBM(c, storage=storage)
+    b = Batch([c, c], storage=storage)
+    for steps in (1, 2, 1, 16, 3):          # both parities of the arrays, launches and a graph
+        plain.step(steps)
+        looked.step(steps)
+        b.step(steps)
+        want = looked.components(k, (0, 0, 0), c.n, thr)
+        assert want[1] > 0
+        for s in (b.members[1], looked):
+            assert s.components(k, (0, 0, 0), c.n, thr) == want
+            assert s.components(k, (1, 1, 0), (c.n[0] - 1, c.n[1] - 1, c.n[2]), -1.0)[1] > 0
+    want = plain.get_state(), plain.mass_flux()
+    for s in (looked, b.members[0], b.members[1]):
+        assert np.array_equal(s.get_state(), want[0]) and s.mass_flux() == want[1]
