@@ -1077,28 +1077,6 @@ __global__ __launch_bounds__(256) void k_psi(const typename Codec<STORE>::T *__r
     psi_body<DIM, STORE>(((S / G) * 8 + r) * G + S % G, src, type, g, psi, ref);
 }
 
-// Density and momentum of the populations of one component.  The momentum is
-// summed over opposite pairs, f_i - f_opp(i) first: the two are close, so
-// their difference is exact and the small differences add with little
-// rounding (the velocity is a small difference of large populations).
-template <int DIM>
-__device__ __forceinline__ void moments_of(const float (&f)[Lat<DIM>::Q], float &rho, float (&J)[3])
-{
-    rho = 0.0f;
-    static_for<Lat<DIM>::Q>([&](auto ic) { rho += f[decltype(ic)::value]; });
-    static_for<3>([&](auto dc) {
-        constexpr int d = decltype(dc)::value;
-        float acc = 0.0f;
-        static_for<Pairs<DIM>::P>([&](auto pc) {
-            constexpr int i = Pairs<DIM>::first(decltype(pc)::value);
-            constexpr int e = Lat<DIM>::E[i][d];
-            if constexpr (e == 1) acc += f[i] - f[Lat<DIM>::OPP[i]];
-            else if constexpr (e == -1) acc -= f[i] - f[Lat<DIM>::OPP[i]];
-        });
-        J[d] = acc;
-    });
-}
-
 // ---------------------------------------------------------------------------
 // k_moments: rho_k and the common velocity of eqs. (7)-(8) (with this
 // state's force, before any outlet override) of every node: the node update's

@@ -191,6 +191,9 @@ __device__ __forceinline__ void to_pairs(const float (&f)[Lat<DIM>::Q], PairF<DI
     });
 }
 
+// The momentum from the differences of opposite populations: the two are
+// close, so their difference is exact and the small differences add with
+// little rounding (the velocity is a small difference of large populations).
 template <int DIM>
 __device__ __forceinline__ void pair_momentum(const PairF<DIM> &q, float (&J)[3])
 {

@@ -64,7 +64,6 @@ struct Maps {
     bool moving = false;
     std::vector<InletRec> in;
     std::vector<OutletRec> out;
-    int n_xp = 0;                  // fluid x_{N-1} nodes (slots n_in .. n_in + n_xp)
     bool uc_neighbours = true;         // x' streams from its outlet node and that one's neighbours in record order only
     bool inlet_pulls_outlet = false;   // an inlet node x1 or x2 streams from an outlet node
 };
@@ -385,16 +384,12 @@ std::string build_maps(const lbm_config *c, Maps &m)
         }
     }
     // face slots: the inlet nodes in record order, then the fluid x_{N-1}
-    // nodes in outlet record order (so the eq. 23 sums read two contiguous
-    // ranges in a fixed order), then every other role node in box order
+    // nodes in outlet record order (neighbouring waves of the face kernels
+    // then read neighbouring slots), then every other role node in box order
     int32_t slot = 0;
     for (auto &r : m.in) m.bslot[r.b1] = slot++;
-    m.n_xp = 0;
     for (auto &r : m.out)
-        if (r.bP >= 0 && m.bslot[r.bP] < 0) {
-            m.bslot[r.bP] = slot++;
-            m.n_xp++;
-        }
+        if (r.bP >= 0 && m.bslot[r.bP] < 0) m.bslot[r.bP] = slot++;
     for (int64_t b = 0; b < N; b++)
         if ((m.type[b] & (T_ROLE | T_MOVWALL)) && m.bslot[b] < 0) m.bslot[b] = slot++;
     for (int64_t b = 0; b < N; b++)
@@ -1091,7 +1086,6 @@ lbm_status create_ctx(const lbm_config *cfg, void *dev_ws, size_t ws_bytes, void
     bd.in = (const InletRec *)(ws + L.o_in);
     bd.out = (const OutletRec *)(ws + L.o_out);
     bd.bslot = (const int *)(ws + L.o_bslot);
-    bd.n_xp = m.n_xp;
     bd.faceF = (float *)(ws + L.o_faceF);
     bd.faceU = (float *)(ws + L.o_faceU);
     bd.qacc = (unsigned long long *)(ws + L.o_qacc);

@@ -90,8 +90,6 @@ struct Boundary {
     int uc_early;             // eq. (21) summed in the outlet collision's launch (see UcMap)
     uint64_t out_enter;       // byte m: lane of the m-th direction entering through the outlet
     const int *bslot;         // [N] face-buffer slot of role nodes, -1 elsewhere
-    int n_xp;                 // fluid x_{N-1} nodes; face slots [0, n_in) are the inlet nodes and
-                              // [n_in, n_in + n_xp) the x_{N-1} nodes, both in record order
     float *faceF;             // [slots][2][3] force of this step at role nodes
     float *faceU;             // [slots] normal velocity at x' (outward)
     // [2 parities][2] the eq. 23 sums Q_in and Q' of a step as integers in
