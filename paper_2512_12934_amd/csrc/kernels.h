@@ -9,7 +9,9 @@
 //     f_i(x, t+1) = padding slot at x - e_i if that lies beyond an open face
 // Two arrays alternate between source and destination every step.
 //
-// One step is four (fused mode) or five (two-pass mode) launches:
+// The launches of one step.  A closed domain takes one (fused mode) or two
+// (two-pass mode), an open one at most five; k_inlet is left out where nothing
+// remains for it, so an open 2-D step in the fused mode is usually three:
 //   k_psi            (two-pass mode) psi_k = rho_k of every node into an array
 //   k_main           all fluid nodes, swept along the last axis: densities of
 //                    each plane plus a two-node lateral halo into an LDS ring
@@ -22,10 +24,11 @@
 //   k_faces          chi = Q_in / Q' (eq. 23) and the collision of the outlet
 //                    column with the corrected normal velocity (eq. 22); the
 //                    inlet nodes too when none of them pulls from the outlet
-//                    column
+//                    column; in 2-D the partial sums of eq. (21) too where the
+//                    face's order allows it (UcMap)
 //   k_inlet          alpha-corrected NEQ extrapolation (eqs. 13-19) into the
 //                    padding slots (the inlet nodes k_faces did not take);
-//                    partial sums of eq. (21)
+//                    the partial sums of eq. (21) that k_faces did not take
 //   k_outlet_fill    convective outflow (eq. 20) into the padding slots
 #pragma once
 
@@ -444,9 +447,9 @@ __device__ __forceinline__ double flow_unfix(unsigned long long v) { return (dou
 // iteration and keeps psi of the planes it needs (window plus two on each
 // side) in an LDS ring of W + 4 planes, so psi is computed once per plane and
 // only the lateral two-node halo is recomputed by neighbouring blocks.
-// Work items are ordered lateral-x fastest, then lateral-y, then chunk, and
-// each of the eight XCDs takes a contiguous range of them, so the blocks that
-// share halo data share an L2.
+// Work items are ordered lateral-x fastest, then lateral-y, then chunk, or in
+// square blocks of tiles (see xcd_group); each of the eight XCDs takes a few
+// consecutive ones per turn, so that blocks which share halo data share an L2.
 // ---------------------------------------------------------------------------
 //
 // PSRC selects where psi comes from: 0 = recomputed here from the gathered
@@ -999,8 +1002,9 @@ __device__ __forceinline__ void main_item(const typename Codec<STORE>::T *__rest
     }
 }
 
-// One context: one block per work item (tiles that hold fluid, in tile
-// order).
+// One context: one block per work item (tiles that hold fluid, in the order
+// of the work list or, for populations beyond the last level cache, against
+// it).
 // Binary16 storage asks for four waves per SIMD (128 VGPRs): its 64x4 tile
 // then runs at occupancy 4 instead of 3 without spilling, 2.4% faster; FP32
 // gains nothing from the request and takes what it needs.

@@ -17,7 +17,9 @@ struct TileCfg {
     int psrc, tx, ty, w, zc, keepb;
 };
 
-// The tuning space.  Entry 0 is the default when no measured choice exists.
+// The tuning space.  Where the caller names no entry, the domain's size picks
+// one (default_cfg); entry 0 is the one that others are compared with, bit for
+// bit.
 constexpr TileCfg CFG2[] = {
     {1, 64, 1, 4, 16, 1},
     {1, 64, 1, 4, 32, 1},

@@ -157,7 +157,14 @@ constexpr int xcd_group(int dim, int psrc, bool one_window)
 // one block per turn fetched into two L2s (binary16, with 64 populations a
 // line, read 1.28 times the populations of the 600x120x120 device, now 1.10;
 // FP32 1.16, now 1.06).  300x60x60 binary16 23.0 -> 20.1 us, 250x51x51 15.7
-// -> 14.1, FP32 and larger domains within 1%; 4 and 64 blocks are no better.
+// -> 14.1, 400x90x90 65.5 -> 64.4, 600x120x120 188 -> 185.5; FP32 up to 1%; 4
+// and 64 blocks are no better.
+//
+// On the 600x120x120 device the binary16 pass takes longer the sooner the node
+// update before it is done: after node updates of 488, 388, 372 and 357 us
+// (older kernels, other tiles) it took 176, 180, 182 and 185.5 us, with its
+// own code and address forms old or new alike.  Presumably it shares memory
+// with the write-back of what the node update stored.
 constexpr int PSI_GROUP = 16;
 
 // One member of a batch: what a single context passes to its step kernels.
