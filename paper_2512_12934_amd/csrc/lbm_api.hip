@@ -1023,16 +1023,6 @@ lbm_status create_ctx(const lbm_config *cfg, void *dev_ws, size_t ws_bytes, void
     c->ws = (char *)dev_ws;
     c->stream = (hipStream_t)hip_stream;
     c->pin = pin;
-    if (!pin) {
-        void *p = nullptr;
-        if (hipHostMalloc(&p, PIN_BYTES, hipHostMallocDefault) != hipSuccess) {
-            (void)hipGetLastError();
-            delete c;
-            return fail(nullptr, LBM_ENOMEM, "no pinned host memory");
-        }
-        c->pin = (char *)p;
-        c->own_pin = true;
-    }
     if (hipGetDevice(&c->device) != hipSuccess) {
         delete c;
         return fail(nullptr, LBM_EDEVICE, "hipGetDevice failed");
@@ -1045,6 +1035,17 @@ lbm_status create_ctx(const lbm_config *cfg, void *dev_ws, size_t ws_bytes, void
             delete c;
             return fail(nullptr, LBM_EDEVICE, why);
         }
+    }
+    if (!pin) {
+        void *p = nullptr;
+        const hipError_t e = hipHostMalloc(&p, PIN_BYTES, hipHostMallocDefault);
+        if (e != hipSuccess) {
+            (void)hipGetLastError();
+            delete c;
+            return fail(nullptr, LBM_EDEVICE, std::string("pinned host memory: ") + hipGetErrorString(e));
+        }
+        c->pin = (char *)p;
+        c->own_pin = true;
     }
 
     // relaxation rates (eqs. 4-5, Sec. III A)
@@ -1493,11 +1494,12 @@ lbm_status lbm_batch_create(const lbm_config *cfgs, int n, void *dev_ws, size_t 
     b->stream = (hipStream_t)hip_stream;
     b->dim = mc[0].dim;
     b->storage = mc[0].storage;
-    if (hipHostMalloc(&b->pin, (size_t)n * PIN_BYTES, hipHostMallocDefault) != hipSuccess) {
+    const hipError_t e = hipHostMalloc(&b->pin, (size_t)n * PIN_BYTES, hipHostMallocDefault);
+    if (e != hipSuccess) {
         (void)hipGetLastError();
         b->pin = nullptr;
         delete b;
-        return bfail(nullptr, LBM_ENOMEM, "no pinned host memory");
+        return bfail(nullptr, LBM_EDEVICE, std::string("pinned host memory: ") + hipGetErrorString(e));
     }
     char *ws = (char *)dev_ws;
     size_t off = 0;

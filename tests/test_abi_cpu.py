@@ -144,3 +144,23 @@ def test_stream_probe_rejects_bad_arguments(lib):
     assert call(38 * 4 * 128 * 128 * 19, 4) == LBM_EINVAL
     assert call(1 << 31, 5) == LBM_EINVAL            # beyond 32-bit buffer offsets
     assert pl.lbm_stream_probe(None, fake, C.c_size_t(1 << 20), 0, 1, None, C.byref(r)) == LBM_EINVAL
+
+
+def test_create_without_a_device_is_a_device_error(lib):
+    """With no GPU in the machine a valid configuration and workspace fail on
+    the device, not for want of memory, for a context and for a batch."""
+    import torch
+    if torch.cuda.is_available() or os.path.exists("/dev/kfd"):
+        pytest.skip("the machine has a GPU, which must not be given this host memory")
+    from paper_2512_12934_amd import cases
+    from paper_2512_12934_amd.lbm import LBM_EDEVICE, Config, make_config
+    cfg, keep = make_config(cases.laplace(n=16, R=4.0))
+    one = (Config * 1)(cfg)
+    for need, create, args, error in [
+            (lib.lbm_workspace_bytes(C.byref(cfg)), lib.lbm_create, (C.byref(cfg),), lib.lbm_last_error),
+            (lib.lbm_batch_workspace_bytes(one, 1), lib.lbm_batch_create, (one, 1), lib.lbm_batch_last_error)]:
+        buf = np.zeros(need + 256, np.uint8)
+        ws = (buf.ctypes.data + 255) // 256 * 256
+        h = C.c_void_p()
+        st = create(*args, C.c_void_p(ws), need, None, C.byref(h))
+        assert st == LBM_EDEVICE and h.value is None, error(None)
