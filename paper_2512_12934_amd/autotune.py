@@ -31,8 +31,8 @@ TABLE = os.path.join(HERE, "tuning.json")
 # with the domain, from 16 rows or 4 planes where the halo it re-reads is what
 # costs, to one pass of a block where too few items would leave CUs idle; the
 # classes end where the measured picks of either lattice change.
-CLASSES = ((100_000, "100k"), (250_000, "250k"), (1_000_000, "1M"), (3_000_000, "3M"), (5_000_000, "5M"),
-           (16_000_000, "16M"))
+CLASSES = ((100_000, "100k"), (250_000, "250k"), (450_000, "450k"), (1_000_000, "1M"), (3_000_000, "3M"),
+           (5_000_000, "5M"), (16_000_000, "16M"))
 
 
 def size_class(nodes: int) -> str:
@@ -71,6 +71,54 @@ def lookup(dim: int, storage: str, nodes: int) -> int:
     # the reference-density form's tuning
     entry = _table().get(key(dim, "f16" if storage == "f16fixed" else storage, nodes))
     return int(entry["best"]) if entry else -1
+
+
+# Domains whose fluid fills 64-wide tiles badly: the lanes of the 64-wide tiles
+# that hold fluid, over those of the 32-wide ones.  From NARROW on (a channel 70
+# wide fills half of its second tile) the latter are faster: node updates with
+# 64 / 32 columns 97x5000 FP32 28.9 / 26.1 us, 16x200x200 129 / 107, 70x70x70
+# binary16 51 / 39; below it, 130x4000 32.6 / 33.2, 130x60x60 56.0 / 55.6.  From
+# ONE_TILE on (a single 32-wide tile across) the fused 2-D mode, whose halo
+# columns then hold little, beats the two-pass one: 33x8000 14.9 / 16.4, 33x40000
+# 55.5 / 65.2; below it, 65x5000 26.1 / 22.8.
+NARROW, ONE_TILE = 1.25, 1.75
+
+
+def lane_ratio(members, layout="caller") -> float:
+    """Lanes in 64-wide tiles over lanes in 32-wide tiles, of one domain or of
+    a batch (1.0 where there is no fluid)."""
+    import numpy as np
+    lanes = {32: 0, 64: 0}
+    for c in members:
+        faces = [c.outlet] if c.outlet is not None else c.inlets
+        turned = layout == "face_last" and c.dim == 3 and len(faces) > 0 and faces[0]["axis"] == 0
+        x = 1 if turned else 0              # the caller's axis that is contiguous in memory
+        nz, ny, nx = (c.n[2] if c.dim == 3 else 1), c.n[1], c.n[0]
+        fluid = (np.asarray(c.solid).reshape(nz, ny, nx) == 0).any(axis=tuple(a for a in range(3) if a != 2 - x))
+        for w in lanes:
+            tiles = np.add.reduceat(fluid, np.arange(0, len(fluid), w)) > 0
+            lanes[w] += int(tiles.sum()) * w * (c.N // c.n[x])
+    return lanes[64] / lanes[32] if lanes[32] else 1.0
+
+
+def choose(members, storage: str, layout="caller") -> int:
+    """The tile that tile_config="auto" stands for: the class's pick, or for
+    narrow domains the class's fastest of at most 32 columns."""
+    from .lbm import tile_config_desc, tile_configs
+    dim, nodes = members[0].dim, sum(c.N for c in members)
+    best = lookup(dim, storage, nodes)
+    if best < 0:
+        return best
+    desc = {c: tile_config_desc(dim, c) for c in range(tile_configs(dim))}
+    if desc[best]["tx"] <= 32 and (dim == 3 or desc[best]["psrc"] == 0):
+        return best
+    ratio = lane_ratio(members, layout)
+    if ratio < (NARROW if desc[best]["tx"] > 32 else ONE_TILE):
+        return best
+    entry = _table()[key(dim, "f16" if storage == "f16fixed" else storage, nodes)]
+    fits = lambda d: d["tx"] <= 32 and (dim == 3 or ratio < ONE_TILE or d["psrc"] == 0)
+    times = {int(c): t for c, t in entry["ms_per_step"].items() if entry["identical"][c] and fits(desc[int(c)])}
+    return min(times, key=times.get) if times else best
 
 
 def pick(times: dict, identical: dict, prefer=None):
@@ -138,6 +186,7 @@ WORKLOADS = {
     "taylor": lambda c: c.taylor(5.0, 0.05, nx=320, H=160, R=32.0),
     "tjunction": lambda c: c.tjunction(),
     "tjunction_small": lambda c: c.tjunction(W=32, length=256, x_side=48, side_width=32, side_len=32),
+    "droplet_540": lambda c: c.laplace(n=540, R=135.0),
     "droplet_900": lambda c: c.laplace(n=900, R=225.0),
     "tjunction_W256": lambda c: c.sweep_case(256, 0.03, 0.5, 1.0),
     # the sweep geometry at W = 512 (2.4M fluid nodes)
@@ -158,8 +207,9 @@ WORKLOADS = {
 # The one that stands for each size class of the table, larger classes first
 # (a pick depends on the next larger one's).  3-D domains beyond 16M nodes have
 # none and take the library's choice.
-TABLE_WORKLOADS = ("sweep_256", "sweep_64", "tjunction_W512", "tjunction_W256", "droplet_900", "tjunction", "taylor",
-                   "coflow3d", "coflow3d_400", "coflow3d_half", "channel3d_250", "coflow3d_quarter", "coflow3d_80")
+TABLE_WORKLOADS = ("sweep_256", "sweep_64", "tjunction_W512", "tjunction_W256", "droplet_900", "droplet_540",
+                   "tjunction", "taylor", "coflow3d", "coflow3d_400", "coflow3d_half", "channel3d_250", "coflow3d_200",
+                   "coflow3d_quarter", "coflow3d_80")
 
 
 def main(argv=None):

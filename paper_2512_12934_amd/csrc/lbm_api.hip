@@ -445,13 +445,51 @@ std::string build_maps(const lbm_config *c, Maps &m)
 // 64x64 box FP32 15.7 / 5.9, 320x160 17.4 / 7.5, 150x30x30 103 / 35.7,
 // 250x51x51 binary16 149 / 69.5 (32x8 with two planes 70.1), 300x60x60
 // binary16 160 / 94, 600x120x120 FP32 963 / 896.
-int default_cfg(int dim, int storage, int64_t nodes)
+//
+// ratio: the lanes of the 64-wide tiles that hold fluid over those of the
+// 32-wide ones (see Lanes).  From 1.25 on (a channel 70 wide fills half of its
+// second tile) the latter are faster: us per step, 64 / 32 columns, 97x5000
+// FP32 28.9 / 26.1, 16x200x200 129 / 107, 70x70x70 binary16 51 / 39; below it,
+// 130x4000 32.6 / 33.2, 130x60x60 56.0 / 55.6.  From 1.75 on (a single 32-wide
+// tile across) the fused 2-D tile, whose halo columns then hold little, beats
+// the two-pass one: 33x8000 14.9 / 16.4, 33x40000 55.5 / 65.2; below it,
+// 65x5000 26.1 / 22.8.
+int default_cfg(int dim, int storage, int64_t nodes, double ratio)
 {
-    const bool f32 = storage == LBM_STORE_F32;
-    if (dim == 2) return f32 ? (nodes < 250000 ? 10 : 11) : (nodes < 5000000 ? 10 : (nodes < 16000000 ? 11 : 4));
+    const bool f32 = storage == LBM_STORE_F32, narrow = ratio >= 1.25;
+    if (dim == 2) {
+        if (f32 && nodes >= 250000 && nodes < (narrow ? 1000000 : 450000) && ratio < 1.75) return 8;
+        if (narrow || nodes < (f32 ? 250000 : 5000000)) return 10;
+        return f32 || nodes < 16000000 ? 11 : 4;
+    }
     if (nodes < 250000) return 10;
+    if (narrow) return 9;
     return f32 || nodes < 3000000 ? 11 : 8;
 }
+
+// Lanes of the x-tiles that hold fluid, 32 and 64 columns wide, summed over
+// the rows of one or more domains (memory frame).
+struct Lanes {
+    double of32 = 0, of64 = 0;
+    void add(const lbm_config *c)
+    {
+        const int nx = c->n[0];
+        const int64_t rows = (int64_t)c->n[1] * (c->dim == 3 ? c->n[2] : 1);
+        std::vector<uint8_t> fluid(nx, 0);
+        for (int64_t r = 0; r < rows; r++)
+            for (int x = 0; x < nx; x++) fluid[x] |= c->solid[r * nx + x] == 0;
+        auto held = [&](int w) {
+            int n = 0;
+            for (int x0 = 0; x0 < nx; x0 += w)
+                n += std::find(fluid.begin() + x0, fluid.begin() + std::min(x0 + w, nx), 1) !=
+                     fluid.begin() + std::min(x0 + w, nx);
+            return (double)n * w * (double)rows;
+        };
+        of32 += held(32);
+        of64 += held(64);
+    }
+    double ratio() const { return of32 > 0 ? of64 / of32 : 1.0; }
+};
 
 // Fills the records' padded indices and the slot tables of the face kernels.
 template <int DIM>
@@ -562,7 +600,12 @@ Layout make_layout(const Canon &k, const Maps &m)
             }
         }
     }
-    L.cfg = c->tile_config >= 0 ? c->tile_config : default_cfg(c->dim, c->storage, g.N);
+    L.cfg = c->tile_config;
+    if (L.cfg < 0) {
+        Lanes lanes;
+        lanes.add(c);
+        L.cfg = default_cfg(c->dim, c->storage, g.N, lanes.ratio());
+    }
     const TileCfg &tc = tile_cfg(c->dim, L.cfg);
     L.psi_mode = tc.psrc;
     if (c->dim == 2) {
@@ -1398,10 +1441,16 @@ std::string batch_plan(const lbm_config *cfgs, int n, std::vector<lbm_config> &m
     bytes.assign(n, 0);
     int cfg = cfgs[0].tile_config;
     if (cfg == -1) {                                   // one for all members, by their total
-        double nodes = 0;                              // sizes are checked below
-        for (int i = 0; i < n; i++) nodes += (double)cfgs[i].n[0] * cfgs[i].n[1] * (cfgs[i].dim == 3 ? cfgs[i].n[2] : 1);
+        double nodes = 0;
+        Lanes lanes;
+        for (int i = 0; i < n; i++) {
+            Canon k;
+            if (!canonicalize(&cfgs[i], k).empty()) continue;   // reported below
+            nodes += (double)k.c.n[0] * k.c.n[1] * k.c.n[2];
+            lanes.add(&k.c);
+        }
         if (cfgs[0].dim == 2 || cfgs[0].dim == 3)
-            cfg = default_cfg(cfgs[0].dim, cfgs[0].storage, (int64_t)std::min(nodes, 1e15));
+            cfg = default_cfg(cfgs[0].dim, cfgs[0].storage, (int64_t)std::min(nodes, 1e15), lanes.ratio());
     }
     total = 0;
     int64_t items = 0;

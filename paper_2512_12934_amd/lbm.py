@@ -240,11 +240,11 @@ def tile_config_desc(dim, i):
     return dict(zip(("psrc", "tx", "ty", "w", "zc", "keepb"), list(out)))
 
 
-def resolve_tile_config(case, storage, tile_config):
+def resolve_tile_config(case, storage, tile_config, layout="caller"):
     """'auto' looks the lattice / storage / size class up in the autotuner table."""
     if tile_config == "auto":
-        from .autotune import lookup
-        return lookup(case.dim, storage, case.N)
+        from .autotune import choose
+        return choose([case], storage, layout)
     return int(tile_config)
 
 
@@ -264,7 +264,7 @@ class LBM:
         self.Q = 9 if case.dim == 2 else 19
         self.N = int(np.prod(case.n))
         self.device = torch.device(device)
-        self.tile_config = resolve_tile_config(case, storage, tile_config)
+        self.tile_config = resolve_tile_config(case, storage, tile_config, layout)
         cfg, keep = make_config(case, storage, self.tile_config, layout)
         nbytes = int(L.lbm_workspace_bytes(C.byref(cfg)))
         if nbytes == 0:
@@ -394,8 +394,8 @@ class Batch:
         if tile_config == "auto" and n:
             # the tuned configuration of the lattice and storage for the
             # batch's total size
-            from .autotune import lookup
-            self.tile_config = lookup(self.cases[0].dim, storage, sum(c.N for c in self.cases))
+            from .autotune import choose
+            self.tile_config = choose(self.cases, storage)
         else:
             self.tile_config = resolve_tile_config(self.cases[0], storage, tile_config) if n else -1
         cfgs = (Config * n)()

@@ -2,6 +2,8 @@
 import json
 import os
 
+import numpy as np
+
 from paper_2512_12934_amd import autotune
 
 
@@ -77,3 +79,42 @@ def test_pick():
     assert autotune.pick(t, ok, prefer=2) == 2
     assert autotune.pick(t, ok, prefer=0) == 1
     assert autotune.pick(t, ok, prefer=3) == 1
+
+
+def test_narrow_domains_take_narrow_tiles():
+    """A 64-wide pick gives way to the class's fastest tile of at most 32
+    columns where the fluid fills 64-wide tiles badly, counted along the axis
+    that is contiguous in memory and over all members of a batch; a 2-D domain
+    of one such tile across takes the fused one."""
+    from paper_2512_12934_amd import cases
+    from paper_2512_12934_amd.lbm import tile_config_desc
+
+    def box(shape, walls):
+        return cases.random_box(shape, seed=3, dim=2 if shape[2] == 1 else 3, periodic=(not walls,) * 3, walls=walls)
+
+    for shape, walls, ratio in [((97, 8000, 1), True, 4 / 3), ((97, 8000, 1), False, 1.0),
+                                ((65, 12000, 1), False, 4 / 3), ((65, 12000, 1), True, 1.0),
+                                ((33, 40000, 1), True, 2.0), ((128, 6000, 1), False, 1.0),
+                                ((130, 6000, 1), False, 1.2), ((16, 200, 200), True, 2.0),
+                                ((70, 90, 90), False, 4 / 3), ((130, 60, 90), False, 1.2),
+                                ((200, 60, 60), True, 8 / 7), ((33, 8000, 1), True, 2.0), ((40, 8000, 1), True, 1.0)]:
+        c = box(shape, walls)
+        assert abs(autotune.lane_ratio([c]) - ratio) < 1e-12, (shape, walls)
+        for st in ("f32", "f16", "f16fixed"):
+            picked = autotune.lookup(c.dim, st, c.N)
+            was = tile_config_desc(c.dim, picked)
+            now = tile_config_desc(c.dim, autotune.choose([c], st))
+            if ratio < autotune.NARROW:
+                assert now == was
+            else:
+                assert now["tx"] == 32 and (was["tx"] == 64 or now == was or ratio >= autotune.ONE_TILE)
+            if c.dim == 2 and ratio >= autotune.ONE_TILE:
+                assert now["psrc"] == 0
+    assert autotune.lane_ratio([box((20, 30, 1), False).copy(solid=np.ones(600, np.uint8))]) == 1.0
+    # a wide member and a narrow one, by the rows of each
+    few, many = box((33, 40, 40), True), box((33, 400, 100), True)
+    assert autotune.lane_ratio([box((64, 400, 100), False), few]) < autotune.NARROW
+    assert autotune.lane_ratio([box((64, 20, 20), False), many]) > autotune.NARROW
+    # the caller's x leaves the front where the open faces go last
+    c = cases.coflow3d(length=200, width=68, inner=16)
+    assert autotune.lane_ratio([c]) < autotune.NARROW <= autotune.lane_ratio([c], "face_last")

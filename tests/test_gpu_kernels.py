@@ -343,3 +343,41 @@ def test_moments_of_the_held_state(shape, walls, storage):
         rho, u = g.moments()
         assert (np.abs(rho - ro)[:, fluid] / ro[:, fluid].sum(axis=0)).max() < 2e-6
         assert np.abs(u - uo)[:, fluid].max() < 1e-5
+
+
+# a 2-D class of its own (250 to 450 thousand nodes), and domains whose fluid
+# fills 64-wide tiles badly
+@pytest.mark.parametrize("storage", ["f32", "f16"])
+@pytest.mark.parametrize("shape,walls", [((1000, 300, 1), False), ((5000, 65, 1), True), ((33, 8000, 1), True),
+                                         ((33, 40000, 1), True), ((16, 200, 200), False), ((70, 70, 70), True)])
+def test_chosen_tile_is_near_the_fastest(shape, walls, storage):
+    """The tile that is taken where none is named, and by "auto", costs a step
+    at most 8% more than the fastest of the shallow ones (choices by class
+    were measured at one shape of each and are up to 6% off at others), and
+    gives its bits.  Each time is the least of five runs of 32 steps."""
+    import torch
+    from paper_2512_12934_amd.lbm import LBM
+    dim = 2 if shape[2] == 1 else 3
+    c = cases.random_box(shape, seed=3, dim=dim, periodic=(not walls,) * 3, walls=walls, u_amp=0.01)
+    print(f"[gpu] chosen tile {shape} walls={walls} {storage}", flush=True)
+    cost, states = {}, {}
+    for cfg in (-1, "auto", 8, 9, 10, 11):
+        g = LBM(c, storage=storage, tile_config=cfg)
+        g.set_graph_steps(16)
+        g.step(32)
+        best = float("inf")
+        for _ in range(5):
+            torch.cuda.synchronize()
+            a, b = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+            a.record()
+            g.step(32)
+            b.record()
+            torch.cuda.synchronize()
+            best = min(best, a.elapsed_time(b) / 32 * 1e3)
+        cost[cfg] = best
+        states[cfg] = g.get_state()
+    print("  us per step", {k: round(v, 1) for k, v in cost.items()}, flush=True)
+    fastest = min(cost[k] for k in (8, 9, 10, 11))
+    for cfg in (-1, "auto"):
+        assert cost[cfg] < 1.08 * fastest, cfg
+        assert np.array_equal(states[cfg], states[8])
